@@ -17,7 +17,7 @@
 // factors F, G kept for the back substitution in slots the host schedule
 // assigns) and a pool of 3M vectors [r | g | x].
 #include "mrcm_internal.h"
-#include "pivot4.h"
+#include "gj16.h"
 
 #include <type_traits>
 
@@ -25,212 +25,114 @@ namespace mrcm {
 namespace {
 
 // ------------------------------------------------------------------ inverse
-// In-place Gauss-Jordan inversion of one n x n block (n <= 128, n % 8 == 0)
-// per workgroup of 512 threads; thread (tr, tc) holds the 4 x 8 tile at rows
-// 4 tr.., columns 8 tc.. in registers.  Pivots are taken four at a time
-// (block Gauss-Jordan without pivoting): for the pivot rows and columns K,
-// with P = A[K][K],
-//   A[K][j] <- P^{-1} A[K][j],   A[i][K] <- -A[i][K] P^{-1},
-//   A[K][K] <- P^{-1},           A[i][j] <- A[i][j] - A[i][K] P^{-1} A[K][j],
-// which equals four scalar pivot steps.  Thread 16 tr + tc holds tile
-// (tr, tc), so a tile row is one row of 16 lanes of a wave.  The pivot rows
-// of a step are one tile row and the pivot columns half a tile column.  One
-// step, with R = P^{-1} A~[K][:] (A~ with unit vectors in the columns K)
-// already in LDS:
-//   1. every thread applies the rank-4 update A[i][j] <- A[i][j] -
-//      A[i][K] R[:, j] to its tile (zero base in the columns K) and the
-//      owners of rows K take R.  A[i][K] of a tile row is held by one lane
-//      of the same 16-lane row (the owner of the pivot columns), and row
-//      broadcasts hand it to the other 15: the columns never go through LDS;
-//   2. look-ahead: the wave that holds the next step's pivot rows runs its
-//      update at raised priority, publishes those rows to LDS, factors the
-//      next 4 x 4 pivot block (closed form, redundantly in every lane) and
-//      forms the next R, two columns per lane, while the other waves are
-//      still updating;
-//   3. one barrier.
-// R alternates between two LDS buffers.  It is stored in 16-byte pieces
-// interleaved over the tile columns so that the update reads are free of
-// bank conflicts.  Two waves per SIMD hide each other's LDS latency.
-constexpr int TR = 4, TC = 8, PB = 4;  // tile rows / columns; pivots per step
-constexpr int kInvThreads = 512;
-
-// cv[i][m] = w[i][K2 + m] of lane KT of this lane's row of 16 lanes
-template <int KT, int K2>
-__device__ __forceinline__ void bcast_cols(const double w[TR][TC], double cv[TR][PB]) {
-#pragma unroll
-  for (int i = 0; i < TR; ++i)
-#pragma unroll
-    for (int m = 0; m < PB; ++m) {
-      const long long u = __builtin_bit_cast(long long, w[i][K2 + m]);
-      const int lo = __builtin_amdgcn_mov_dpp((int)(u & 0xffffffffLL), 0x150 + KT, 0xF, 0xF, false);
-      const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), 0x150 + KT, 0xF, 0xF, false);
-      cv[i][m] = __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
-    }
-}
-
-template <int K2>
-__device__ __forceinline__ void bcast_cols(int kt, const double w[TR][TC], double cv[TR][PB]) {
-  switch (kt) {
-#define MRCM_BC(N) \
-  case N:          \
-    bcast_cols<N, K2>(w, cv); \
-    break;
-    MRCM_BC(0) MRCM_BC(1) MRCM_BC(2) MRCM_BC(3) MRCM_BC(4) MRCM_BC(5) MRCM_BC(6) MRCM_BC(7)
-    MRCM_BC(8) MRCM_BC(9) MRCM_BC(10) MRCM_BC(11) MRCM_BC(12) MRCM_BC(13) MRCM_BC(14) MRCM_BC(15)
-#undef MRCM_BC
-    default:
-      break;
-  }
-}
-
-// R = P^{-1} A~[K][:] of step st (pivots K = 4 st .. 4 st + 3, A~ with
-// unit vectors in the columns K), formed by the one wave that holds the
-// pivot rows (tile row st): its 16 lanes of that tile row publish the rows
-// to rp, then every lane of the wave forms two columns of R into rq (the
-// interleaved pieces the update reads).  Returns whether the pivot block
-// is unusable (zero, infinite or NaN pivot).
-__device__ __forceinline__ bool form_r(int st, int t, int tr, int bp, int ntc, int c0,
-                                       const double w[TR][TC], double* rp, double* rq) {
-  if (tr == st) {
-#pragma unroll
-    for (int m = 0; m < PB; ++m) {
-      double2* d = reinterpret_cast<double2*>(rp + m * kBcrInvMax + c0);
-#pragma unroll
-      for (int jj = 0; jj < TC / 2; ++jj) d[jj] = make_double2(w[m][2 * jj], w[m][2 * jj + 1]);
-    }
-  }
-  // the rows are read by other lanes of the same wave: LDS stores complete
-  // before the loads below
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-  const int k = st * PB;
-  double P[PB][PB];
-#pragma unroll
-  for (int m = 0; m < PB; ++m)
-#pragma unroll
-    for (int j = 0; j < PB; ++j) P[m][j] = rp[m * kBcrInvMax + k + j];
-  const PivBlock<double> q = piv_block(P);
-  const bool bad = !(piv_usable(q.d0) && piv_usable(q.da) && piv_usable(q.s0) && piv_usable(q.ds));
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int col = (t & 63) + 64 * h;
-    if (col < bp) {
-      const int ck = col - k;
-      const bool pc = ck >= 0 && ck < PB;
-      double r[PB], v[PB];
-      // unit vector in the pivot columns, formed arithmetically (a select
-      // on a load becomes a branch with its own LDS wait)
-#pragma unroll
-      for (int m = 0; m < PB; ++m)
-        r[m] = fma(rp[m * kBcrInvMax + col], pc ? 0.0 : 1.0, (pc && ck == m) ? 1.0 : 0.0);
-      piv_apply(q, r, v);
-      const int tq = col / TC, jj = (col % TC) / 2, e = col & 1;
-#pragma unroll
-      for (int m = 0; m < PB; ++m) rq[((m * (TC / 2) + jj) * ntc + tq) * 2 + e] = v[m];
-    }
-  }
-  return bad;
-}
-
-__global__ void __launch_bounds__(kInvThreads) k_bcr_inv(double* __restrict__ pool,
-                                                         const long long* __restrict__ offs,
-                                                         const int* __restrict__ npiv, int bp,
-                                                         int ld, int* flags) {
-  __shared__ __align__(16) double rpan[PB * kBcrInvMax];     // [m][col] = A[k + m][col]
-  __shared__ __align__(16) double rpp[2][PB * kBcrInvMax];   // R, interleaved pieces
+// In-place Gauss-Jordan inversion of one n x n block (n = 16 NW <= 128) per
+// workgroup of NW waves, 16 pivots per step, no pivoting.  Wave v holds rows 16 v .. 16 v + 15 as NW 16 x 16
+// tiles in the accumulator layout of the FP64 matrix instructions.  Step p,
+// with P the pivot block, R the pivot rows and C a wave's pivot columns:
+//   P <- P^{-1},  R <- P^{-1} R,  C <- -C P^{-1},  A <- A - C P^{-1} R.
+// The old pivot rows are in LDS in operand B's layout (the accumulators as
+// they are), P^{-1} in LDS too, so a wave needs only its own pivot-column
+// tile transposed (through LDS, within the wave): -(C P^{-1})^T, formed as
+// a product, comes out in operand A's layout.  Look-ahead: the wave that
+// holds the next pivot rows updates the next pivot block first, inverts it
+// in registers while the other waves update, and publishes it and its rows;
+// one barrier per 16 pivots.  The tiles rotate by one slot per step (slot i
+// holds column block p + i), so the step is one loop body: a body unrolled
+// per step would not stay in the instruction cache.
+//
+// Bound: FP64 matrix instructions of one CU (2 n^3 flop: 14 us for n = 128
+// at 128 flop per cycle) plus, on the SIMD of the wave that looks ahead, the
+// pivot block's inversion, which uses the same FP64 units (8600 cycles per
+// step there, 5000 on the other SIMDs).  Measured per launch, against four
+// pivots per step on the vector unit with two to one barriers: n = 128
+// 50.5 -> 30.9 us, n = 96 with 66 pivots 30.7 -> 16.5 us, n = 32 7.7 ->
+// 4.2 us.  Matrix instructions interleaved with the inversion's pivots were
+// no faster (34 us): a wave's vector instructions wait for them.
+template <int NW>
+__global__ void __launch_bounds__(64 * NW) k_bcr_inv(double* __restrict__ pool,
+                                                     const long long* __restrict__ offs,
+                                                     const int* __restrict__ npiv, int ld, int* flags) {
+  __shared__ __align__(16) double rb[2][NW * 256];      // pivot rows, operand B's layout
+  __shared__ __align__(16) double pq[2][kTile];      // inverse of the pivot block
+  __shared__ __align__(16) double tw[NW][kTile];     // per wave: transposition
   double* A = pool + offs[blockIdx.x];
-  const int ntr = bp / TR, ntc = bp / TC;  // tiles per column / per row
-  const int t = threadIdx.x;
-  const int tr = t >> 4, tc = t & 15;
-  const bool act = tr < ntr && tc < ntc;
-  const int r0 = tr * TR, c0 = tc * TC;
-  double w[TR][TC];
+  const int l = threadIdx.x & 63, lc = l & 15, lg = l >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // pivots beyond the block's own size act on identity padding, which they
+  // leave unchanged: skipped
+  const int np = min((npiv[blockIdx.x] + 15) / 16, NW);
+  dbl4 T[NW];
 #pragma unroll
-  for (int i = 0; i < TR; ++i)
+  for (int i = 0; i < NW; ++i)
 #pragma unroll
-    for (int j = 0; j < TC; ++j) w[i][j] = 0.0;
-  if (act) {
-#pragma unroll
-    for (int i = 0; i < TR; ++i) {
-      const double2* src = reinterpret_cast<const double2*>(A + (long long)(r0 + i) * ld + c0);
-#pragma unroll
-      for (int jj = 0; jj < TC / 2; ++jj) {
-        const double2 u = src[jj];
-        w[i][2 * jj] = u.x;
-        w[i][2 * jj + 1] = u.y;
-      }
-    }
-  }
-  // pivots beyond the block's own size act on identity padding, which
-  // they leave unchanged: skipped
-  const int kend = npiv[blockIdx.x];
-  const int nstep = (kend + PB - 1) / PB;
-  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);  // holds tile rows 4 wv .. 4 wv + 3
+    for (int r = 0; r < 4; ++r) T[i][r] = A[(long long)(16 * wv + 4 * r + lg) * ld + 16 * i + lc];
   bool bad = false;
-  if (nstep > 0 && wv == 0) bad |= form_r(0, t, tr, bp, ntc, c0, w, rpan, rpp[0]);
+  double* mine = tw[wv];
+  // inverse of the pivot block in tile t, published for step st
+  auto invert = [&](const dbl4& t, int st) {
+    double a[16];
+    tile_put(mine, t);
+    wave_lds_sync();
+    tile_get_rows(mine, a);
+    inv16<false>(a, bad);
+    tile_put_rows(pq[st & 1], a);
+  };
+  auto publish = [&](int st) {
+#pragma unroll
+    for (int i = 1; i < NW; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) rb[st & 1][(4 * i + r) * 64 + l] = T[i][r];
+  };
+  if (np > 0 && wv == 0) {
+    invert(T[0], 0);
+    publish(0);
+  }
   __syncthreads();
-  for (int kt = 0; kt * TC < kend; ++kt) {
-    const bool own_c = tc == kt;
+#pragma unroll 1
+  for (int p = 0; p < np; ++p) {
+    const double* R = rb[p & 1];
+    const double* P = pq[p & 1];
+    const dbl4 zero = {0.0, 0.0, 0.0, 0.0};
+    if (wv == p) {
+      const dbl4 pa = tile_get_t(P);
 #pragma unroll
-    for (int k2 = 0; k2 < TC; k2 += PB) {
-      const int st = kt * (TC / PB) + k2 / PB;  // step: pivots 4 st .. 4 st + 3
-      if (st >= nstep) break;
-      const bool own_r = tr == st;
-      // the wave that holds the next step's pivot rows updates first, then
-      // forms that step's R while the other waves finish this update
-      const bool ahead = st + 1 < nstep && wv == (st + 1) / (64 / 16);
+      for (int i = 1; i < NW; ++i) T[i - 1] = mfma16(pa, T[i], zero);
+      T[NW - 1] = tile_get(P);
+    } else {
+      const bool ahead = wv == p + 1 && p + 1 < np;
       if (ahead) __builtin_amdgcn_s_setprio(2);
-      {
-        // every lane takes part in the row broadcasts
-        double rv[PB][TC], cv[TR][PB];
-        if (k2 == 0) bcast_cols<0>(kt, w, cv);
-        else bcast_cols<PB>(kt, w, cv);
-        const double2* q2 = reinterpret_cast<const double2*>(rpp[st & 1]);
+      const dbl4 pn = -tile_get(P);
+      tile_put(mine, T[0]);
+      wave_lds_sync();
+      const dbl4 mt = mfma16(pn, tile_get_t(mine), zero);  // -(C P^{-1})^T: operand A
+      auto update = [&](int i) {
+        dbl4 r;
 #pragma unroll
-        for (int m = 0; m < PB; ++m)
-#pragma unroll
-          for (int jj = 0; jj < TC / 2; ++jj) {
-            const double2 x = q2[(m * (TC / 2) + jj) * ntc + tc];
-            rv[m][2 * jj] = x.x;
-            rv[m][2 * jj + 1] = x.y;
-          }
-        if (own_c) {
-#pragma unroll
-          for (int i = 0; i < TR; ++i)
-#pragma unroll
-            for (int m = 0; m < PB; ++m) w[i][k2 + m] = 0.0;
-        }
-#pragma unroll
-        for (int i = 0; i < TR; ++i)
-#pragma unroll
-          for (int j = 0; j < TC; ++j) {
-            double acc = w[i][j];
-#pragma unroll
-            for (int m = 0; m < PB; ++m) acc = fma(-cv[i][m], rv[m][j], acc);
-            w[i][j] = acc;
-          }
-        if (own_r) {
-#pragma unroll
-          for (int m = 0; m < PB; ++m)
-#pragma unroll
-            for (int j = 0; j < TC; ++j) w[m][j] = rv[m][j];
-        }
-      }
+        for (int c = 0; c < 4; ++c) r[c] = R[(4 * i + c) * 64 + l];
+        T[i - 1] = mfma16(mt, r, T[i]);
+      };
+      update(1);
       if (ahead) {
-        bad |= form_r(st + 1, t, tr, bp, ntc, c0, w, rpan, rpp[(st + 1) & 1]);
+        invert(T[0], p + 1);
+        wave_lds_sync();
+      }
+      tile_put(mine, mt);
+#pragma unroll
+      for (int i = 2; i < NW; ++i) update(i);
+      wave_lds_sync();
+      T[NW - 1] = tile_get_t(mine);  // -C P^{-1}
+      if (ahead) {
+        publish(p + 1);
         __builtin_amdgcn_s_setprio(0);
       }
-      __syncthreads();
     }
+    __syncthreads();
   }
-  if (act) {
 #pragma unroll
-    for (int i = 0; i < TR; ++i) {
-      double2* dst = reinterpret_cast<double2*>(A + (long long)(r0 + i) * ld + c0);
+  for (int i = 0; i < NW; ++i) {
+    const int cb = np + i < NW ? np + i : np + i - NW;  // np <= NW, i < NW
 #pragma unroll
-      for (int jj = 0; jj < TC / 2; ++jj) dst[jj] = make_double2(w[i][2 * jj], w[i][2 * jj + 1]);
-    }
+    for (int r = 0; r < 4; ++r) A[(long long)(16 * wv + 4 * r + lg) * ld + 16 * cb + lc] = T[i][r];
   }
   if (bad) atomicOr(flags, kFlagSingular);
 }
@@ -241,8 +143,6 @@ __global__ void __launch_bounds__(kInvThreads) k_bcr_inv(double* __restrict__ po
 // (whole blocks, or quarters of a block in the two-by-two inverse).  One
 // workgroup of 256 threads (four waves) per 32 x 32 output tile.
 constexpr int GT = 32;
-
-typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 // One 32 x 32 output tile of a product task (tile = row-major tile index).
 // Each of the four waves computes one 16 x 16 quadrant with FP64 matrix
@@ -424,8 +324,16 @@ hipError_t launch_bcr_inv(double* pool, const long long* offs, const int* npiv, 
                           int ld, int* flags,
                           hipStream_t s) {
   if (nblk <= 0) return hipSuccess;
-  if (n % TC || n > kBcrInvMax) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_bcr_inv, dim3(nblk), dim3(kInvThreads), 0, s, pool, offs, npiv, n, ld, flags);
+  switch (n) {
+#define MRCM_INV(NW)                                                                             \
+  case 16 * NW:                                                                                  \
+    hipLaunchKernelGGL(k_bcr_inv<NW>, dim3(nblk), dim3(64 * NW), 0, s, pool, offs, npiv, ld, flags); \
+    break;
+    MRCM_INV(2) MRCM_INV(4) MRCM_INV(6) MRCM_INV(8)
+#undef MRCM_INV
+    default:
+      return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
