@@ -10,198 +10,287 @@
 // couplings of the plane) and diagonal couplings between planes.  The
 // factor is the sequence of block inverses W_j = S_j^{-1} of the block
 // LDL^T recurrence S_j = D_j - t_{j-1} W_{j-1} t_{j-1} (t: plane couplings).
-// One workgroup of NW wavefronts works on one box: lane c of wave v holds
-// rows 16v .. 16v + 15 of column c of the 64 x 64 block (padded with the
-// identity) in 16 registers, so a box of 64-cell planes spreads its block
-// over four waves (four SIMDs) and smaller planes take fewer.  W_j is
-// computed in place by Gauss-Jordan elimination with four pivots per step:
-// the wave holding the pivot rows publishes them through LDS, and every
-// lane applies the rank-4 update to its 16 entries.  The inverses are
-// symmetric, so lane c also holds entries 16v .. 16v + 15 of row c, and a
-// block-vector product y = W_j z is a 16-term partial dot product per lane
-// (z read from LDS) summed over the waves through LDS.  Solves:
+// One workgroup of NW wavefronts works on one box; wave v holds rows 16v ..
+// 16v + 15 of the plane block (padded with the identity to 16 NW) as NW
+// 16 x 16 tiles in the accumulator layout of the FP64 matrix instructions,
+// so a box of 64-cell planes spreads its block over four waves (four SIMDs)
+// and smaller planes take fewer.  W_j is computed in place by the symmetric
+// sweep of 16 pivots at a time (sweep3); block-vector products of all
+// right-hand sides are matrix instructions on the same tiles.  Solves:
 //   forward   z_j = W_j (b_j + t_{j-1} .* z_{j-1})
 //   backward  x_j = z_j + W_j (t_j .* x_{j+1}).
 // The inverses are stored whole (nb x nb, row-major), the layout the
 // smoothing kernel reads back.
+#include "gj16.h"
 #include "local3_common.h"
-#include "pivot4.h"
 
 namespace mrcm {
 namespace {
 
-// Pivot data of one elimination step (two alternating buffers) and the
-// flag.  vb holds the step's multipliers v_c = P^-1 A[k..k+3][c] of every
-// column c (m-major: lane c reads vb[m][c], no bank conflicts), rs the
-// pivot-column entries A[i][k+m] of every row i (row-major, read as
-// broadcasts), pb the 4 x 4 pivot block on its way to the wave that factors
-// it.  vb and rs also hold the per-wave partial sums of the block-vector
-// products (4 right-hand sides x NW waves x 64 lanes <= 1024 values), which
-// never overlap an elimination.
+// LDS of a workgroup beside its box: the three pivot-row tiles and (last)
+// the pivot tile of an elimination step; also a tile per wave to transpose
+// through, the x and y couplings of a plane while its block is built, and
+// the per-wave partial sums of the smoothing sweep's products (NW waves x 64
+// lanes).  8 KB: with the box arrays of 8 x 8 x 8 cells and six seeds,
+// three boxes fit a CU.
 struct __align__(16) Gj3 {
-  double vb[2][G3 * P3];
-  double rs[2][P3 * G3];
-  double pb[2][G3 * G3];
+  double buf[4][kTile];
   int flag;
 };
 
-__device__ __forceinline__ double* partials3(Gj3& sm) { return &sm.vb[0][0]; }
+__device__ __forceinline__ double* partials3(Gj3& sm) { return &sm.buf[0][0]; }
 
-// S_j = D_j - t_{j-1} W_{j-1} t_{j-1} (the lane's 16 entries of column c),
-// w holding W_{j-1} on entry when j > 0; identity outside the nb x nb block.
-__device__ __forceinline__ void build3(const Geo& g, const Box& B, const Box3& s, int j, double w[R3]) {
-  const int c = lane3();
-  const int r0 = R3 * wave3();
+// T <- S_j = D_j - t_{j-1} W_{j-1} t_{j-1}, T holding -W_{j-1} on entry
+// (sweep3) when j > 0; identity outside the nb x nb block.
+template <int NW>
+__device__ __forceinline__ void build3(const Geo& g, const Box& B, const Box3& s, int j, Gj3& sm,
+                                       dbl4 T[NW]) {
   const int nb = s.m0 * s.m1, m0 = s.m0;
-  const bool cin = c < nb;
-  const int cc = cin ? c : 0;
-  const double dc = s.Dg[j * nb + cc];
-  const double txm = (cin && cc % m0 > 0) ? tplane(g, B, s, j, cc - 1, 0) : 0.0;
-  const double txp = cin ? tplane(g, B, s, j, cc, 0) : 0.0;
-  const double tym = (cin && cc >= m0) ? tplane(g, B, s, j, cc - m0, 1) : 0.0;
-  const double typ = cin ? tplane(g, B, s, j, cc, 1) : 0.0;
+  double* tx = sm.buf[0];
+  double* ty = sm.buf[1];
+  for (int e = threadIdx.x; e < 2 * nb; e += 64 * NW) {
+    const int ax = e >= nb, c = e - ax * nb;
+    (ax ? ty : tx)[c] = tplane(g, B, s, j, c, ax);
+  }
+  lsync<NW>();
+  const int lc = lane3() & 15, lg = lane3() >> 4, r0 = 16 * wave3() + lg;
+  const double* dj = s.Dg + j * nb;
   const double* tp = s.Tz + (j > 0 ? j - 1 : 0) * nb;
-  const double tcp = (j > 0 && cin) ? tp[cc] : 0.0;
+  double di[4], txi[4], tyi[4], ti[4];
 #pragma unroll
-  for (int ii = 0; ii < R3; ++ii) {
-    const int i = r0 + ii;
-    // sums of selects: with one-cell-wide planes (m0 = 1) the x and y
-    // neighbours of the block numbering coincide
-    double v = (i == c) ? dc : 0.0;
-    v -= (i == c - 1) ? txm : 0.0;
-    v -= (i == c + 1) ? txp : 0.0;
-    v -= (i == c - m0) ? tym : 0.0;
-    v -= (i == c + m0) ? typ : 0.0;
-    if (j > 0 && i < nb) v = fma(-tp[i] * tcp, w[ii], v);
-    w[ii] = (i < nb && cin) ? v : (i == c ? 1.0 : 0.0);
+  for (int r = 0; r < 4; ++r) {
+    const int i = min(r0 + 4 * r, nb - 1);
+    di[r] = dj[i];
+    txi[r] = tx[i];
+    tyi[r] = ty[i];
+    ti[r] = j > 0 ? tp[i] : 0.0;
   }
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const int c = 16 * w + lc, cc = min(c, nb - 1);
+    if (j > 0) {
+      const double tc = tp[cc];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) T[w][r] *= ti[r] * tc;
+    }
+    // tiles that hold no diagonal, x or y coupling are left alone (uniform)
+    const int dist = 16 * abs(w - wave3());
+    if (dist <= 16 || abs(dist - m0) < 16) {
+      const double txc = tx[cc], tyc = ty[cc];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = r0 + 4 * r;
+        // sums of selects: with one-cell-wide planes (m0 = 1) the x and y
+        // neighbours of the block numbering coincide (the couplings across
+        // the box sides are zero)
+        double v = i == c ? di[r] : 0.0;
+        v -= c == i + 1 ? txi[r] : 0.0;
+        v -= c + 1 == i ? txc : 0.0;
+        v -= c == i + m0 ? tyi[r] : 0.0;
+        v -= c + m0 == i ? tyc : 0.0;
+        T[w][r] += v;
+      }
+    }
+    if (nb < 16 * NW) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = r0 + 4 * r;
+        T[w][r] = i < nb && c < nb ? T[w][r] : i == c ? 1.0 : 0.0;
+      }
+    }
+  }
+  lsync<NW>();
 }
 
-// In-place Gauss-Jordan inverse of the block, four pivots per step, no
-// pivoting (the Schur complements are SPD).  The pivot columns are not
-// exchanged: for a symmetric matrix under in-place Gauss-Jordan, column
-// k + m equals row k + m on the rows not yet eliminated and its negative
-// on the rows already eliminated (i < k), so the wave holding rows
-// k .. k + 3 publishes them with that sign as the pivot-column entries of
-// every row.  That wave also factors the 4 x 4 pivot block (closed form)
-// and publishes the multipliers v_c = P^-1 A[k..k+3][c] of every column c
-// (a unit right-hand side for the pivot columns), so the other waves only
-// read v_c and apply the rank-4 update A[i][c] -= sum_m A[i][k+m] v_c[m] to
-// their rows.  Look-ahead: during step k the wave holding rows k + 4 ..
-// k + 7 updates those rows first and publishes step k + 4's pivot data
-// before updating the rest, so one workgroup barrier per step suffices and
-// the pivot factorisation overlaps the other waves' updates.  The step
-// index is a template parameter: every register index is a compile-time
-// constant.
-template <int NW, int K>
-__device__ __forceinline__ void gj3_pivot(int nb, Gj3& sm, double w[R3], bool& bad) {
-  // publish step K's pivot data (the calling wave holds rows K .. K + 3)
-  constexpr int RI = K % R3;
-  const int c = lane3_here();
-  const int ck = c - K;
-  const bool pc = ck >= 0 && ck < G3;
-  double* vb = sm.vb[(K / G3) & 1];
-  double* rs = sm.rs[(K / G3) & 1];
-  double* pb = sm.pb[(K / G3) & 1];
-  if (pc) {
-    *reinterpret_cast<double2*>(pb + ck * G3) = make_double2(w[RI], w[RI + 1]);
-    *reinterpret_cast<double2*>(pb + ck * G3 + 2) = make_double2(w[RI + 2], w[RI + 3]);
-  }
-  const double sg = c < K ? -1.0 : 1.0;
-  *reinterpret_cast<double2*>(rs + c * G3) = make_double2(sg * w[RI], sg * w[RI + 1]);
-  *reinterpret_cast<double2*>(rs + c * G3 + 2) = make_double2(sg * w[RI + 2], sg * w[RI + 3]);
-  bsync<1>();  // the pivot block is read back by this wave only
-  double P[G3][G3], r[G3], v[G3];
-#pragma unroll
-  for (int j = 0; j < G3; ++j)
-#pragma unroll
-    for (int m = 0; m < G3; ++m) P[m][j] = pb[j * G3 + m];
-#pragma unroll
-  for (int m = 0; m < G3; ++m) {
-    // select values, not addresses (a select between the address of a
-    // constant and of w[] would keep w out of registers)
-    const double wm = w[RI + m];
-    const double unit = ck == m ? 1.0 : 0.0;
-    r[m] = pc ? unit : wm;
-  }
-  const PivBlock<double> q = piv_block(P);
-  bad |= !(q.d0 > 0.0 && q.da > 0.0 && q.s0 > 0.0 && q.ds > 0.0);
-  piv_apply(q, r, v);
-#pragma unroll
-  for (int m = 0; m < G3; ++m) vb[m * P3 + c] = v[m];
-  (void)nb;
+// Pivot tile -> its inverse, in sm.buf[3], by the wave that holds it.
+__device__ __forceinline__ void pivot3(Gj3& sm, const dbl4& t, bool& bad) {
+  double a[16];
+  tile_put(sm.buf[3], t);
+  wave_lds_sync();
+  tile_get_rows(sm.buf[3], a);
+  inv16<true>(a, bad);
+  wave_lds_sync();
+  tile_put_rows(sm.buf[3], a);
 }
 
-// rows [R0, R1) of the lane's 16: A[i][c] = (pivot column ? 0 : A[i][c]) -
-// sum_m rs[i][m] v[m]
-template <int R0, int R1>
-__device__ __forceinline__ void gj3_rows(const double* rw, unsigned long long keep, const double v[G3],
-                                         double w[R3]) {
+// The other tiles of the pivot rows, as operand B reads them.
+template <int NW, int P>
+__device__ __forceinline__ void publish3(Gj3& sm, const dbl4 T[NW]) {
 #pragma unroll
-  for (int ii = R0; ii < R1; ++ii) {
-    const double2 c01 = *reinterpret_cast<const double2*>(rw + ii * G3);
-    const double2 c23 = *reinterpret_cast<const double2*>(rw + ii * G3 + 2);
-    double acc = __longlong_as_double(__double_as_longlong(w[ii]) & keep);
-    acc = fma(-c01.x, v[0], acc);
-    acc = fma(-c01.y, v[1], acc);
-    acc = fma(-c23.x, v[2], acc);
-    acc = fma(-c23.y, v[3], acc);
-    w[ii] = acc;
-  }
+  for (int w = 0; w < NW; ++w)
+    if (w != P) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sm.buf[w < P ? w : w - 1][64 * r + lane3()] = T[w][r];
+    }
 }
 
-template <int NW, int K>
-__device__ __forceinline__ void gj3_step(int nb, Gj3& sm, double w[R3], bool& bad) {
-  constexpr int OWN = K / R3, RI = K % R3;
-  constexpr int KN = K + G3, OWNN = KN / R3, RIN = KN % R3;
-  const int c = lane3_here();
-  const int wv = wave3();
-  const double* vb = sm.vb[(K / G3) & 1];
-  const double* rw = sm.rs[(K / G3) & 1] + R3 * wv * G3;
-  const int ck = c - K;
-  const bool pc = ck >= 0 && ck < G3;
-  // the pivot columns start from zero: a bit mask, not a branch per row
-  const unsigned long long keep = pc ? 0ull : ~0ull;
-  double v[G3];
+// T <- -(block)^{-1} by the symmetric sweep operator, 16 pivots per step, no
+// pivoting (the Schur complements are SPD).  Step P, with A_PP the pivot
+// block and Q its inverse (inv16):
+//   A_PP <- -Q,  A_Pw <- Q A_Pw,  A_vP <- A_vP Q,  A_vw <- A_vw - A_vP Q A_Pw,
+// which keeps the whole matrix symmetric, so the pivot columns are the
+// transposed pivot rows: a wave's operands are the pivot rows in LDS as
+// their owner's accumulators hold them (operand B; read as operand A, the
+// tile is its transpose), and Q A_Pv comes out of its product as operand A
+// of the update.  No transposition, 20 matrix instructions per wave and
+// step.  The pivot rows and Q have one buffer each: every wave takes its
+// operands into registers, a barrier frees the buffers, and the wave that
+// holds the next pivot rows updates its pivot tile first, inverts it and
+// publishes while the others update.
+//
+// Bound (64 x 64 blocks, three boxes per CU): the FP64 units, by the matrix
+// instructions (64 cycles each) and the vector work of the pivot inverses
+// and of the block set-up, about three quarters of the kernel's time; the
+// rest is the chain of four pivot inverses per plane.  Measured against four
+// pivots per step on the vector unit (17,920 boxes of 8 x 8 x 8 cells):
+// six seeds 5.92 -> 4.84 ms, 18 seeds (4,480 boxes) 2.00 -> 1.46 ms, the
+// particular problems of 4 x 4 x 4 cells 0.37 -> 0.25 ms.
+template <int NW, int P>
+__device__ __forceinline__ void sweep3_step(int np, Gj3& sm, dbl4 T[NW], bool& bad) {
+  if constexpr (P < NW) {
+    if (P < np) {
+      const dbl4 zero = {0.0, 0.0, 0.0, 0.0};
+      const int wv = wave3();
+      const dbl4 qa = tile_get_t(sm.buf[3]), qb = tile_get(sm.buf[3]);
+      if (wv == P) {
+        lsync<NW>();
 #pragma unroll
-  for (int m = 0; m < G3; ++m) v[m] = vb[m * P3 + c];
-  if constexpr (KN < R3 * NW) {
-    // look-ahead: every wave updates the rows at the next pivot rows' place
-    // first (the order of the rows does not matter otherwise); the wave
-    // that holds them then publishes the next step's pivot data before it
-    // updates the rest
-    gj3_rows<RIN, RIN + G3>(rw, keep, v, w);
-    if (KN < nb && wv == OWNN) gj3_pivot<NW, KN>(nb, sm, w, bad);
-    gj3_rows<0, RIN>(rw, keep, v, w);
-    gj3_rows<RIN + G3, R3>(rw, keep, v, w);
-  } else {
-    gj3_rows<0, R3>(rw, keep, v, w);
-  }
-  if (wv == OWN) {
+        for (int w = 0; w < NW; ++w)
+          if (w != P) T[w] = mfma16(qa, T[w], zero);
+        T[P] = -qb;
+      } else {
+        dbl4 rv, r[NW];
+        const double* mv = sm.buf[wv < P ? wv : wv - 1];
 #pragma unroll
-    for (int m = 0; m < G3; ++m) w[RI + m] = v[m];
-  }
-  bsync<NW>();
-}
-
-template <int NW, int K>
-__device__ __forceinline__ void gj3_steps(int nb, Gj3& sm, double w[R3], bool& bad) {
-  if constexpr (K < R3 * NW) {
-    if (K < nb) {
-      gj3_step<NW, K>(nb, sm, w, bad);
-      gj3_steps<NW, K + G3>(nb, sm, w, bad);
+        for (int c = 0; c < 4; ++c) rv[c] = mv[64 * c + lane3()];
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+          if (w != P) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) r[w][c] = sm.buf[w < P ? w : w - 1][64 * c + lane3()];
+          }
+        lsync<NW>();
+        const dbl4 u = -mfma16(qa, rv, zero);
+        if constexpr (P + 1 < NW) T[P + 1] = mfma16(u, r[P + 1], T[P + 1]);
+        T[P] = mfma16(rv, qb, zero);
+        if constexpr (P + 1 < NW) {
+          if (wv == P + 1 && P + 1 < np) pivot3(sm, T[P + 1], bad);
+        }
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+          if (w != P && w != P + 1) T[w] = mfma16(u, r[w], T[w]);
+        if constexpr (P + 1 < NW) {
+          if (wv == P + 1 && P + 1 < np) publish3<NW, P + 1>(sm, T);
+        }
+      }
+      lsync<NW>();
+      sweep3_step<NW, P + 1>(np, sm, T, bad);
     }
   }
 }
 
 template <int NW>
-__device__ __forceinline__ void gj3(int nb, Gj3& sm, double w[R3]) {
+__device__ __forceinline__ void sweep3(int nb, Gj3& sm, dbl4 T[NW]) {
   bool bad = false;
-  if (wave3() == 0) gj3_pivot<NW, 0>(nb, sm, w, bad);
-  bsync<NW>();
-  gj3_steps<NW, 0>(nb, sm, w, bad);
-  if (bad && lane3() == 0) atomicOr(&sm.flag, kFlagNotPD);
-  bsync<NW>();
+  if (wave3() == 0) {
+    pivot3(sm, T[0], bad);
+    publish3<NW, 0>(sm, T);
+  }
+  lsync<NW>();
+  sweep3_step<NW, 0>((nb + 15) / 16, sm, T, bad);
+  if (bad) atomicOr(&sm.flag, kFlagNotPD);
+}
+
+// Rows 16v .. of W_j as operand A: the transposed tiles of -W_j in T.
+template <int NW>
+__device__ __forceinline__ void operand3(Gj3& sm, const dbl4 T[NW], dbl4 wa[NW]) {
+  double* t = sm.buf[wave3()];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    tile_put(t, T[w]);
+    wave_lds_sync();
+    wa[w] = -tile_get_t(t);
+    wave_lds_sync();
+  }
+}
+
+// The same from the stored inverse: column block v of the rows, by symmetry
+// (four 128-byte pieces per load).
+template <int NW>
+__device__ __forceinline__ void load_operand3(const double* Wj, int nb, dbl4 wa[NW]) {
+  const int lc = lane3() & 15, lg = lane3() >> 4, c = 16 * wave3() + lc;
+#pragma unroll
+  for (int w = 0; w < NW; ++w)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int i = 16 * w + 4 * k + lg;
+      wa[w][k] = i < nb && c < nb ? Wj[i * nb + c] : 0.0;
+    }
+}
+
+__device__ __forceinline__ void store_tiles3(double* Wj, int nb, int w, const dbl4& t) {
+  const int lc = lane3() & 15, lg = lane3() >> 4, c = 16 * w + lc;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int i = 16 * wave3() + 4 * r + lg;
+    if (i < nb && c < nb) Wj[i * nb + c] = -t[r];
+  }
+}
+
+// X_j (+)= W_j Z for the nrhs vectors staged in s.Z (entry i of vector k at
+// Z[nrhs i + k]), 16 right-hand sides per pass of matrix instructions.
+template <int NW, bool ACC>
+__device__ __forceinline__ void apply3(const Box3& s, int nb, int j, int nrhs, const dbl4 wa[NW]) {
+  const int lc = lane3() & 15, lg = lane3() >> 4;
+  for (int k0 = 0; k0 < nrhs; k0 += 16) {
+    const int k = k0 + lc, kk = min(k, nrhs - 1);
+    dbl4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      dbl4 z;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) z[c] = s.Z[(16 * w + 4 * c + lg) * nrhs + kk];
+      acc = mfma16(wa[w], z, acc);
+    }
+    if (k < nrhs) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * wave3() + 4 * r + lg;
+        if (i < nb) {
+          double* x = s.X + k * s.nc + j * nb + i;
+          *x = ACC ? *x + acc[r] : acc[r];
+        }
+      }
+    }
+  }
+  lsync<NW>();
+}
+
+// Forward step of block j for all right-hand sides.
+template <int NW>
+__device__ __forceinline__ void fwd_tiles3(const Box3& s, int nb, int j, int nrhs, const dbl4 wa[NW]) {
+  for (int e = threadIdx.x; e < nrhs * 16 * NW; e += 64 * NW) {
+    const int k = e / (16 * NW), i = e % (16 * NW);
+    double v = 0.0;
+    if (i < nb) {
+      v = s.X[k * s.nc + j * nb + i];
+      if (j > 0) v = fma(s.Tz[(j - 1) * nb + i], s.X[k * s.nc + (j - 1) * nb + i], v);
+    }
+    s.Z[i * nrhs + k] = v;
+  }
+  lsync<NW>();
+  apply3<NW, false>(s, nb, j, nrhs, wa);
+}
+
+// Backward step of block j: x_j += W_j (t_j .* x_{j+1}).
+template <int NW>
+__device__ __forceinline__ void bwd_tiles3(const Box3& s, int nb, int j, int nrhs, const dbl4 wa[NW]) {
+  for (int e = threadIdx.x; e < nrhs * 16 * NW; e += 64 * NW) {
+    const int k = e / (16 * NW), i = e % (16 * NW);
+    s.Z[i * nrhs + k] = i < nb ? s.Tz[j * nb + i] * s.X[k * s.nc + (j + 1) * nb + i] : 0.0;
+  }
+  lsync<NW>();
+  apply3<NW, true>(s, nb, j, nrhs, wa);
 }
 
 // The lane's share of y = W z for the staged vector z (64 values in LDS):
@@ -297,45 +386,47 @@ __device__ __forceinline__ void load3(const double* Wj, int nb, double w[R3]) {
   }
 }
 
-__device__ __forceinline__ void store3(double* Wj, int nb, const double w[R3]) {
-  const int c = lane3(), r0 = R3 * wave3();
-#pragma unroll
-  for (int ii = 0; ii < R3; ++ii) {
-    const int i = r0 + ii;
-    if (i < nb && c < nb) Wj[i * nb + c] = w[ii];
-  }
-}
-
 // Factor of the box fused with the forward sweep of nrhs right-hand sides
 // already in X; inverses to Wg.
 template <int NW>
 __device__ __forceinline__ void factor3(const Geo& g, const Box& B, const Box3& s, double* Wg, int nrhs,
                                         Gj3& sm) {
   const int nb = s.m0 * s.m1;
-  double w[R3];
+  dbl4 T[NW];
 #pragma unroll
-  for (int i = 0; i < R3; ++i) w[i] = 0.0;
+  for (int w = 0; w < NW; ++w) T[w] = dbl4{0.0, 0.0, 0.0, 0.0};
   for (int j = 0; j < s.m2; ++j) {
-    build3(g, B, s, j, w);
-    gj3<NW>(nb, sm, w);
-    store3(Wg + (long long)j * nb * nb, nb, w);
-    if (nrhs > 0) fwd3<NW>(s, sm, nb, j, nrhs, w);
+    build3<NW>(g, B, s, j, sm, T);
+    sweep3<NW>(nb, sm, T);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) store_tiles3(Wg + (long long)j * nb * nb, nb, w, T[w]);
+    if (nrhs > 0) {
+      dbl4 wa[NW];
+      operand3<NW>(sm, T, wa);
+      fwd_tiles3<NW>(s, nb, j, nrhs, wa);
+    }
   }
 }
 
-// PF: the next plane's inverse is loaded while the current one is applied
-template <int NW, bool PF>
-__device__ __forceinline__ void backward3(const Box3& s, Gj3& sm, const double* Wg, int nrhs) {
+// Back substitution; the next plane's inverse is loaded while the current
+// one is applied.
+template <int NW>
+__device__ __forceinline__ void backward3(const Box3& s, const double* Wg, int nrhs) {
   const int nb = s.m0 * s.m1;
-  double w[R3], wn[R3];
-  if (PF && s.m2 >= 2) load3(Wg + (long long)(s.m2 - 2) * nb * nb, nb, w);
-  for (int j = s.m2 - 2; j >= 0; --j) {
-    if (!PF) load3(Wg + (long long)j * nb * nb, nb, w);
-    if (PF && j > 0) load3(Wg + (long long)(j - 1) * nb * nb, nb, wn);
-    bwd3<NW>(s, sm, nb, j, nrhs, w);
-    if (PF) {
-#pragma unroll
-      for (int ii = 0; ii < R3; ++ii) w[ii] = wn[ii];
+  // the stored inverses are read back by other lanes than wrote them
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  if constexpr (NW > 1) __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  const long long bs = (long long)nb * nb;
+  dbl4 w0[NW], w1[NW];
+  int j = s.m2 - 2;
+  if (j >= 0) load_operand3<NW>(Wg + j * bs, nb, w0);
+  for (; j >= 0; j -= 2) {
+    if (j > 0) load_operand3<NW>(Wg + (j - 1) * bs, nb, w1);
+    bwd_tiles3<NW>(s, nb, j, nrhs, w0);
+    if (j > 0) {
+      if (j > 1) load_operand3<NW>(Wg + (j - 2) * bs, nb, w0);
+      bwd_tiles3<NW>(s, nb, j - 1, nrhs, w1);
     }
   }
 }
@@ -359,7 +450,7 @@ __device__ __forceinline__ void basis3(const Geo& g, const Box& B, const Seed* _
   double* Wg = fac + B.fac;
   factor3<NW>(g, B, s, Wg, nrhs, sm);
   if (FO) return;
-  backward3<NW, true>(s, sm, Wg, nrhs);
+  backward3<NW>(s, Wg, nrhs);
   basis_out3<NW>(g, B, s, seeds, beta, nrhs, Pk, tr_u, tr_phi, tr_beta);
 }
 
@@ -380,7 +471,7 @@ __device__ __forceinline__ void particular3(const Geo& g, const Box& B,
   bsync<NW>();
   double* Wg = fac + B.fac;
   factor3<NW>(g, B, s, Wg, 1, sm);
-  backward3<NW, true>(s, sm, Wg, 1);
+  backward3<NW>(s, Wg, 1);
   part_out3<NW>(g, B, s, beta, pbar, ubar, pibar);
 }
 
@@ -405,7 +496,10 @@ __device__ __forceinline__ void smooth3(const Geo& g, const Box& B, const double
     load3(Wg + (long long)j * nb * nb, nb, w);
     fwd3<NW>(s, sm, nb, j, 1, w);
   }
-  backward3<NW, false>(s, sm, Wg, 1);
+  for (int j = s.m2 - 2; j >= 0; --j) {
+    load3(Wg + (long long)j * nb * nb, nb, w);
+    bwd3<NW>(s, sm, nb, j, 1, w);
+  }
   smooth_out3<NW>(g, B, s, p, gflux, beta);
 }
 
