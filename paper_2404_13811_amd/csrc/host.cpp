@@ -91,6 +91,11 @@ struct mrcm_ctx {
   size_t lds3f_basis = 0, lds3f_part = 0, lds3f_smooth = 0;
   int nw3_box = 4, nw3_part = 4;  // wavefronts per 3-D box (oversampled, subdomain)
   size_t lds_basis = 0, lds_part = 0, lds_smooth = 0;
+  // 2-D smoothing with the factors of a box resident in LDS: its LDS bytes
+  // (0: some box does not fit, the factors are streamed) and what it keeps
+  // per box
+  size_t lds_smooth_res = 0;
+  SmoothArrays sarr{nullptr, nullptr, nullptr, 0};
   size_t lds32_basis = 0, lds32_part = 0, lds32_smooth = 0;
   float *fac32 = nullptr, *facp32 = nullptr;
   int* d_iters = nullptr;
@@ -223,6 +228,7 @@ void free_plan(mrcm_ctx* c) {
   dfree(c->d_obox); dfree(c->d_pbox); dfree(c->d_seeds); dfree(c->d_basis);
   dfree(c->d_seed_off); dfree(c->d_ifc); dfree(c->d_members); dfree(c->d_obox_col);
   dfree(c->fac); dfree(c->fact); dfree(c->facs); dfree(c->facts); dfree(c->fac32s); dfree(c->facp); dfree(c->scr); dfree(c->tco); dfree(c->tcp);
+  dfree(c->sarr.b0); dfree(c->sarr.fc); dfree(c->sarr.gc);
   dfree(c->fac32); dfree(c->facp32); dfree(c->d_iters); dfree(c->d_resid);
   dfree(c->Pk); dfree(c->tr_u); dfree(c->tr_phi); dfree(c->tr_beta);
   dfree(c->pbar); dfree(c->ubar); dfree(c->pibar);
@@ -633,10 +639,11 @@ mrcm_status make_plan(mrcm_ctx* c) {
     B.ncell = B.nb * B.nblk;
     B.seed0 = c->seed_off[i];
     B.nrhs = (int)c->seeds.size() - B.seed0;
+    // even offsets: 16-byte pieces of a box's factors and vectors
     B.fac = fac;
-    fac += (long long)B.nblk * B.nb * B.nb;
+    fac += (B.nblk * std::max<long long>((long long)B.nb * B.nb, wave_packed_elems(B.nb)) + 1) / 2 * 2;
     B.scr = scr;
-    scr += (long long)B.ncell * std::max(B.nrhs, 1);
+    scr += ((long long)B.ncell * std::max(B.nrhs, 1) + 1) / 2 * 2;
     if (B.nb > kMaxBlock)
       return fail(c, MRCM_EINVAL, "oversampled box block of %d cells exceeds %d", B.nb, kMaxBlock);
     if (B.nrhs > kMaxRhs)
@@ -651,7 +658,7 @@ mrcm_status make_plan(mrcm_ctx* c) {
     P.ncell = P.nb * P.nblk;
     P.nrhs = 1;
     P.fac = facp;
-    facp += (long long)P.nblk * P.nb * P.nb;
+    facp += P.nblk * std::max<long long>((long long)P.nb * P.nb, wave_packed_elems(P.nb));
     P.scr = scrp;
     scrp += P.ncell;
     if (P.nb > kMaxBlock)
@@ -665,7 +672,7 @@ mrcm_status make_plan(mrcm_ctx* c) {
   c->scro_n = scr;
   c->scrp_n = scrp;
   c->wave = c->d == 2;
-  c->lds_basis = c->lds_part = c->lds_smooth = c->lds_factor = 0;
+  c->lds_basis = c->lds_part = c->lds_smooth = c->lds_factor = c->lds_smooth_res = 0;
   c->lds_adj_smooth = c->lds_adj_basis = c->lds_adj_part = 0;
   c->lds_adj32_smooth = c->lds_adj32_basis = c->lds_adj32_part = 0;
   for (int i = 0; i < nsub; ++i) {
@@ -677,6 +684,7 @@ mrcm_status make_plan(mrcm_ctx* c) {
     c->lds_basis = std::max(c->lds_basis, wave_basis_lds_bytes(bm0, bm1, std::max(B.nrhs, 1), kc));
     c->lds_factor = std::max(c->lds_factor, wave_basis_lds_bytes(bm0, bm1, 0, kc));
     c->lds_smooth = std::max(c->lds_smooth, wave_smooth_lds_bytes(bm0, bm1, kc));
+    c->lds_smooth_res = std::max(c->lds_smooth_res, wave_smooth_res_lds_bytes(bm0, bm1));
     c->lds_part = std::max(c->lds_part, wave_lds_bytes(P.hi[0] - P.lo[0], P.hi[1] - P.lo[1], 1, kc));
     c->lds32_basis = std::max(c->lds32_basis, wave32_lds_bytes(bm0, bm1, std::max(B.nrhs, 1), 0, kc));
     c->lds32_smooth = std::max(c->lds32_smooth, wave32_smooth_lds_bytes(bm0, bm1, kc));
@@ -694,6 +702,7 @@ mrcm_status make_plan(mrcm_ctx* c) {
   }
   if (c->lds_basis > 150 * 1024 || c->lds_smooth > 150 * 1024 || 2 * c->lds_part + 16 > 150 * 1024)
     c->wave = false;
+  if (!c->wave || c->lds_smooth_res > 150 * 1024) c->lds_smooth_res = 0;
   // 3-D boxes: one wave per box with plane blocks of at most 64 cells
   c->d3 = c->d == 3;
   c->lds3_basis = c->lds3_part = c->lds3_smooth = 0;
@@ -801,6 +810,12 @@ mrcm_status make_plan(mrcm_ctx* c) {
   ALLOC(c->facp, c->facp_n);
   ALLOC(c->scr, c->scr_n);
   ALLOC(c->tco, c->scro_n);
+  if (c->lds_smooth_res) {
+    c->sarr.fstride = 4 * (g.S[0] + g.S[1] + 4 * c->l);
+    ALLOC(c->sarr.b0, c->scro_n);
+    ALLOC(c->sarr.fc, (long long)nsub * c->sarr.fstride);
+    ALLOC(c->sarr.gc, (long long)nsub * g.gstride);
+  }
   ALLOC(c->tcp, c->scrp_n);
   ALLOC(c->fac32, c->fac_n);
   ALLOC(c->facp32, c->facp_n);
@@ -1233,7 +1248,7 @@ mrcm_status mrcm_build_basis(mrcm_ctx* c) {
     HIPCHK(c, launch_local_w(c->geo, c->d_obox, c->d_pbox, c->geo.nsub, c->d_seeds, c->logk, c->K, c->f,
                              c->bcv, c->beta_mbf, c->fac, c->tco, c->facp, c->tcp, c->Pk, c->tr_u,
                              c->tr_phi, c->tr_beta, c->pbar, c->ubar, c->pibar, c->fact,
-                             c->flags, std::max(c->lds_basis, 2 * c->lds_part + 16), c->lds_part, s));
+                             c->sarr, c->flags, std::max(c->lds_basis, 2 * c->lds_part + 16), c->lds_part, s));
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[9], s));
   } else if (c->d3) {
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[8], s));
@@ -1270,8 +1285,8 @@ mrcm_status mrcm_build_basis(mrcm_ctx* c) {
     } else if (c->wave) {
       HIPCHK(c, grow(c->facs, c->fac_n));
       HIPCHK(c, grow(c->facts, c->fac_n));
-      HIPCHK(c, launch_factor_w(c->geo, c->d_obox, c->geo.nsub, c->logk, c->beta_sm, c->facs,
-                                c->facts, c->flags, c->lds_factor, s));
+      HIPCHK(c, launch_factor_w(c->geo, c->d_obox, c->geo.nsub, c->logk, c->beta_sm, c->f, c->bcv,
+                                c->facs, c->facts, c->sarr, c->flags, c->lds_factor, s));
     } else if (c->d3) {
       HIPCHK(c, grow(c->facs, c->fac_n));
       HIPCHK(c, launch_basis3(c->geo, c->d_obox, c->geo.nsub, c->d_seeds, c->logk, c->beta_sm,
@@ -1400,7 +1415,7 @@ mrcm_status sweep(mrcm_ctx* c, hipStream_t s, int nt, double* p, double* gflux, 
     } else if (c->wave) {
       HIPCHK(c, launch_smooth_w(c->geo, c->d_obox_col + m0, m1 - m0, c->K, c->f, c->bcv,
                                 c->beta_sm, own ? c->facs : c->fac, own ? c->facts : c->fact,
-                                c->tco, c->scr, p, gflux, c->lds_smooth, nt, s));
+                                c->tco, c->sarr, p, gflux, c->lds_smooth, c->lds_smooth_res, nt, s));
     } else if (c->d3) {
       HIPCHK(c, launch_smooth3(c->geo, c->d_obox_col + m0, m1 - m0, c->K, c->f, c->bcv, c->beta_sm,
                                own ? c->facs : c->fac, p, gflux, c->lds3_smooth, c->nw3_box, s));
@@ -1591,8 +1606,9 @@ mrcm_status mrcm_smooth(mrcm_ctx* c, int nsteps) {
     const hipError_t e =
         launch_smooth_grid(c->geo, c->d_obox_col, ph, nphase, c->K, c->f, c->bcv, c->beta_sm,
                            c->beta_sm != c->beta_mbf ? c->facs : c->fac,
-                           c->beta_sm != c->beta_mbf ? c->facts : c->fact, c->tco, c->p,
-                           c->gflux, c->lds_smooth, c->smooth_nt, c->persist_groups, s);
+                           c->beta_sm != c->beta_mbf ? c->facts : c->fact, c->tco, c->sarr, c->p,
+                           c->gflux, c->lds_smooth, c->lds_smooth_res, c->smooth_nt,
+                           c->persist_groups, s);
     if (e == hipSuccess) {
       c->persist_used = true;
       c->n_smooth_launches = 1;

@@ -99,7 +99,10 @@ __device__ __forceinline__ void basis_box(const Geo& g, const Box& B, const Seed
                                           double* __restrict__ tcoup,
                                           double* __restrict__ Pk, double* __restrict__ tr_u,
                                           double* __restrict__ tr_phi,
-                                          double* __restrict__ tr_beta, double* dsm, WaveSmem* sm) {
+                                          double* __restrict__ tr_beta,
+                                          const double* __restrict__ f,
+                                          const double* __restrict__ bcv, const SmoothStatic& st,
+                                          double* dsm, WaveSmem* sm) {
   const int L = lane_id();
   const int tid = threadIdx.x, wv = tid >> 6;
   const int nrhs = FO ? 0 : B.nrhs;
@@ -110,6 +113,7 @@ __device__ __forceinline__ void basis_box(const Geo& g, const Box& B, const Seed
   // set-up by both waves: box arrays (K from log K), seed right-hand
   // sides, couplings
   load_box<128, true>(g, B, logK, beta, s);
+  if (st.b0) smooth_static<128>(g, B, s, f, bcv, beta, st);
   for (int e = tid; e < nrhs * nc; e += 128) s.X[e] = 0.0;
   __syncthreads();
   // T^R times the seed on the cells of its side, all seeds at once
@@ -307,8 +311,8 @@ __global__ void __launch_bounds__(128) k_local_w(Geo g, const Box* __restrict__ 
                                                  double* __restrict__ pbar,
                                                  double* __restrict__ ubar,
                                                  double* __restrict__ pibar,
-                                                 double* __restrict__ fact, int npart,
-                                                 int part_ld, int* flags) {
+                                                 double* __restrict__ fact, SmoothStatic st,
+                                                 int npart, int part_ld, int* flags) {
   extern __shared__ __align__(16) double dsm[];
   __shared__ WaveSmem sm[2];
   const int L = lane_id(), wv = threadIdx.x >> 6;
@@ -316,7 +320,7 @@ __global__ void __launch_bounds__(128) k_local_w(Geo g, const Box* __restrict__ 
   const int b = blockIdx.x;
   if (b < nbox) {
     const Box B = obox[b];
-    basis_box(g, B, seeds, logK, beta, fac, fact, tcoup, Pk, tr_u, tr_phi, tr_beta, dsm, sm);
+    basis_box(g, B, seeds, logK, beta, fac, fact, tcoup, Pk, tr_u, tr_phi, tr_beta, f, bcv, st, dsm, sm);
   } else {
     // npart (1 or 2) subdomains per workgroup, one per wave, each in its own
     // part_ld doubles of LDS
@@ -336,15 +340,18 @@ __global__ void __launch_bounds__(128) k_local_w(Geo g, const Box* __restrict__ 
 // per box as in k_local_w, into their own forward / backward inverses.
 __global__ void __launch_bounds__(128) k_factor_w(Geo g, const Box* __restrict__ obox,
                                                   const double* __restrict__ logK, double beta,
+                                                  const double* __restrict__ f,
+                                                  const double* __restrict__ bcv,
                                                   double* __restrict__ fac,
-                                                  double* __restrict__ fact, int* flags) {
+                                                  double* __restrict__ fact, SmoothStatic st,
+                                                  int* flags) {
   extern __shared__ __align__(16) double dsm[];
   __shared__ WaveSmem sm[2];
   const int L = lane_id(), wv = threadIdx.x >> 6;
   if (L == 0) sm[wv].flag = 0;
   const Box B = obox[blockIdx.x];
   basis_box<true>(g, B, nullptr, logK, beta, fac, fact, nullptr, nullptr, nullptr, nullptr,
-                  nullptr, dsm, sm);
+                  nullptr, f, bcv, st, dsm, sm);
   __syncthreads();
   if (threadIdx.x == 0 && (sm[0].flag | sm[1].flag)) atomicOr(flags, sm[0].flag | sm[1].flag);
 }
@@ -380,34 +387,179 @@ __device__ __forceinline__ void smooth_box(const Geo& g, const Box& B, const dou
   smooth_out<NT>(g, B, r, r.b.X, beta, p, gflux);
 }
 
+// The fields of Geo a smoothing box uses, as scalars: every inlined use of
+// the kernel argument itself counts against the compiler's limit for
+// reading it in place, beyond which it is copied to scratch memory.
+struct Geo2 {
+  int n0, n1, cut, l, S0, S1, M0, M1, mcut, gstride, go0, go1, go2, go3;
+  double area;
+};
+__device__ __forceinline__ Geo2 geo2(const Geo& g) {
+  return Geo2{g.n[0], g.n[1], g.cut, g.l, g.S[0], g.S[1], g.M[0], g.M[1], g.mcut, g.gstride,
+              g.gside_off[0], g.gside_off[1], g.gside_off[2], g.gside_off[3], g.area};
+}
+__device__ __forceinline__ int gside2(const Geo2& g, int q) {
+  return q == 0 ? g.go0 : q == 1 ? g.go1 : q == 2 ? g.go2 : g.go3;
+}
+// moving from `from` to `to` along an axis of n entries (cut: batch members)
+__device__ __forceinline__ bool off2(int n, int cut, int from, int to) {
+  return to < 0 || to >= n || (cut > 0 && to / cut != from / cut);
+}
+
+// What the Robin term of box-side face u reads: its two coefficients, the
+// state on this side (va; without overlap the neighbour's flux at the face)
+// and beyond the face (vb).  Zero on the domain boundary.
+struct FaceIn {
+  double c0, c1, va, vb;
+};
+__device__ __forceinline__ FaceIn face_in(const Geo2& g, int lo0, int lo1, int hi0, int hi1, int sub, int u,
+                                          const double* __restrict__ fc, const double* p,
+                                          const double* gflux) {
+  FaceIn r{0.0, 0.0, 0.0, 0.0};
+  int t, x, y, ox, oy;
+  const int q = face_side(hi0 - lo0, hi1 - lo1, u, t), a = q >> 1, sd = q & 1, n0 = g.n0;
+  face_cells(lo0, lo1, hi0, hi1, q, t, x, y, ox, oy);
+  const bool dom = off2(a == 0 ? g.n0 : g.n1, a == 0 ? 0 : g.cut, a == 0 ? x : y, a == 0 ? ox : oy);
+  if (dom) return r;
+  r.c0 = fc[2 * u];
+  r.c1 = fc[2 * u + 1];
+  r.vb = p[ox + n0 * oy];
+  if (g.l > 0) {
+    r.va = p[x + n0 * y];
+  } else {
+    // the face's place on the neighbour's opposite side
+    const int isub = sub % g.M0, jsub = sub / g.M0;
+    const int j = sub + (a == 0 ? (sd ? 1 : -1) : (sd ? g.M0 : -g.M0));
+    const int tj = a == 0 ? y - jsub * g.S1 : x - isub * g.S0;
+    r.va = gflux[(long long)j * g.gstride + gside2(g, q ^ 1) + tj];
+  }
+  return r;
+}
+// T^R lambda of that face
+__device__ __forceinline__ double face_add(bool overlap, const FaceIn& r) {
+  return overlap ? fma(r.c0, r.va, -r.c1 * (r.va - r.vb)) : fma(r.c0, r.vb, r.c1 * r.va);
+}
+
+// Gamma face u of a subdomain (side by side): side q, position t, and its
+// index in the subdomain's Gamma fluxes
+__device__ __forceinline__ int gamma_face(const Geo2& g, int u, int& q, int& t) {
+  q = face_side(g.S0, g.S1, u, t);
+  return gside2(g, q) + t;
+}
+
+// The same with the box's factors resident in LDS and what does not change
+// between phases read from the smooth_static arrays (see lds_sweep): the
+// form of every box whose LDS fits a workgroup.  Ends with a barrier.
+//
+// Bound: latency, one box per CU or two.  Of 20,000 cycles of a 24 x 24 box,
+// 12,000 are the 25 block steps, 3,500 the staging, 1,600 the outputs.
+template <int NT>
+__device__ __forceinline__ void smooth_box_res(const Geo2& g, const Box& B, const SmoothStatic& st,
+                                               const double* Wf, const double* Wt,
+                                               const double* __restrict__ tcoup, double* p,
+                                               double* gflux, double* dsm) {
+  const int tid = threadIdx.x % NT;
+  const int lo0 = B.lo[0], lo1 = B.lo[1], hi0 = B.hi[0], hi1 = B.hi[1], sub = B.sub;
+  const int m0 = hi0 - lo0, m1 = hi1 - lo1, nc = m0 * m1, nce = (nc + 1) / 2 * 2;
+  const int n0 = g.n0, ns = 2 * (m0 + m1), ng = 2 * (g.S0 + g.S1);
+  double* img = dsm;
+  double* X = img + factor_image_doubles(m0, m1);
+  double* Tn = X + nce;
+  double* AF = Tn + nce;  // T^R lambda of the box sides
+  const double* fc = st.fc + (long long)sub * st.fstride;
+  const double* gc = st.gc + (long long)sub * g.gstride;
+  // the first faces' loads are in flight before the staging is issued
+  FaceIn first{0.0, 0.0, 0.0, 0.0};
+  if (tid < ns) first = face_in(g, lo0, lo1, hi0, hi1, sub, tid, fc, p, gflux);
+  stage_factors<NT>(B, Wf, Wt, img);
+  stage_lds<NT>(st.b0 + B.scr, X, nc);
+  stage_lds<NT>(tcoup + B.scr, Tn, nc);
+  if (tid < ns) AF[tid] = face_add(g.l > 0, first);
+#pragma unroll 1
+  for (int u = tid + NT; u < ns; u += NT)
+    AF[u] = face_add(g.l > 0, face_in(g, lo0, lo1, hi0, hi1, sub, u, fc, p, gflux));
+  staged_wait<NT>();
+  // both sides of an axis in one pass, except in a box one cell thick along
+  // it, where they add to the same cells
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    const int nf = a == 0 ? m1 : m0, st0 = a == 0 ? 1 : m0;  // faces per side, step along a side's normal
+    const int base = a == 0 ? 0 : 2 * m1, ma = a == 0 ? m0 : m1, stf = a == 0 ? m0 : 1;
+    if (ma > 1) {
+      for (int u = tid; u < 2 * nf; u += NT) {
+        const int hiq = u >= nf, t = u - (hiq ? nf : 0);
+        X[t * stf + (hiq ? (ma - 1) * st0 : 0)] += AF[base + u];
+      }
+    } else {
+      for (int t = tid; t < nf; t += NT) X[t * stf] += AF[base + t] + AF[base + nf + t];
+    }
+    bsync<NT>();
+  }
+  int q0, t0;
+  const double gc0 = tid < ng ? gc[gamma_face(g, tid, q0, t0)] : 0.0;  // in flight during the sweep
+  lds_sweep<NT>(B, img, Tn, X);
+  // Omega_i's Gamma fluxes and p on Omega_i
+  const int ix = sub % g.M0, iy = sub / g.M0, w0 = ix * g.S0, w1 = iy * g.S1;
+#pragma unroll 1
+  for (int u = tid; u < ng; u += NT) {
+    int q, t;
+    const int at = gamma_face(g, u, q, t), a = q >> 1, so = q & 1;
+    const int nj = (a == 0 ? ix : iy) + (so ? 1 : -1);
+    if (off2(a == 0 ? g.M0 : g.M1, a == 0 ? 0 : g.mcut, a == 0 ? ix : iy, nj)) continue;
+    const int cx = a == 0 ? (so ? w0 + g.S0 - 1 : w0) : w0 + t, cy = a == 1 ? (so ? w1 + g.S1 - 1 : w1) : w1 + t;
+    const double* x = X + (cx - lo0) + m0 * (cy - lo1);
+    double v;
+    if (g.l > 0) {
+      v = (u == tid ? gc0 : gc[at]) * (*x - x[a == 0 ? (so ? 1 : -1) : (so ? m0 : -m0)]);
+    } else {
+      // the box is Omega_i: T^R (x_c - lambda) / |e|
+      const int uf = face_off(m0, m1, q) + t;
+      v = (fc[2 * uf] * *x - AF[uf]) * rcp_d(g.area);
+    }
+    gflux[(long long)sub * g.gstride + at] = v;
+  }
+  const int ncell_o = g.S0 * g.S1;
+#pragma unroll 1
+  for (int t = tid; t < ncell_o; t += NT) {
+    const int cx = w0 + t % g.S0, cy = w1 + t / g.S0;
+    p[cx + n0 * cy] = X[(cx - lo0) + m0 * (cy - lo1)];
+  }
+  bsync<NT>();
+}
+
 // Steps 6-7: one color phase of the smoothing sweep, one workgroup of NT
 // threads (64, 128 or 256, chosen by the autotuner) per box.  The result
-// does not depend on NT.
-template <int NT>
+// does not depend on NT.  RES: factors resident in LDS.
+template <int NT, bool RES>
 __global__ void __launch_bounds__(NT) k_smooth_w(Geo g, const Box* __restrict__ boxes,
                                                  const double* __restrict__ K,
                                                  const double* __restrict__ f,
                                                  const double* __restrict__ bcv, double beta,
                                                  const double* __restrict__ fac,
                                                  const double* __restrict__ fact,
-                                                 const double* __restrict__ tcoup,
+                                                 const double* __restrict__ tcoup, SmoothStatic st,
                                                  double* __restrict__ p,
                                                  double* __restrict__ gflux) {
   extern __shared__ __align__(16) double dsm[];
   const Box B = boxes[blockIdx.x];
-  double w[RING][HB], zm[HB];
-  smooth_preload<NT>(B, fac + B.fac, fact + B.fac, w, zm);
-  smooth_box<NT>(g, B, K, f, bcv, beta, fac + B.fac, fact + B.fac, tcoup, p, gflux, w, zm, dsm);
+  if constexpr (RES) {
+    smooth_box_res<NT>(geo2(g), B, st, fac + B.fac, fact + B.fac, tcoup, p, gflux, dsm);
+  } else {
+    double w[RING][HB], zm[HB];
+    smooth_preload<NT>(B, fac + B.fac, fact + B.fac, w, zm);
+    smooth_box<NT>(g, B, K, f, bcv, beta, fac + B.fac, fact + B.fac, tcoup, p, gflux, w, zm, dsm);
+  }
 }
 
 // All colour phases of nphase / ncol smoothing steps in one cooperative
 // launch.  In phase k (colour k % ncol) workgroup b takes boxes b, b + G,
 // b + 2G, ... of that colour (G workgroups, all resident at once), and a
 // grid-wide barrier separates the phases, so that a phase reads the state
-// its predecessors wrote.  After each box a workgroup already loads the
-// first factor blocks of its next box, also across the barrier (factors do
-// not change during smoothing).  Every workgroup passes every barrier.
-template <int NT>
+// its predecessors wrote.  Without resident factors (RES) a workgroup loads
+// the first factor blocks of its next box already after each box, also
+// across the barrier (factors do not change during smoothing).  Every
+// workgroup passes every barrier.
+template <int NT, bool RES>
 __global__ void __launch_bounds__(NT) k_smooth_grid(Geo g, const Box* __restrict__ boxes,
                                                     SmoothPhases ph, int nphase,
                                                     const double* __restrict__ K,
@@ -415,34 +567,45 @@ __global__ void __launch_bounds__(NT) k_smooth_grid(Geo g, const Box* __restrict
                                                     const double* __restrict__ bcv, double beta,
                                                     const double* __restrict__ fac,
                                                     const double* __restrict__ fact,
-                                                    const double* __restrict__ tcoup, double* p,
-                                                    double* gflux) {
+                                                    const double* __restrict__ tcoup,
+                                                    SmoothStatic st, double* p, double* gflux) {
   extern __shared__ __align__(16) double dsm[];
   cooperative_groups::grid_group grid = cooperative_groups::this_grid();
   const int G = gridDim.x, b0 = blockIdx.x;
   auto count = [&](int k) { return ph.off[k % ph.ncol + 1] - ph.off[k % ph.ncol]; };
   auto box_at = [&](int k, int j) { return ph.off[k % ph.ncol] + j; };
-  auto preload = [&](int bi, double w[RING][HB], double zm[HB]) {
-    const Box B = boxes[bi];
-    smooth_preload<NT>(B, fac + B.fac, fact + B.fac, w, zm);
-  };
-  double w[RING][HB], zm[HB];
-  int bi = b0 < count(0) ? box_at(0, b0) : -1;
-  if (bi >= 0) preload(bi, w, zm);
-  for (int k = 0; k < nphase; ++k) {
-    const int n = count(k);
-    const int n1 = k + 1 < nphase ? count(k + 1) : 0;
-    for (int j = b0; j < n; j += G) {
+  if constexpr (RES) {
+    for (int k = 0; k < nphase; ++k) {
+      for (int j = b0; j < count(k); j += G) {
+        const Box B = boxes[box_at(k, j)];
+        smooth_box_res<NT>(geo2(g), B, st, fac + B.fac, fact + B.fac, tcoup, p, gflux, dsm);
+      }
+      grid.sync();
+    }
+  } else {
+    auto preload = [&](int bi, double w[RING][HB], double zm[HB]) {
       const Box B = boxes[bi];
-      smooth_box<NT>(g, B, K, f, bcv, beta, fac + B.fac, fact + B.fac, tcoup, p, gflux, w, zm, dsm);
-      bi = j + G < n ? box_at(k, j + G) : (b0 < n1 ? box_at(k + 1, b0) : -1);
-      if (bi >= 0) preload(bi, w, zm);
+      smooth_preload<NT>(B, fac + B.fac, fact + B.fac, w, zm);
+    };
+    double w[RING][HB], zm[HB];
+    int bi = b0 < count(0) ? box_at(0, b0) : -1;
+    if (bi >= 0) preload(bi, w, zm);
+    for (int k = 0; k < nphase; ++k) {
+      const int n = count(k);
+      const int n1 = k + 1 < nphase ? count(k + 1) : 0;
+      for (int j = b0; j < n; j += G) {
+        const Box B = boxes[bi];
+        smooth_box<NT>(g, B, K, f, bcv, beta, fac + B.fac, fact + B.fac, tcoup, p, gflux, w, zm, dsm);
+        bsync<NT>();  // the next box stages over what its outputs read
+        bi = j + G < n ? box_at(k, j + G) : (b0 < n1 ? box_at(k + 1, b0) : -1);
+        if (bi >= 0) preload(bi, w, zm);
+      }
+      if (b0 >= n && b0 < n1) {
+        bi = box_at(k + 1, b0);
+        preload(bi, w, zm);
+      }
+      grid.sync();
     }
-    if (b0 >= n && b0 < n1) {
-      bi = box_at(k + 1, b0);
-      preload(bi, w, zm);
-    }
-    grid.sync();
   }
 }
 
@@ -453,6 +616,8 @@ hipError_t set_lds(KF kern, size_t bytes) {
                                (int)bytes);
   return hipSuccess;
 }
+
+SmoothStatic statics(const SmoothArrays& a) { return SmoothStatic{a.b0, a.fc, a.gc, a.fstride}; }
 
 }  // namespace
 
@@ -466,13 +631,17 @@ size_t wave_lds_bytes(int m0, int m1, int nrhs, int kc) {
 
 size_t wave_smooth_lds_bytes(int m0, int m1, int kc) { return sizeof(double) * smooth_lds_doubles(m0, m1, kc); }
 
+size_t wave_smooth_res_lds_bytes(int m0, int m1) { return sizeof(double) * smooth_res_doubles(m0, m1); }
+
+long long wave_packed_elems(int nb) { return packed_elems(nb); }
+
 hipError_t launch_local_w(const Geo& g, const Box* obox, const Box* pbox, int nbox,
                           const Seed* seeds, const double* logK, double* K, const double* f,
                           const double* bcv,
                           double beta, double* fac, double* tcoup, double* facp, double* tcp,
                           double* Pk, double* tr_u, double* tr_phi, double* tr_beta, double* pbar,
-                          double* ubar, double* pibar, double* fact, int* flags, size_t lds,
-                          size_t lds_part, hipStream_t s) {
+                          double* ubar, double* pibar, double* fact, const SmoothArrays& sa,
+                          int* flags, size_t lds, size_t lds_part, hipStream_t s) {
   if (nbox <= 0) return hipSuccess;
   hipError_t e = set_lds(k_local_w, lds);
   if (e != hipSuccess) return e;
@@ -490,35 +659,42 @@ hipError_t launch_local_w(const Geo& g, const Box* obox, const Box* pbox, int nb
   if ((size_t)part_ld * sizeof(double) > lds) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_local_w, dim3(nbox + (nbox + npart - 1) / npart), dim3(128), lds, s, g, obox,
                      pbox, nbox, seeds, logK, K, f, bcv, beta, fac, tcoup, facp, tcp, Pk, tr_u,
-                     tr_phi, tr_beta, pbar, ubar, pibar, fact, npart, part_ld, flags);
+                     tr_phi, tr_beta, pbar, ubar, pibar, fact, statics(sa), npart, part_ld, flags);
   return hipGetLastError();
 }
 
 hipError_t launch_factor_w(const Geo& g, const Box* obox, int nbox, const double* logK,
-                           double beta, double* fac, double* fact, int* flags, size_t lds,
-                           hipStream_t s) {
+                           double beta, const double* f, const double* bcv, double* fac, double* fact,
+                           const SmoothArrays& sa, int* flags, size_t lds, hipStream_t s) {
   if (nbox <= 0) return hipSuccess;
   if (!fac || !fact) return hipErrorInvalidValue;
   hipError_t e = set_lds(k_factor_w, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_factor_w, dim3(nbox), dim3(128), lds, s, g, obox, logK, beta, fac, fact,
-                     flags);
+  hipLaunchKernelGGL(k_factor_w, dim3(nbox), dim3(128), lds, s, g, obox, logK, beta, f, bcv, fac, fact,
+                     statics(sa), flags);
   return hipGetLastError();
 }
 
 hipError_t launch_smooth_w(const Geo& g, const Box* boxes, int nmem,
                            const double* K, const double* f, const double* bcv, double beta,
-                           const double* fac, const double* fact, const double* tcoup, double* scr,
-                           double* p, double* gflux, size_t lds, int nt, hipStream_t s) {
-  (void)scr;
+                           const double* fac, const double* fact, const double* tcoup,
+                           const SmoothArrays& sa, double* p, double* gflux, size_t lds, size_t lds_res,
+                           int nt, hipStream_t s) {
   if (nmem <= 0) return hipSuccess;
   if (!fact) return hipErrorInvalidValue;
   hipError_t e;
 #define MRCM_SMOOTH_NT(N)                                                                     \
-  e = set_lds(k_smooth_w<N>, lds);                                                            \
-  if (e != hipSuccess) return e;                                                              \
-  hipLaunchKernelGGL(k_smooth_w<N>, dim3(nmem), dim3(N), lds, s, g, boxes, K, f, bcv,          \
-                     beta, fac, fact, tcoup, p, gflux);
+  if (lds_res) {                                                                              \
+    e = set_lds(k_smooth_w<N, true>, lds_res);                                                \
+    if (e != hipSuccess) return e;                                                            \
+    hipLaunchKernelGGL((k_smooth_w<N, true>), dim3(nmem), dim3(N), lds_res, s, g, boxes, K, f, bcv, \
+                       beta, fac, fact, tcoup, statics(sa), p, gflux);                        \
+  } else {                                                                                    \
+    e = set_lds(k_smooth_w<N, false>, lds);                                                   \
+    if (e != hipSuccess) return e;                                                            \
+    hipLaunchKernelGGL((k_smooth_w<N, false>), dim3(nmem), dim3(N), lds, s, g, boxes, K, f, bcv, \
+                       beta, fac, fact, tcoup, statics(sa), p, gflux);                        \
+  }
   if (nt == 64) {
     MRCM_SMOOTH_NT(64)
   } else if (nt == 128) {
@@ -534,8 +710,8 @@ hipError_t launch_smooth_w(const Geo& g, const Box* boxes, int nmem,
 
 hipError_t launch_smooth_grid(const Geo& g, const Box* boxes, const SmoothPhases& ph, int nphase, const double* K, const double* f,
                               const double* bcv, double beta, const double* fac, const double* fact,
-                              const double* tcoup, double* p, double* gflux, size_t lds, int nt,
-                              int max_groups, hipStream_t s) {
+                              const double* tcoup, const SmoothArrays& sa, double* p, double* gflux,
+                              size_t lds_ring, size_t lds_res, int nt, int max_groups, hipStream_t s) {
   if (nphase <= 0) return hipSuccess;
   if (!fact || ph.ncol <= 0 || ph.ncol > 8 || max_groups < 0) return hipErrorInvalidValue;
   int nbox = 0;
@@ -549,7 +725,9 @@ hipError_t launch_smooth_grid(const Geo& g, const Box* boxes, const SmoothPhases
   if (!coop) return hipErrorNotSupported;
   Geo gg = g;
   SmoothPhases pp = ph;
-  void* args[] = {&gg, &boxes, &pp, &nphase, &K, &f, &bcv, &beta, &fac, &fact, &tcoup, &p, &gflux};
+  SmoothStatic st = statics(sa);
+  const size_t lds = lds_res ? lds_res : lds_ring;
+  void* args[] = {&gg, &boxes, &pp, &nphase, &K, &f, &bcv, &beta, &fac, &fact, &tcoup, &st, &p, &gflux};
   auto go = [&](auto kern, int N) -> hipError_t {
     hipError_t r = set_lds(kern, lds);
     if (r != hipSuccess) return r;
@@ -561,9 +739,9 @@ hipError_t launch_smooth_grid(const Geo& g, const Box* boxes, const SmoothPhases
     if (grid <= 0) return hipErrorCooperativeLaunchTooLarge;
     return hipLaunchCooperativeKernel((const void*)kern, dim3((unsigned)grid), dim3(N), args, lds, s);
   };
-  if (nt == 64) return go(k_smooth_grid<64>, 64);
-  if (nt == 128) return go(k_smooth_grid<128>, 128);
-  if (nt == 256) return go(k_smooth_grid<256>, 256);
+  if (nt == 64) return lds_res ? go(k_smooth_grid<64, true>, 64) : go(k_smooth_grid<64, false>, 64);
+  if (nt == 128) return lds_res ? go(k_smooth_grid<128, true>, 128) : go(k_smooth_grid<128, false>, 128);
+  if (nt == 256) return lds_res ? go(k_smooth_grid<256, true>, 256) : go(k_smooth_grid<256, false>, 256);
   return hipErrorInvalidValue;
 }
 

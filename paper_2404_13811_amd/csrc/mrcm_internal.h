@@ -145,6 +145,18 @@ size_t wave_lds_bytes(int m0, int m1, int nrhs, int kc);
 // LDS of a two-wave basis box of k_local_w
 size_t wave_basis_lds_bytes(int m0, int m1, int nrhs, int kc);
 size_t wave_smooth_lds_bytes(int m0, int m1, int kc);
+// LDS of a smoothing box with its factors resident, and the doubles of one
+// packed factor block of nb cells
+size_t wave_smooth_res_lds_bytes(int m0, int m1);
+long long wave_packed_elems(int nb);
+// What smoothing keeps per box beside the factors (written with them; null:
+// not kept): the static right-hand side (layout of the block couplings),
+// two coefficients per box-side face (fstride doubles per box), one per
+// Gamma face (layout of the Gamma fluxes).
+struct SmoothArrays {
+  double *b0, *fc, *gc;
+  int fstride;
+};
 // Steps 1-2 (oversampled boxes obox) and Step 4 (subdomain boxes pbox, one
 // or two per workgroup) in one launch; lds_part = LDS of one subdomain box,
 // lds >= the basis boxes' need and lds_part (two per workgroup when lds
@@ -158,19 +170,22 @@ hipError_t launch_local_w(const Geo& g, const Box* obox, const Box* pbox, int nb
                           const double* bcv,
                           double beta, double* fac, double* tcoup, double* facp, double* tcp,
                           double* Pk, double* tr_u, double* tr_phi, double* tr_beta, double* pbar,
-                          double* ubar, double* pibar, double* fact, int* flags, size_t lds,
-                          size_t lds_part, hipStream_t s);
+                          double* ubar, double* pibar, double* fact, const SmoothArrays& sa,
+                          int* flags, size_t lds, size_t lds_part, hipStream_t s);
 // Algorithm 1, Step 6: the oversampled boxes factored again with the
 // smoothing Robin parameter into fac (forward inverses) and fact (backward
 // inverses, meeting block), the layout k_local_w writes; lds as its basis
 // boxes with no right-hand side
 hipError_t launch_factor_w(const Geo& g, const Box* obox, int nbox, const double* logK,
-                           double beta, double* fac, double* fact, int* flags, size_t lds,
-                           hipStream_t s);
+                           double beta, const double* f, const double* bcv, double* fac, double* fact,
+                           const SmoothArrays& sa, int* flags, size_t lds, hipStream_t s);
+// lds_res != 0: the form with resident factors (LDS bytes of its largest
+// box); 0: the form that streams them (lds bytes)
 hipError_t launch_smooth_w(const Geo& g, const Box* boxes, int nmem,
                            const double* K, const double* f, const double* bcv, double beta,
-                           const double* fac, const double* fact, const double* tcoup, double* scr,
-                           double* p, double* gflux, size_t lds, int nt, hipStream_t s);
+                           const double* fac, const double* fact, const double* tcoup,
+                           const SmoothArrays& sa, double* p, double* gflux, size_t lds, size_t lds_res,
+                           int nt, hipStream_t s);
 // colour phases of the smoothing sweep: boxes of colour c are
 // members[off[c] .. off[c+1])
 struct SmoothPhases {
@@ -186,8 +201,8 @@ struct SmoothPhases {
 // launched in either case)
 hipError_t launch_smooth_grid(const Geo& g, const Box* boxes, const SmoothPhases& ph, int nphase, const double* K, const double* f,
                               const double* bcv, double beta, const double* fac, const double* fact,
-                              const double* tcoup, double* p, double* gflux, size_t lds, int nt,
-                              int max_groups, hipStream_t s);
+                              const double* tcoup, const SmoothArrays& sa, double* p, double* gflux,
+                              size_t lds_ring, size_t lds_res, int nt, int max_groups, hipStream_t s);
 
 // one-wavefront-per-box 3-D kernels (local3.hip), plane blocks of <= 64 cells
 size_t box3_lds_bytes(int m0, int m1, int m2, int nrhs, int kc);

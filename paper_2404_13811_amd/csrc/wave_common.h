@@ -93,14 +93,17 @@ __device__ __forceinline__ float half_sum_f(float v) {
 // into zeros; the block index goes into the scalar offset.  FP64 blocks are
 // the inverses of symmetric Schur complements and are stored as their lower
 // triangle, row-major (entry (r, c), r >= c, at r (r + 1) / 2 + c; both
-// (r, c) and (c, r) read it): half the bytes of a full block.  FP32 blocks
+// (r, c) and (c, r) read it): half the bytes of a full block, padded to an
+// even number so that every block starts at a 16-byte boundary.  FP32 blocks
 // are stored whole (nb x nb row-major).
 template <typename T>
 __host__ __device__ constexpr bool packed_blocks() { return sizeof(T) == 8; }
 
+__host__ __device__ inline int packed_elems(int nb) { return (nb * (nb + 1) / 2 + 1) / 2 * 2; }
+
 template <typename T>
 __host__ __device__ inline int block_elems(int nb) {
-  return packed_blocks<T>() ? nb * (nb + 1) / 2 : nb * nb;
+  return packed_blocks<T>() ? packed_elems(nb) : nb * nb;
 }
 template <typename T>
 struct BlockSrc {
@@ -467,11 +470,12 @@ __device__ __forceinline__ int bloc(const Box& B, const BoxLds& s, int x, int y)
 }
 
 // Physical right-hand side (source, boundary data) of box B into out.
+template <int NT = 64>
 __device__ __forceinline__ void physical_rhs(const Geo& g, const Box& B, const BoxLds& s, const double* f,
                              const double* bcv, double* out) {
   const int nc = s.m0 * s.m1;
   #pragma unroll 1
-  for (int loc = lane_id(); loc < nc; loc += 64) {
+  for (int loc = threadIdx.x % NT; loc < nc; loc += NT) {
     const int x = B.lo[0] + loc % s.m0, y = B.lo[1] + loc / s.m0;
     const int ci = x + g.n[0] * y;
     double b = f[ci] * g.vol;
@@ -754,6 +758,35 @@ __device__ __forceinline__ double wgemv2(const double w[HB], const double* z) {
     a1 = fma(w[2 * i + 1], v.y, a1);
   }
   return half_sum(a0 + a1);
+}
+
+// W_j z without LDS, for the single-vector sweeps: the lane holds z[zi],
+// zi = 16 h + lane % 16 (the index its half of the columns needs), and a row
+// broadcast hands z[16 h + k] to the 16 lanes of its row inside the
+// multiply-add (v_fmac_f64 with row_newbcast), so a block step is 16
+// instructions in four chains, the sum of the halves and one exchange of
+// 16-lane rows.  The leading wait states cover the write of z.
+__device__ __forceinline__ double wgemv_rows(const double w[HB], double z) {
+  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+#define MRCM_F(A, I, K) "v_fmac_f64_dpp %" #A ", %4, %" #I " row_newbcast:" #K " row_mask:0xf bank_mask:0xf\n\t"
+  asm("s_nop 1\n\t" MRCM_F(0, 5, 0) MRCM_F(1, 6, 1) MRCM_F(2, 7, 2) MRCM_F(3, 8, 3) MRCM_F(0, 9, 4)
+          MRCM_F(1, 10, 5) MRCM_F(2, 11, 6) MRCM_F(3, 12, 7) MRCM_F(0, 13, 8) MRCM_F(1, 14, 9)
+              MRCM_F(2, 15, 10) MRCM_F(3, 16, 11) MRCM_F(0, 17, 12) MRCM_F(1, 18, 13) MRCM_F(2, 19, 14)
+                  MRCM_F(3, 20, 15)
+      : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3)
+      : "v"(z), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]),
+        "v"(w[8]), "v"(w[9]), "v"(w[10]), "v"(w[11]), "v"(w[12]), "v"(w[13]), "v"(w[14]), "v"(w[15]));
+#undef MRCM_F
+  return half_sum((a0 + a1) + (a2 + a3));
+}
+
+// y of column c = lane % 32 -> y of index zi, by a swap of 16-lane rows
+__device__ __forceinline__ double to_rows(double y) {
+  const int lo = __double2loint(y), hi = __double2hiint(y);
+  const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  const bool h = lane_id() >= 32;
+  return __hiloint2double(h ? b[1] : b[0], h ? a[1] : a[0]);
 }
 
 // Forward step of block j for all right-hand sides, inverse in w, with jp
@@ -1082,30 +1115,29 @@ __device__ __forceinline__ void twist_preload(const TwistHalf& hf, double w[RING
 
 // Forward half (ring preloaded); z_j replaces b_j in s.X.
 __device__ __forceinline__ void twist_fwd(const Box& B, const TwistHalf& hf, const BoxLds& s,
-                                          double* z, bool bottom, double w[RING][HB]) {
+                                          bool bottom, double w[RING][HB]) {
   const int L = lane_id();
-  const int c = L & 31, h = L >> 5;
+  const int c = L & 31, h = L >> 5, zi = HB * h + (L & 15);
   const int nb = B.nb;
-  const bool cv = c < nb;
+  const bool cv = c < nb, zv = zi < nb;
   const int cnt = hf.cnt;
   if (cnt <= 0) return;
-  double y = 0.0, tp = 0.0;
-  double xn = cv ? s.X[hf.j0 * nb + c] : 0.0;
+  double yz = 0.0, tp = 0.0;
+  double xn = zv ? s.X[hf.j0 * nb + zi] : 0.0;
   for (int v0 = 0; v0 < cnt + hf.o; v0 += RING) {
 #pragma unroll
     for (int q = 0; q < RING; ++q) {
       const int t = v0 + q - hf.o;
       if (t >= 0 && t < cnt) {
         const int j = hf.j0 + hf.dj * t;
-        double* zb = z + (t & 1) * NBW;
-        if (h == 0) zb[c] = cv ? fma(tp, y, xn) : 0.0;
-        __builtin_amdgcn_wave_barrier();
+        const double z = fma(tp, yz, xn);
         const bool more = t + 1 < cnt;
         const int jn = j + hf.dj;             // next block of this half
         const int ti = bottom ? jn : j;       // coupling between j and jn
-        xn = (more && cv) ? s.X[jn * nb + c] : 0.0;
-        tp = (more && cv) ? s.Tn[ti * nb + c] : 0.0;
-        y = wgemv2(w[q], zb);
+        xn = (more && zv) ? s.X[jn * nb + zi] : 0.0;
+        tp = (more && zv) ? s.Tn[ti * nb + zi] : 0.0;
+        const double y = wgemv_rows(w[q], z);
+        yz = to_rows(y);
         if (h == 0 && cv) s.X[j * nb + c] = y;
         if (t + RING < cnt) wload_block(hf.src, hf.j0 + hf.dj * (t + RING), w[q]);
       }
@@ -1115,33 +1147,29 @@ __device__ __forceinline__ void twist_fwd(const Box& B, const TwistHalf& hf, con
 
 // Meeting block: x_m from b_m and the neighbouring z of both halves; zm
 // holds Z_m in the block register layout.
-__device__ __forceinline__ void twist_mid(const Box& B, const double zm[HB], const BoxLds& s,
-                                          double* z, int m) {
+__device__ __forceinline__ void twist_mid(const Box& B, const double zm[HB], const BoxLds& s, int m) {
   const int L = lane_id();
-  const int c = L & 31, h = L >> 5;
+  const int c = L & 31, h = L >> 5, zi = HB * h + (L & 15);
   const int nb = B.nb, nblk = B.nblk;
-  const bool cv = c < nb;
   double v = 0.0;
-  if (cv) {
-    v = s.X[m * nb + c];
-    if (m > 0) v = fma(s.Tn[(m - 1) * nb + c], s.X[(m - 1) * nb + c], v);
-    if (m + 1 < nblk) v = fma(s.Tn[m * nb + c], s.X[(m + 1) * nb + c], v);
+  if (zi < nb) {
+    v = s.X[m * nb + zi];
+    if (m > 0) v = fma(s.Tn[(m - 1) * nb + zi], s.X[(m - 1) * nb + zi], v);
+    if (m + 1 < nblk) v = fma(s.Tn[m * nb + zi], s.X[(m + 1) * nb + zi], v);
   }
-  if (h == 0) z[c] = v;
-  __builtin_amdgcn_wave_barrier();
-  const double y = wgemv2(zm, z);
-  if (h == 0 && cv) s.X[m * nb + c] = y;
+  const double y = wgemv_rows(zm, v);
+  if (h == 0 && c < nb) s.X[m * nb + c] = y;
 }
 
 // Back-substitution half, outwards from the meeting block.  With
 // have_ring the ring is the one the forward pass of this half left behind.
-__device__ __forceinline__ void twist_back(const Box& B, const TwistHalf& hf, const BoxLds& s,
-                                           double* z, int m, bool bottom, bool have_ring,
-                                           double w[RING][HB]) {
+__device__ __forceinline__ void twist_back(const Box& B, const TwistHalf& hf, const BoxLds& s, int m,
+                                           bool bottom, bool have_ring, double w[RING][HB]) {
   const int L = lane_id();
-  const int c = L & 31, h = L >> 5;
+  const int h = L >> 5, zi = HB * h + (L & 15);
   const int nb = B.nb;
-  const bool cv = c < nb;
+  const bool zv = zi < nb;
+  const bool own = zv && !(L & 16);  // one lane per index
   const int cnt = hf.cnt;
   if (cnt <= 0) return;
   if (!have_ring) {
@@ -1152,9 +1180,9 @@ __device__ __forceinline__ void twist_back(const Box& B, const TwistHalf& hf, co
     }
   }
   const int jf = hf.j0 + hf.dj * (cnt - 1);  // first block of the back pass (next to m)
-  double xnext = cv ? s.X[m * nb + c] : 0.0;
-  double tj = cv ? s.Tn[(bottom ? jf - 1 : jf) * nb + c] : 0.0;
-  double wj = cv ? s.X[jf * nb + c] : 0.0;
+  double xnext = zv ? s.X[m * nb + zi] : 0.0;
+  double tj = zv ? s.Tn[(bottom ? jf - 1 : jf) * nb + zi] : 0.0;
+  double wj = zv ? s.X[jf * nb + zi] : 0.0;
   for (int v0 = 0; v0 < cnt; v0 += RING) {
 #pragma unroll
     for (int q = 0; q < RING; ++q) {
@@ -1162,16 +1190,14 @@ __device__ __forceinline__ void twist_back(const Box& B, const TwistHalf& hf, co
       if (t < cnt) {
         const int b = cnt - 1 - t;
         const int j = hf.j0 + hf.dj * b;
-        double* zb = z + (t & 1) * NBW;
-        if (h == 0) zb[c] = cv ? tj * xnext : 0.0;
-        __builtin_amdgcn_wave_barrier();
+        const double z = tj * xnext;
         const double wcur = wj;
         const bool more = t + 1 < cnt;
         const int jn = j - hf.dj;             // next block, away from m
-        tj = (more && cv) ? s.Tn[(bottom ? jn - 1 : jn) * nb + c] : 0.0;
-        wj = (more && cv) ? s.X[jn * nb + c] : 0.0;
-        xnext = wcur + wgemv2(w[RING - 1 - q], zb);
-        if (h == 0 && cv) s.X[j * nb + c] = xnext;
+        tj = (more && zv) ? s.Tn[(bottom ? jn - 1 : jn) * nb + zi] : 0.0;
+        wj = (more && zv) ? s.X[jn * nb + zi] : 0.0;
+        xnext = wcur + to_rows(wgemv_rows(w[RING - 1 - q], z));
+        if (own) s.X[j * nb + zi] = xnext;
         if (b - RING >= 0) wload_block(hf.src, hf.j0 + hf.dj * (b - RING), w[RING - 1 - q]);
       }
     }
@@ -1192,32 +1218,358 @@ __device__ __forceinline__ void sweep_twisted(const Box& B, const double* Wf, co
                                               const double zm[HB]) {
   const int wv = threadIdx.x >> 6;
   const int m = B.nblk / 2;
-  double* za = z;
-  double* zb = z + 2 * NBW;
   const TwistHalf top = twist_half(B, Wf, m, false);
   const TwistHalf bot = twist_half(B, Wt, m, true);
   if (NT == 64) {
     twist_preload(top, w);
-    twist_fwd(B, top, s, za, false, w);
+    twist_fwd(B, top, s, false, w);
     twist_preload(bot, w);
-    twist_fwd(B, bot, s, zb, true, w);
+    twist_fwd(B, bot, s, true, w);
   } else if (wv == 0) {
-    twist_fwd(B, top, s, za, false, w);
+    twist_fwd(B, top, s, false, w);
   } else if (wv == 1) {
-    twist_fwd(B, bot, s, zb, true, w);
+    twist_fwd(B, bot, s, true, w);
   }
   bsync<NT>();
-  if (wv == 0) twist_mid(B, zm, s, za, m);
+  if (wv == 0) twist_mid(B, zm, s, m);
   bsync<NT>();
   if (NT == 64) {
-    twist_back(B, top, s, za, m, false, false, w);
-    twist_back(B, bot, s, zb, m, true, false, w);
+    twist_back(B, top, s, m, false, false, w);
+    twist_back(B, bot, s, m, true, false, w);
   } else if (wv == 0) {
-    twist_back(B, top, s, za, m, false, true, w);
+    twist_back(B, top, s, m, false, true, w);
   } else if (wv == 1) {
-    twist_back(B, bot, s, zb, m, true, true, w);
+    twist_back(B, bot, s, m, true, true, w);
   }
   bsync<NT>();
+}
+
+// ------------------------------------------------- factors resident in LDS
+// The two-ended sweep with all block inverses of the box in LDS: an image of
+// the packed blocks 0 .. m-1 (forward) and m .. nblk-1 (meeting block and
+// backward), copied there once by the whole workgroup in 16-byte pieces
+// (global_load_lds: no registers, every piece in flight at once).
+// Why: read per lane from memory, a block is 16 gathers of 64 scattered
+// 8-byte entries, and their address processing, not the dependency chain,
+// set the time of a block step (760 cycles on lines of 24 cells, the same
+// with the products' operands through LDS or by row broadcasts, in the
+// forward pass from memory and in the back pass from L2).  From LDS the
+// gathers are nearly free of bank conflicts (triangular numbers modulo 32
+// are a permutation) and each block crosses the memory bus once instead of
+// twice.  A block step takes 480 cycles: 192 of dependency chain, the rest
+// the issue of its reads and their addresses by the one wave.
+// Measured per colour phase, with smooth_static: 64 boxes of 24 x 24 cells
+// 17.4 -> 10.2 us, 4 boxes of 20 x 20 15.6 -> 8.2 us, 1024 boxes of 24 x 24
+// (two per CU) 39 -> 27 us.
+__host__ __device__ inline size_t factor_image_doubles(int nb, int nblk) {
+  return (size_t)nblk * packed_elems(nb);
+}
+
+// n doubles (rounded up to even) from src to LDS, both 16-byte aligned, by
+// the NT threads of the box; complete after staged_wait.
+template <int NT>
+__device__ __forceinline__ void stage_lds(const double* src, double* dst, int n) {
+  const int n2 = (n + 1) / 2, l = lane_id();
+  const int w0 = __builtin_amdgcn_readfirstlane((int)(threadIdx.x % NT) & ~63);
+  for (int e = w0; e < n2; e += NT) {
+    auto* d = (__attribute__((address_space(3))) void*)(unsigned)(uintptr_t)(dst + 2 * e);
+    auto* a = (__attribute__((address_space(1))) void*)(uintptr_t)(src + 2 * (e + l));
+    if (e + l < n2) __builtin_amdgcn_global_load_lds(a, d, 16, 0, 0);
+  }
+}
+template <int NT>
+__device__ __forceinline__ void staged_wait() {
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  bsync<NT>();
+}
+
+template <int NT>
+__device__ __forceinline__ void stage_factors(const Box& B, const double* Wf, const double* Wt, double* img) {
+  const int m = B.nblk / 2, be = packed_elems(B.nb);
+  stage_lds<NT>(Wf, img, m * be);
+  stage_lds<NT>(Wt + (long long)m * be, img + m * be, (B.nblk - m) * be);
+}
+
+// Lanes of a block step with resident factors: the lines are cut into two
+// parts of nh = (nb + 1) / 2 <= KN entries; lane (g, i) (g = lane / 16,
+// i = lane % 16) holds row nh (g % 2) + i and the columns of part g / 2, and
+// of a vector entry nh (g / 2) + i.  The exchange of 16-lane rows (to_rows)
+// then turns products into vector entries as before, and a step takes KN
+// products and reads instead of 16.  Entries outside the block read a valid
+// one instead: rows beyond give results nobody reads, columns beyond meet a
+// zero.
+template <int KN>
+struct LdsFac {
+  const double* img;
+  int off[KN], be, nb, nblk;
+  int zi, ci;     // vector entry and row of the lane
+  bool zv, cv;    // valid; cv: in one lane per row
+  bool zo;        // valid in one lane per entry
+};
+template <int KN>
+__device__ __forceinline__ LdsFac<KN> lds_fac(const Box& B, const double* img) {
+  LdsFac<KN> f;
+  f.img = img;
+  f.nb = B.nb;
+  f.nblk = B.nblk;
+  f.be = packed_elems(B.nb);
+  const int nb = B.nb, nh = (nb + 1) / 2, L = lane_id(), i = L & 15, g = L >> 4;
+  const int rr = nh * (g & 1) + i, zz = nh * (g >> 1) + i;
+  const bool in = i < nh;
+  f.cv = in && rr < nb && g < 2;
+  f.zv = in && zz < nb;
+  f.zo = f.zv && !(g & 1);
+  f.ci = min(rr, nb - 1);
+  f.zi = min(zz, nb - 1);
+  const int c = f.ci;
+#pragma unroll
+  for (int k = 0; k < KN; ++k) {
+    const int r = min(nh * (g >> 1) + k, nb - 1);
+    const int hi = r > c ? r : c, lo = r > c ? c : r;
+    f.off[k] = hi * (hi + 1) / 2 + lo;
+  }
+  return f;
+}
+template <int KN, int K0 = 0, int K1 = KN>
+__device__ __forceinline__ void lds_block(const LdsFac<KN>& f, int j, double w[KN]) {
+  const double* b = f.img + j * f.be;
+#pragma unroll
+  for (int k = K0; k < K1; ++k) w[k] = b[f.off[k]];
+}
+// reads issued before the current block's products: at most 15 LDS
+// operations can be told apart by a wait, and more would make it wait for
+// some of the new ones
+constexpr int kAhead = 8;
+
+// y of the lane's row: wgemv_rows over KN columns
+template <int KN>
+__device__ __forceinline__ double lds_gemv(const double w[KN], double z) {
+  double a0 = 0.0, a1 = 0.0;
+#define MRCM_P(I0, K0, I1, K1)                                                                     \
+  "v_fmac_f64_dpp %0, %2, %" #I0 " row_newbcast:" #K0 " row_mask:0xf bank_mask:0xf\n\t"            \
+  "v_fmac_f64_dpp %1, %2, %" #I1 " row_newbcast:" #K1 " row_mask:0xf bank_mask:0xf\n\t"
+#define MRCM_S10                                                                                   \
+  "s_nop 1\n\t" MRCM_P(3, 0, 4, 1) MRCM_P(5, 2, 6, 3) MRCM_P(7, 4, 8, 5) MRCM_P(9, 6, 10, 7)       \
+      MRCM_P(11, 8, 12, 9)
+#define MRCM_S12 MRCM_S10 MRCM_P(13, 10, 14, 11)
+#define MRCM_S14 MRCM_S12 MRCM_P(15, 12, 16, 13)
+#define MRCM_S16 MRCM_S14 MRCM_P(17, 14, 18, 15)
+#define MRCM_W10                                                                                   \
+  "v"(z), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]),    \
+      "v"(w[8]), "v"(w[9])
+  static_assert(KN == 10 || KN == 12 || KN == 14 || KN == 16, "products per block step");
+  if constexpr (KN == 10) asm(MRCM_S10 : "+v"(a0), "+v"(a1) : MRCM_W10);
+  if constexpr (KN == 12) asm(MRCM_S12 : "+v"(a0), "+v"(a1) : MRCM_W10, "v"(w[10]), "v"(w[11]));
+  if constexpr (KN == 14)
+    asm(MRCM_S14 : "+v"(a0), "+v"(a1) : MRCM_W10, "v"(w[10]), "v"(w[11]), "v"(w[12]), "v"(w[13]));
+  if constexpr (KN == 16)
+    asm(MRCM_S16
+        : "+v"(a0), "+v"(a1)
+        : MRCM_W10, "v"(w[10]), "v"(w[11]), "v"(w[12]), "v"(w[13]), "v"(w[14]), "v"(w[15]));
+#undef MRCM_P
+#undef MRCM_S10
+#undef MRCM_S12
+#undef MRCM_S14
+#undef MRCM_S16
+#undef MRCM_W10
+  return half_sum(a0 + a1);
+}
+
+// One half of the two-ended sweep (see twist_fwd and twist_back), the next
+// block's entries and the next line's vector entries read before the current
+// block's products are issued.
+template <int KN>
+__device__ __forceinline__ void lds_fwd(const LdsFac<KN>& f, const double* Tn, double* X, int m, bool bottom) {
+  const int nb = f.nb, cnt = bottom ? f.nblk - 1 - m : m;
+  if (cnt <= 0) return;
+  const int dj = bottom ? -1 : 1;
+  int j = bottom ? f.nblk - 1 : 0;
+  double yz = 0.0, tp = 0.0;
+  double xn = X[j * nb + f.zi];
+  xn = f.zv ? xn : 0.0;
+  double wa[KN], wb[KN];
+  lds_block(f, j, wa);
+  auto step = [&](const double* w, double* wn, bool more) {
+    const double z = fma(tp, yz, xn);
+    const int jn = more ? j + dj : j;
+    xn = X[jn * nb + f.zi];
+    tp = Tn[(bottom ? jn : j) * nb + f.zi];
+    lds_block<KN, 0, kAhead>(f, jn, wn);
+    __builtin_amdgcn_sched_barrier(0);
+    const double y = lds_gemv<KN>(w, z);
+    lds_block<KN, kAhead>(f, jn, wn);
+    yz = to_rows(y);
+    if (f.cv) X[j * nb + f.ci] = y;
+    xn = f.zv ? xn : 0.0;
+    tp = f.zv ? tp : 0.0;
+    j = jn;
+  };
+  int t = 0;
+  for (; t + 1 < cnt; t += 2) {
+    step(wa, wb, true);
+    step(wb, wa, t + 2 < cnt);
+  }
+  if (t < cnt) step(wa, wb, false);
+}
+
+template <int KN>
+__device__ __forceinline__ void lds_mid(const LdsFac<KN>& f, const double* Tn, double* X, int m) {
+  const int nb = f.nb;
+  double w[KN];
+  lds_block(f, m, w);
+  double v = X[m * nb + f.zi];
+  if (m > 0) v = fma(Tn[(m - 1) * nb + f.zi], X[(m - 1) * nb + f.zi], v);
+  if (m + 1 < f.nblk) v = fma(Tn[m * nb + f.zi], X[(m + 1) * nb + f.zi], v);
+  const double y = lds_gemv<KN>(w, f.zv ? v : 0.0);
+  if (f.cv) X[m * nb + f.ci] = y;
+}
+
+template <int KN>
+__device__ __forceinline__ void lds_back(const LdsFac<KN>& f, const double* Tn, double* X, int m, bool bottom) {
+  const int nb = f.nb, cnt = bottom ? f.nblk - 1 - m : m;
+  if (cnt <= 0) return;
+  const int dj = bottom ? 1 : -1;
+  int j = m + dj;
+  double xnext = X[m * nb + f.zi];
+  double tj = Tn[(bottom ? j - 1 : j) * nb + f.zi];
+  tj = f.zv ? tj : 0.0;
+  double wj = X[j * nb + f.zi];
+  double wa[KN], wb[KN];
+  lds_block(f, j, wa);
+  auto step = [&](const double* w, double* wn, bool more) {
+    const double z = tj * xnext, wcur = wj;
+    const int jn = more ? j + dj : j;
+    tj = Tn[(bottom ? jn - 1 : jn) * nb + f.zi];
+    wj = X[jn * nb + f.zi];
+    lds_block<KN, 0, kAhead>(f, jn, wn);
+    __builtin_amdgcn_sched_barrier(0);
+    const double y = lds_gemv<KN>(w, z);
+    lds_block<KN, kAhead>(f, jn, wn);
+    xnext = wcur + to_rows(y);
+    if (f.zo) X[j * nb + f.zi] = xnext;
+    tj = f.zv ? tj : 0.0;
+    j = jn;
+  };
+  int t = 0;
+  for (; t + 1 < cnt; t += 2) {
+    step(wa, wb, true);
+    step(wb, wa, t + 2 < cnt);
+  }
+  if (t < cnt) step(wa, wb, false);
+}
+
+template <int NT, int KN>
+__device__ __forceinline__ void lds_sweep_k(const Box& B, const double* img, const double* Tn, double* X) {
+  const int wv = (int)(threadIdx.x % NT) >> 6, m = B.nblk / 2;
+  const LdsFac<KN> f = lds_fac<KN>(B, img);
+  if (wv < 2) {
+    if (NT == 64 || wv == 0) lds_fwd(f, Tn, X, m, false);
+    if (NT == 64 || wv == 1) lds_fwd(f, Tn, X, m, true);
+  }
+  bsync<NT>();
+  if (wv == 0) lds_mid(f, Tn, X, m);
+  bsync<NT>();
+  if (wv < 2) {
+    if (NT == 64 || wv == 0) lds_back(f, Tn, X, m, false);
+    if (NT == 64 || wv == 1) lds_back(f, Tn, X, m, true);
+  }
+  bsync<NT>();
+}
+
+// The whole two-ended sweep of one right-hand side in X (LDS; couplings to
+// the next line in Tn) by the NT threads of a box: the halves on waves 0
+// and 1 when NT >= 128, else one after the other.  The result does not
+// depend on NT.  Ends with a barrier of the box.
+template <int NT>
+__device__ __forceinline__ void lds_sweep(const Box& B, const double* img, const double* Tn, double* X) {
+  if (B.nb <= 20) lds_sweep_k<NT, 10>(B, img, Tn, X);
+  else if (B.nb <= 24) lds_sweep_k<NT, 12>(B, img, Tn, X);
+  else if (B.nb <= 28) lds_sweep_k<NT, 14>(B, img, Tn, X);
+  else lds_sweep_k<NT, 16>(B, img, Tn, X);
+}
+
+// ------------------------------------------------ what smoothing keeps per box
+// Everything of a box's smoothing problem that does not change between
+// colour phases is written once with the factors (smooth_static):
+//   b0   its right-hand side of the source and the boundary data,
+//   fc   two coefficients per face of the box sides (side_off order): with
+//        overlap T^R and T = |e| K_H / h, so that T^R lambda =
+//        T^R p_c - T (p_c - p_o); without, T^R and T^R (beta - h / (2 K_o))
+//        of lambda = p_o + (beta - h / (2 K_o)) u_j; zero on the domain
+//        boundary,
+//   gc   K_H / h of every Gamma face (the layout of gflux).
+// A phase then reads the factors, b0, the couplings, these coefficients and
+// the pressures on both sides of the box sides, and no permeability.
+struct SmoothStatic {
+  double *b0, *fc, *gc;
+  int fstride;  // doubles of fc per box
+};
+
+__device__ __forceinline__ int face_off(int m0, int m1, int q) {
+  return q == 0 ? 0 : q == 1 ? m1 : q == 2 ? 2 * m1 : 2 * m1 + m0;
+}
+// side of face u (side_off order) and its position on it
+__device__ __forceinline__ int face_side(int m0, int m1, int u, int& t) {
+  const int q = u < 2 * m1 ? (u < m1 ? 0 : 1) : (u < 2 * m1 + m0 ? 2 : 3);
+  t = u - face_off(m0, m1, q);
+  return q;
+}
+// its cell in the box [lo0, hi0) x [lo1, hi1) and the one across (by value:
+// a select between fields of a Box held by reference is one of addresses)
+__device__ __forceinline__ void face_cells(int lo0, int lo1, int hi0, int hi1, int q, int t, int& x, int& y,
+                                           int& ox, int& oy) {
+  const int a = q >> 1, sd = q & 1;
+  x = a == 0 ? (sd ? hi0 - 1 : lo0) : lo0 + t;
+  y = a == 1 ? (sd ? hi1 - 1 : lo1) : lo1 + t;
+  ox = x + (a == 0 ? (sd ? 1 : -1) : 0);
+  oy = y + (a == 1 ? (sd ? 1 : -1) : 0);
+}
+
+// from the K tile of the box in LDS, by NT threads
+template <int NT>
+__device__ __forceinline__ void smooth_static(const Geo& g, const Box& B, const BoxLds& s,
+                                              const double* __restrict__ f,
+                                              const double* __restrict__ bcv, double beta,
+                                              const SmoothStatic& st) {
+  const int tid = threadIdx.x % NT, m0 = s.m0, m1 = s.m1;
+  physical_rhs<NT>(g, B, s, f, bcv, st.b0 + B.scr);
+  double* fc = st.fc + (long long)B.sub * st.fstride;
+#pragma unroll 1
+  for (int u = tid; u < 2 * (m0 + m1); u += NT) {
+    int t, x, y, ox, oy;
+    const int q = face_side(m0, m1, u, t), a = q >> 1;
+    face_cells(B.lo[0], B.lo[1], B.hi[0], B.hi[1], q, t, x, y, ox, oy);
+    double c0 = 0.0, c1 = 0.0;
+    if (!off_domain(g, a, a == 0 ? x : y, a == 0 ? ox : oy)) {
+      const double kc = kat(s, B, x, y, a), ko = kat(s, B, ox, oy, a);
+      double bt;
+      robin_face(g, a, kc, ko, beta, bt, c0);
+      c1 = g.l > 0 ? g.area * 2.0 * kc * ko * rcp_d(kc + ko) * rcp_d(g.h)
+                   : c0 * (bt - g.h * 0.5 * rcp_d(ko));
+    }
+    fc[2 * u] = c0;
+    fc[2 * u + 1] = c1;
+  }
+  int olo[3], ohi[3];
+  womega(g, B.sub, olo, ohi);
+#pragma unroll 1
+  for (int u = tid; u < 2 * (g.S[0] + g.S[1]); u += NT) {
+    int t;
+    const int q = face_side(g.S[0], g.S[1], u, t), a = q >> 1, so = q & 1;
+    int x, y;
+    wgface(olo, ohi, q, t, x, y);
+    const int ox = x + (a == 0 ? (so ? 1 : -1) : 0), oy = y + (a == 1 ? (so ? 1 : -1) : 0);
+    const double kc = kat(s, B, x, y, a), ko = kat(s, B, ox, oy, a);
+    const int go = q == 0 ? g.gside_off[0] : q == 1 ? g.gside_off[1] : q == 2 ? g.gside_off[2] : g.gside_off[3];
+    st.gc[(long long)B.sub * g.gstride + go + t] = 2.0 * kc * ko * rcp_d(kc + ko) * rcp_d(g.h);
+  }
+}
+
+// LDS of a smoothing box with resident factors: the image, the solution
+// vector, the couplings, the Robin terms of the box sides.
+__host__ __device__ inline size_t smooth_res_doubles(int m0, int m1) {
+  const size_t nc = ((size_t)m0 * m1 + 1) / 2 * 2;
+  return factor_image_doubles(m0, m1) + 2 * nc + 2 * (size_t)(m0 + m1) + 2;
 }
 
 }  // namespace wave
