@@ -177,6 +177,7 @@ struct mrcm_ctx {
   double *a_pibarb = nullptr, *a_mean = nullptr;
   int* d_seed_sub = nullptr;
   size_t lds_adj_smooth = 0, lds_adj_basis = 0, lds_adj_part = 0;
+  size_t lds_adj_res = 0;  // adjoint smoothing with resident factors (0: streamed)
   size_t lds_adj32_smooth = 0, lds_adj32_basis = 0, lds_adj32_part = 0;
 
   hipEvent_t ev[12] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
@@ -673,7 +674,7 @@ mrcm_status make_plan(mrcm_ctx* c) {
   c->scrp_n = scrp;
   c->wave = c->d == 2;
   c->lds_basis = c->lds_part = c->lds_smooth = c->lds_factor = c->lds_smooth_res = 0;
-  c->lds_adj_smooth = c->lds_adj_basis = c->lds_adj_part = 0;
+  c->lds_adj_smooth = c->lds_adj_basis = c->lds_adj_part = c->lds_adj_res = 0;
   c->lds_adj32_smooth = c->lds_adj32_basis = c->lds_adj32_part = 0;
   for (int i = 0; i < nsub; ++i) {
     const Box& B = c->obox[i];
@@ -690,6 +691,7 @@ mrcm_status make_plan(mrcm_ctx* c) {
     c->lds32_smooth = std::max(c->lds32_smooth, wave32_smooth_lds_bytes(bm0, bm1, kc));
     c->lds32_part = std::max(c->lds32_part, wave32_lds_bytes(P.hi[0] - P.lo[0], P.hi[1] - P.lo[1], 1, 1, kc));
     if (c->d == 2) {
+      c->lds_adj_res = std::max(c->lds_adj_res, adj_smooth_res_lds_bytes(bm0, bm1));
       for (int f32 = 0; f32 < 2; ++f32) {
         size_t& ls = f32 ? c->lds_adj32_smooth : c->lds_adj_smooth;
         size_t& lb = f32 ? c->lds_adj32_basis : c->lds_adj_basis;
@@ -1448,7 +1450,11 @@ mrcm_status tune_smoothing(mrcm_ctx* c, hipStream_t s) {
   HIPCHK(c, hipEventRecord(c->ev[10], s));
   float best = 0.f;
   int best_nt = 256, best_var = 8;
-  const std::vector<int> cand = f3 ? std::vector<int>{8, 4, 2, 0} : std::vector<int>{64, 128, 256};
+  // with resident factors one wave per box is never the fastest (1024 boxes
+  // of 24 x 24 cells: 38 us per phase against 27 and 29)
+  const std::vector<int> cand = f3 ? std::vector<int>{8, 4, 2, 0}
+                                : c->prec == MRCM_FP64 && c->lds_smooth_res ? std::vector<int>{256, 128}
+                                                                            : std::vector<int>{64, 128, 256};
   for (int v : cand) {
     const int nt = f3 ? 256 : v;
     if (f3) c->smooth_cached = v;
@@ -1733,7 +1739,7 @@ mrcm_status mrcm_adjoint(mrcm_ctx* c, const double* dJdp, const double* dJdflux,
     HIPCHK(c, launch_adj_smooth(g, c->d_obox, c->d_members + m0, m1 - m0, c->K, c->f, c->bcv,
                                 c->beta_sm, c->fac, c->fact, c->tco, r32 ? &a32 : nullptr,
                                 c->ck_p + ph * np, c->ck_g + ph * ng, c->a_pb, c->a_gfb, c->a_Kb,
-                                lds_sm, s));
+                                lds_sm, c->lds_adj_res <= 150 * 1024 ? c->lds_adj_res : 0, s));
   }
   // MRCM-O assembly
   HIPCHK(c, launch_adj_combine(g, c->d_seed_sub, c->nX, c->X, c->Pk, c->tr_u, c->a_pb, c->a_gfb,

@@ -396,6 +396,9 @@ struct Adj32 {
   int* flags;
 };
 size_t adj_smooth_lds_bytes(int m0, int m1, bool f32);
+// FP64 form with the box's factors resident (launch_adj_smooth's lds_res; 0:
+// streamed)
+size_t adj_smooth_res_lds_bytes(int m0, int m1);
 size_t adj_basis_lds_bytes(int m0, int m1, int nrhs, bool f32);
 size_t adj_part_lds_bytes(int m0, int m1, bool f32);
 hipError_t launch_adj_out(const Geo& g, const double* K, const double* p, const double* bcv,
@@ -405,7 +408,7 @@ hipError_t launch_adj_smooth(const Geo& g, const Box* boxes, const int* members,
                              const double* K, const double* f, const double* bcv, double beta,
                              const double* fac, const double* fact, const double* tcoup,
                              const Adj32* f32, const double* p_in, const double* gf_in, double* pb,
-                             double* gfb, double* Kb, size_t lds, hipStream_t s);
+                             double* gfb, double* Kb, size_t lds, size_t lds_res, hipStream_t s);
 hipError_t launch_adj_combine(const Geo& g, const int* seed_sub, int nX, const double* X,
                               const double* Pk, const double* tr_u, const double* pb,
                               const double* gfb, double* Xb, double* tr_ub, hipStream_t s);
