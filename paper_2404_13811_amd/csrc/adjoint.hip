@@ -249,18 +249,22 @@ __global__ void __launch_bounds__(kAdjNT) k_adj_smooth(Geo g, const Box* __restr
                                                        double* __restrict__ Kb) {
   constexpr int NT = kAdjNT;
   extern __shared__ __align__(16) double dsm[];
-  __shared__ WaveSmemF sm32;
+  __shared__ int flag32;
   const Box B = boxes[members[blockIdx.x]];
   SmoothLds r = carve_smooth(dsm, B);
   const int m0 = r.b.m0, m1 = r.b.m1, nc = m0 * m1, ns = 2 * (m0 + m1);
   BoxR R{};
-  if (F32) R = carve_smooth_r(dsm, r);
+  Lane32<16> fl{};
+  if (F32) {
+    R = carve_smooth_r(dsm, r);
+    fl = lane32<16>(B, rf.fac + B.fac);
+  }
   double* xs = dsm + (F32 ? adj_smooth32_off(m0, m1) : smooth_lds_doubles(m0, m1));  // forward solution
   double* mu = xs + nc;                             // adjoint right-hand side / solution
   double* lb = mu + nc;                             // lambda_bar per box-side face
   double* img = dsm + adj_res_off(m0, m1);          // RES: factor image
   const int tid = threadIdx.x;
-  if (F32 && tid == 0) sm32.flag = 0;
+  if (F32 && tid == 0) flag32 = 0;
   if constexpr (RES) stage_factors<NT>(B, fac + B.fac, fact + B.fac, img);
   // (a) forward solution of this box from the checkpointed state (the
   // forward smoothing step's arithmetic)
@@ -270,11 +274,10 @@ __global__ void __launch_bounds__(kAdjNT) k_adj_smooth(Geo g, const Box* __restr
     smooth_rhs<NT>(g, B, r, beta, R.Bv);
     coef_box<NT>(g, B, beta, R.b);
     scale_box<NT>(B, R);
-    if (tid < 64) {
-      double om = 0.0;
-      const int it = refine<true>(g, B, R, rf.fac + B.fac, 1, nullptr, beta, rf.tol, rf.max_refine, om, sm32);
-      record_refine(it, om, rf.iters, rf.resid);
-    }
+    double om = 0.0;
+    const int it = refine<NT, 16, 0, 1>(g, B, R, fl, Rows32<16, 0>{}, 1, nullptr, beta, rf.tol, rf.max_refine, om,
+                                        flag32);
+    if (tid < 64) record_refine(it, om, rf.iters, rf.resid);
   } else {
     stage_smooth<NT>(g, B, r, K, p_in, f, gf_in, bcv, tcoup);
     __syncthreads();
@@ -350,11 +353,10 @@ __global__ void __launch_bounds__(kAdjNT) k_adj_smooth(Geo g, const Box* __restr
   if (F32) {
     for (int e = tid; e < nc; e += NT) R.Bv[e] = mu[e];
     __syncthreads();
-    if (tid < 64) {
-      double om = 0.0;
-      const int it = refine<true>(g, B, R, rf.fac + B.fac, 1, nullptr, beta, rf.tol, rf.max_refine, om, sm32);
-      record_refine(it, om, rf.iters, rf.resid);
-    }
+    double om = 0.0;
+    const int it = refine<NT, 16, 0, 1>(g, B, R, fl, Rows32<16, 0>{}, 1, nullptr, beta, rf.tol, rf.max_refine, om,
+                                        flag32);
+    if (tid < 64) record_refine(it, om, rf.iters, rf.resid);
     __syncthreads();
     for (int e = tid; e < nc; e += NT) mu[e] = R.b.X[e];
   } else {
@@ -421,7 +423,7 @@ __global__ void __launch_bounds__(kAdjNT) k_adj_smooth(Geo g, const Box* __restr
   }
   if (F32) {
     __syncthreads();
-    if (tid == 0 && sm32.flag) atomicOr(rf.flags, sm32.flag);
+    if (tid == 0 && flag32) atomicOr(rf.flags, flag32);
   }
 }
 
@@ -545,15 +547,17 @@ __global__ void __launch_bounds__(64) k_adj_basis(Geo g, const Box* __restrict__
                                                   const double* __restrict__ tr_betab,
                                                   double* __restrict__ Kb) {
   extern __shared__ __align__(16) double dsm[];
-  __shared__ WaveSmemF sm32;
+  __shared__ int flag32;
   const Box B = boxes[blockIdx.x];
   const int L = lane_id();
   const int nrhs = B.nrhs;
   BoxR R{};
+  Lane32<16> fl{};
   BoxLds s;
   double* xs;  // nrhs x nc forward solutions
   if (F32) {
     R = carve_r(dsm, B, max(nrhs, 1), max(nrhs, 1));
+    fl = lane32<16>(B, rf.fac + B.fac);
     s = R.b;
     xs = dsm + adj_box32_off(s.m0, s.m1, max(nrhs, 1));
   } else {
@@ -561,7 +565,7 @@ __global__ void __launch_bounds__(64) k_adj_basis(Geo g, const Box* __restrict__
     xs = dsm + box_lds_doubles(s.m0, s.m1, nrhs);
   }
   const int nc = B.ncell;
-  if (F32 && L == 0) sm32.flag = 0;
+  if (F32 && L == 0) flag32 = 0;
   load_box(g, B, K, beta, s);
   auto seed_lam = [&](int k, int q, int t) -> double {
     const Seed sd = seeds[B.seed0 + k];
@@ -580,7 +584,8 @@ __global__ void __launch_bounds__(64) k_adj_basis(Geo g, const Box* __restrict__
     scale_box(B, R);
     if (nrhs > 0) {
       double om = 0.0;
-      const int it = refine<false>(g, B, R, rf.fac + B.fac, nrhs, seeds, beta, rf.tol, rf.max_refine, om, sm32);
+      const int it = refine<64, 16, 0, 4, true>(g, B, R, fl, Rows32<16, 0>{}, nrhs, seeds, beta, rf.tol,
+                                                rf.max_refine, om, flag32);
       record_refine(it, om, rf.iters, rf.resid);
     }
   } else {
@@ -674,7 +679,8 @@ __global__ void __launch_bounds__(64) k_adj_basis(Geo g, const Box* __restrict__
     wsync();
     if (nrhs > 0) {
       double om = 0.0;
-      const int it = refine<false>(g, B, R, rf.fac + B.fac, nrhs, nullptr, beta, rf.tol, rf.max_refine, om, sm32);
+      const int it = refine<64, 16, 0, 4>(g, B, R, fl, Rows32<16, 0>{}, nrhs, nullptr, beta, rf.tol, rf.max_refine,
+                                          om, flag32);
       record_refine(it, om, rf.iters, rf.resid);
     }
   } else {
@@ -686,7 +692,7 @@ __global__ void __launch_bounds__(64) k_adj_basis(Geo g, const Box* __restrict__
       [](int, int, int, double) {}, Kb);
   if (F32) {
     wsync();
-    if (L == 0 && sm32.flag) atomicOr(rf.flags, sm32.flag);
+    if (L == 0 && flag32) atomicOr(rf.flags, flag32);
   }
 }
 
@@ -705,14 +711,16 @@ __global__ void __launch_bounds__(64) k_adj_particular(Geo g, const Box* __restr
                                                        const double* __restrict__ pibarb,
                                                        double* __restrict__ Kb) {
   extern __shared__ __align__(16) double dsm[];
-  __shared__ WaveSmemF sm32;
+  __shared__ int flag32;
   const Box B = boxes[blockIdx.x];
   const int L = lane_id();
   BoxR R{};
+  Lane32<16> fl{};
   BoxLds s;
   double* xs;
   if (F32) {
     R = carve_r(dsm, B, 1, 1);
+    fl = lane32<16>(B, rf.fac + B.fac);
     s = R.b;
     xs = dsm + adj_box32_off(s.m0, s.m1, 1);
   } else {
@@ -722,7 +730,7 @@ __global__ void __launch_bounds__(64) k_adj_particular(Geo g, const Box* __restr
   }
   const int nc = B.ncell;
   double* bc = xs + nc;  // boundary value per box-side face
-  if (F32 && L == 0) sm32.flag = 0;
+  if (F32 && L == 0) flag32 = 0;
   load_box(g, B, K, beta, s);
   if (F32) scale_box(B, R);
   const int m0 = s.m0, m1 = s.m1, ns = 2 * (m0 + m1);
@@ -773,7 +781,8 @@ __global__ void __launch_bounds__(64) k_adj_particular(Geo g, const Box* __restr
     for (int e = L; e < nc; e += 64) R.Bv[e] = s.X[e];
     wsync();
     double om = 0.0;
-    const int it = refine<true>(g, B, R, rf.fac + B.fac, 1, nullptr, beta, rf.tol, rf.max_refine, om, sm32);
+    const int it = refine<64, 16, 0, 1>(g, B, R, fl, Rows32<16, 0>{}, 1, nullptr, beta, rf.tol, rf.max_refine, om,
+                                        flag32);
     record_refine(it, om, rf.iters, rf.resid);
   } else {
     sweep1(B, fac + B.fac, s, s.Z);
@@ -783,7 +792,7 @@ __global__ void __launch_bounds__(64) k_adj_particular(Geo g, const Box* __restr
       [&](int q, int t) { return bc[side_off(s, q) + t]; }, [](int, int, int, double) {}, Kb);
   if (F32) {
     wsync();
-    if (L == 0 && sm32.flag) atomicOr(rf.flags, sm32.flag);
+    if (L == 0 && flag32) atomicOr(rf.flags, flag32);
   }
 }
 

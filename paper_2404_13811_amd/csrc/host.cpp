@@ -97,6 +97,7 @@ struct mrcm_ctx {
   size_t lds_smooth_res = 0;
   SmoothArrays sarr{nullptr, nullptr, nullptr, 0};
   size_t lds32_basis = 0, lds32_part = 0, lds32_smooth = 0;
+  int form32 = 0;  // their kernel class (wave32_form of the largest box)
   float *fac32 = nullptr, *facp32 = nullptr;
   int* d_iters = nullptr;
   unsigned long long* d_resid = nullptr;
@@ -705,6 +706,12 @@ mrcm_status make_plan(mrcm_ctx* c) {
   if (c->lds_basis > 150 * 1024 || c->lds_smooth > 150 * 1024 || 2 * c->lds_part + 16 > 150 * 1024)
     c->wave = false;
   if (!c->wave || c->lds_smooth_res > 150 * 1024) c->lds_smooth_res = 0;
+  int nb32 = 1, nblk32 = 1;
+  for (const Box& B : c->obox) {
+    nb32 = std::max(nb32, B.nb);
+    nblk32 = std::max(nblk32, B.nblk);
+  }
+  c->form32 = wave32_form(nb32, nblk32);
   // 3-D boxes: one wave per box with plane blocks of at most 64 cells
   c->d3 = c->d == 3;
   c->lds3_basis = c->lds3_part = c->lds3_smooth = 0;
@@ -1243,7 +1250,7 @@ mrcm_status mrcm_build_basis(mrcm_ctx* c) {
                                c->bcv, c->beta_mbf, c->fac32, c->facp32, c->Pk, c->tr_u, c->tr_phi,
                                c->tr_beta, c->pbar, c->ubar, c->pibar, c->tol, c->max_refine,
                                c->d_iters, c->d_resid, c->flags,
-                               std::max(c->lds32_basis, c->lds32_part), s));
+                               c->form32, std::max(c->lds32_basis, c->lds32_part), s));
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[9], s));
   } else if (c->wave) {
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[8], s));
@@ -1413,7 +1420,7 @@ mrcm_status sweep(mrcm_ctx* c, hipStream_t s, int nt, double* p, double* gflux, 
       HIPCHK(c, launch_smooth32_w(c->geo, c->d_obox_col + m0, m1 - m0, c->K, c->f, c->bcv,
                                   c->beta_sm, own ? c->fac32s : c->fac32, p, gflux, c->tol,
                                   c->max_refine, c->d_iters, c->d_resid, c->flags,
-                                  c->lds32_smooth, nt, s));
+                                  c->form32, c->lds32_smooth, nt, s));
     } else if (c->wave) {
       HIPCHK(c, launch_smooth_w(c->geo, c->d_obox_col + m0, m1 - m0, c->K, c->f, c->bcv,
                                 c->beta_sm, own ? c->facs : c->fac, own ? c->facts : c->fact,

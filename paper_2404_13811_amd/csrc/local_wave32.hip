@@ -1,5 +1,5 @@
 // FP32 local factorisations and solves with FP64 iterative refinement, for
-// the 2-D boxes handled by the one-wavefront-per-box kernels.
+// the 2-D boxes of lines of at most 32 cells.
 //
 // The block-tridiagonal factorisation of local_wave.hip is applied in FP32
 // to the symmetrically scaled matrix  A^ = D^-1/2 A D^-1/2  (D = diag A,
@@ -12,6 +12,20 @@
 //     max_c |r_c| / (|A| |x| + |b|)_c  <=  tol
 // or max_refine corrections have been applied (flag MRCM_ENOCONV).  The
 // interface system and every reduction stay in FP64.
+//
+// A box is solved by four waves (Steps 1-2, 4) or one to four (smoothing):
+// the factor and every sweep from both ends on a pair of waves, residuals
+// and updates on all threads.  The kernels come in classes by the largest
+// box (wave32_form): <KN, NBK> with KN products per block step (half a line)
+// and the inverses of up to NBK blocks per half held in registers over all
+// refinement sweeps.
+// Bound: Steps 1-2 the block inversions, 13 of them in a chain at 24 lines
+// (40 % of a box's time) and the FP64 residuals (a quarter); smoothing the
+// chain of 2 (nblk + 1) / 2 block steps of about 270 cycles per FP32 solve.
+// Measured against one wave per box eliminated from one end (24 x 24 cells,
+// three FP32 solves): Steps 1-2 and 4 of 256 boxes with eight seeds 690 ->
+// 222 us, of 4096 with four 3776 -> 1643 us; smoothing per phase 65 -> 28 us
+// (64 boxes), 140 -> 66 us (1024 boxes).
 #include "wave32_common.h"
 
 namespace mrcm {
@@ -21,31 +35,42 @@ using namespace wave;
 
 // ------------------------------------------------------------------ kernels
 
+constexpr int kLocal32NT = 256;
+
 // Steps 1-2 on an oversampled box: FP32 factor, seeds refined to tol.
+template <int KN, int NBK>
 __device__ __forceinline__ void basis32_box(const Geo& g, const Box& B, const Seed* __restrict__ seeds,
                                             const double* __restrict__ K, double beta,
                                             float* __restrict__ fac32, double* __restrict__ Pk,
                                             double* __restrict__ tr_u, double* __restrict__ tr_phi,
                                             double* __restrict__ tr_beta, double tol, int max_refine,
                                             int* iters, unsigned long long* resid, double* dsm,
-                                            WaveSmemF& sm) {
-  const int L = lane_id();
+                                            WaveSmemF* sm) {
+  constexpr int NT = kLocal32NT;
+  const int L = threadIdx.x;
   const int nrhs = B.nrhs;
   BoxR R = carve_r(dsm, B, max(nrhs, 1), 0, g.kc);
-  load_box(g, B, K, beta, R.b);
-  scale_box(B, R);
+  load_box<NT>(g, B, K, beta, R.b);
+  scale_box<NT>(B, R);
+  if (NBK > 0 && nrhs > 0) seed_faces<NT>(g, B, R, beta);
   float* Wg = fac32 + B.fac;
-  factor32(B, Wg, R, sm);
+  factor32<NT>(B, Wg, R, sm);
   double omega = 0.0;
-  const int it = nrhs > 0 ? refine<false>(g, B, R, Wg, nrhs, seeds, beta, tol, max_refine, omega, sm) : 0;
-  record_refine(it, omega, iters, resid);
+  int it = 0;
+  if (nrhs > 0) {
+    const Lane32<KN> f = lane32<KN>(B, Wg);
+    Rows32<KN, NBK> rw;
+    rows32<KN, NBK>(f, (threadIdx.x >> 6) & 1, rw);
+    it = refine<NT, KN, NBK, 4, true>(g, B, R, f, rw, nrhs, seeds, beta, tol, max_refine, omega, sm[0].flag);
+  }
+  if (L < 64) record_refine(it, omega, iters, resid);
   const BoxLds& s = R.b;
   const int nc = B.ncell;
   int olo[3], ohi[3];
   womega(g, B.sub, olo, ohi);
   const int ncell_o = g.S[0] * g.S[1];
   #pragma unroll 1
-  for (int e = L; e < nrhs * ncell_o; e += 64) {
+  for (int e = L; e < nrhs * ncell_o; e += NT) {
     const int k = e / ncell_o, t = e % ncell_o;
     Pk[(long long)(B.seed0 + k) * ncell_o + t] =
         s.X[k * nc + bloc(B, s, olo[0] + t % g.S[0], olo[1] + t / g.S[0])];
@@ -55,7 +80,7 @@ __device__ __forceinline__ void basis32_box(const Geo& g, const Box& B, const Se
     const bool has = wneighbor(g, B.sub, q) >= 0;
     const int a = q >> 1, so = q & 1;
     #pragma unroll 1
-    for (int e = L; e < nrhs * nf; e += 64) {
+    for (int e = L; e < nrhs * nf; e += NT) {
       const int k = e / nf, t = e % nf;
       const long long oidx = (long long)(B.seed0 + k) * g.gstride + g.gside_off[q] + t;
       if (!has) {
@@ -87,6 +112,7 @@ __device__ __forceinline__ void basis32_box(const Geo& g, const Box& B, const Se
 }
 
 // Step 4 on a subdomain: FP32 factor, particular solution refined to tol.
+template <int KN, int NBK>
 __device__ __forceinline__ void particular32_box(const Geo& g, const Box& B, const double* __restrict__ K,
                                                  const double* __restrict__ f,
                                                  const double* __restrict__ bcv, double beta,
@@ -94,26 +120,30 @@ __device__ __forceinline__ void particular32_box(const Geo& g, const Box& B, con
                                                  double* __restrict__ ubar, double* __restrict__ pibar,
                                                  double tol, int max_refine, int* iters,
                                                  unsigned long long* resid, double* dsm,
-                                                 WaveSmemF& sm) {
-  const int L = lane_id();
+                                                 WaveSmemF* sm) {
+  constexpr int NT = kLocal32NT;
+  const int L = threadIdx.x;
   BoxR R = carve_r(dsm, B, 1, 1, g.kc);
-  load_box(g, B, K, beta, R.b);
-  scale_box(B, R);
-  physical_rhs(g, B, R.b, f, bcv, R.Bv);
-  wsync();
+  load_box<NT>(g, B, K, beta, R.b);
+  scale_box<NT>(B, R);
+  physical_rhs<NT>(g, B, R.b, f, bcv, R.Bv);
+  bsync<NT>();
   float* Wg = fac32 + B.fac;
-  factor32(B, Wg, R, sm);
+  factor32<NT>(B, Wg, R, sm);
   double omega = 0.0;
-  const int it = refine<true>(g, B, R, Wg, 1, nullptr, beta, tol, max_refine, omega, sm);
-  record_refine(it, omega, iters, resid);
+  const Lane32<KN> fl = lane32<KN>(B, Wg);
+  Rows32<KN, NBK> rw;
+  rows32<KN, NBK>(fl, (threadIdx.x >> 6) & 1, rw);
+  const int it = refine<NT, KN, NBK, 1>(g, B, R, fl, rw, 1, nullptr, beta, tol, max_refine, omega, sm[0].flag);
+  if (L < 64) record_refine(it, omega, iters, resid);
   const BoxLds& s = R.b;
-  for (int t = L; t < B.ncell; t += 64) pbar[(long long)B.sub * B.ncell + t] = s.X[t];
+  for (int t = L; t < B.ncell; t += NT) pbar[(long long)B.sub * B.ncell + t] = s.X[t];
   for (int q = 0; q < 4; ++q) {
     const int nf = (q >> 1) == 0 ? g.S[1] : g.S[0];
     const bool has = wneighbor(g, B.sub, q) >= 0;
     const int a = q >> 1, so = q & 1;
     #pragma unroll 1
-    for (int t = L; t < nf; t += 64) {
+    for (int t = L; t < nf; t += NT) {
       const long long oidx = (long long)B.sub * g.gstride + g.gside_off[q] + t;
       if (!has) {
         ubar[oidx] = 0.0;
@@ -135,7 +165,8 @@ __device__ __forceinline__ void particular32_box(const Geo& g, const Box& B, con
 // Steps 1-2 and 4 in one launch: workgroups [0, nbox) take the oversampled
 // boxes, workgroups [nbox, 2 nbox) the particular problems.  The two sets are
 // independent and run side by side.
-__global__ void __launch_bounds__(64) k_local32(Geo g, const Box* __restrict__ obox,
+template <int KN, int NBK>
+__global__ void __launch_bounds__(kLocal32NT, KN == 12 ? 2 : 1) k_local32(Geo g, const Box* __restrict__ obox,
                                                 const Box* __restrict__ pbox, int nbox,
                                                 const Seed* __restrict__ seeds,
                                                 const double* __restrict__ K,
@@ -153,44 +184,43 @@ __global__ void __launch_bounds__(64) k_local32(Geo g, const Box* __restrict__ o
                                                 int max_refine, int* iters,
                                                 unsigned long long* resid, int* flags) {
   extern __shared__ __align__(16) double dsm[];
-  __shared__ WaveSmemF sm;
-  const int L = lane_id();
-  if (L == 0) sm.flag = 0;
+  __shared__ WaveSmemF sm[2];
+  if (threadIdx.x < 2) sm[threadIdx.x].flag = 0;
+  __syncthreads();
   const int b = blockIdx.x;
   if (b < nbox) {
     const Box B = obox[b];
-    basis32_box(g, B, seeds, K, beta, fac32, Pk, tr_u, tr_phi, tr_beta, tol, max_refine, iters,
+    basis32_box<KN, NBK>(g, B, seeds, K, beta, fac32, Pk, tr_u, tr_phi, tr_beta, tol, max_refine, iters,
                 resid, dsm, sm);
   } else {
     const Box B = pbox[b - nbox];
-    particular32_box(g, B, K, f, bcv, beta, facp32, pbar, ubar, pibar, tol, max_refine, iters,
+    particular32_box<KN, NBK>(g, B, K, f, bcv, beta, facp32, pbar, ubar, pibar, tol, max_refine, iters,
                      resid, dsm, sm);
   }
-  wsync();
-  if (L == 0 && sm.flag) atomicOr(flags, sm.flag);
+  __syncthreads();
+  if (threadIdx.x == 0 && (sm[0].flag | sm[1].flag)) atomicOr(flags, sm[0].flag | sm[1].flag);
 }
 
 // Algorithm 1, Step 6 in the FP32 form: the oversampled boxes factored
 // again (FP32, diagonally scaled) with the smoothing Robin parameter; no
 // right-hand side is solved.
-__global__ void __launch_bounds__(64) k_factor32(Geo g, const Box* __restrict__ obox,
+__global__ void __launch_bounds__(kLocal32NT) k_factor32(Geo g, const Box* __restrict__ obox,
                                                  const double* __restrict__ K, double beta,
                                                  float* __restrict__ fac32, int* iters,
                                                  unsigned long long* resid, int* flags) {
   extern __shared__ __align__(16) double dsm[];
-  __shared__ WaveSmemF sm;
-  const int L = lane_id();
-  if (L == 0) sm.flag = 0;
+  __shared__ WaveSmemF sm[2];
+  if (threadIdx.x < 2) sm[threadIdx.x].flag = 0;
+  __syncthreads();
   Box B = obox[blockIdx.x];
   B.nrhs = 0;
-  basis32_box(g, B, nullptr, K, beta, fac32, nullptr, nullptr, nullptr, nullptr, 1.0, 0, iters,
+  basis32_box<16, 0>(g, B, nullptr, K, beta, fac32, nullptr, nullptr, nullptr, nullptr, 1.0, 0, iters,
               resid, dsm, sm);
-  wsync();
-  if (L == 0 && sm.flag) atomicOr(flags, sm.flag);
+  __syncthreads();
+  if (threadIdx.x == 0 && (sm[0].flag | sm[1].flag)) atomicOr(flags, sm[0].flag | sm[1].flag);
 }
 
-
-template <int NT>
+template <int NT, int KN, int NBK>
 __global__ void __launch_bounds__(NT) k_smooth32(Geo g, const Box* __restrict__ boxes,
                                                  const double* __restrict__ K,
                                                  const double* __restrict__ f,
@@ -201,9 +231,13 @@ __global__ void __launch_bounds__(NT) k_smooth32(Geo g, const Box* __restrict__ 
                                                  int max_refine, int* iters,
                                                  unsigned long long* resid, int* flags) {
   extern __shared__ __align__(16) double dsm[];
-  __shared__ WaveSmemF sm;
+  __shared__ int flag;
   const Box B = boxes[blockIdx.x];
-  if (threadIdx.x == 0) sm.flag = 0;
+  if (threadIdx.x == 0) flag = 0;
+  // the inverses of this wave's half, in flight during the set-up
+  const Lane32<KN> fl = lane32<KN>(B, fac32 + B.fac);
+  Rows32<KN, NBK> rw;
+  if (NBK > 0 && threadIdx.x < 128) rows32<KN, NBK>(fl, (threadIdx.x >> 6) & 1, rw);
   SmoothLds r = carve_smooth(dsm, B, g.kc);
   BoxR R = carve_smooth_r(dsm, r);
   stage_smooth<NT>(g, B, r, K, p, f, gflux, bcv, nullptr);
@@ -211,14 +245,12 @@ __global__ void __launch_bounds__(NT) k_smooth32(Geo g, const Box* __restrict__ 
   smooth_rhs<NT>(g, B, r, beta, R.Bv);
   coef_box<NT>(g, B, beta, R.b);
   scale_box<NT>(B, R);
-  if (threadIdx.x < 64) {
-    double omega = 0.0;
-    const int it = refine<true>(g, B, R, fac32 + B.fac, 1, nullptr, beta, tol, max_refine, omega, sm);
-    record_refine(it, omega, iters, resid);
-  }
+  double omega = 0.0;
+  const int it = refine<NT, KN, NBK, 1>(g, B, R, fl, rw, 1, nullptr, beta, tol, max_refine, omega, flag);
+  if (threadIdx.x < 64) record_refine(it, omega, iters, resid);
   __syncthreads();
   smooth_out<NT>(g, B, r, R.b.X, beta, p, gflux);
-  if (threadIdx.x == 0 && sm.flag) atomicOr(flags, sm.flag);
+  if (threadIdx.x == 0 && flag) atomicOr(flags, flag);
 }
 
 template <typename KF>
@@ -235,6 +267,13 @@ size_t wave32_lds_bytes(int m0, int m1, int nrhs, int nbrhs, int kc) {
   return boxr_bytes(m0, m1, nrhs, nbrhs, kc);
 }
 
+// Registers draw the lines: <12, 12> keeps 156 entries of inverses per lane
+// and fits two waves per SIMD (12 x 12 exactly covers lines of 24 cells and
+// 25 blocks), <16, 16> keeps 272 of the 512 that one wave can have; longer
+// boxes stream their blocks.  Where the inverses fit, holding them is the
+// faster: a 256 x 256 solve of 256 boxes 1.10 ms, 1.29 ms streamed.
+int wave32_form(int nb, int nblk) { return nblk > 33 ? 2 : nb <= 24 && nblk <= 25 ? 0 : 1; }
+
 size_t wave32_smooth_lds_bytes(int m0, int m1, int kc) { return smooth32_lds_bytes(m0, m1, kc); }
 
 hipError_t launch_local32_w(const Geo& g, const Box* obox, const Box* pbox, int nbox,
@@ -242,14 +281,18 @@ hipError_t launch_local32_w(const Geo& g, const Box* obox, const Box* pbox, int 
                             double beta, float* fac32, float* facp32, double* Pk, double* tr_u,
                             double* tr_phi, double* tr_beta, double* pbar, double* ubar,
                             double* pibar, double tol, int max_refine, int* iters,
-                            unsigned long long* resid, int* flags, size_t lds, hipStream_t s) {
+                            unsigned long long* resid, int* flags, int form, size_t lds, hipStream_t s) {
   if (nbox <= 0) return hipSuccess;
-  hipError_t e = set_lds(k_local32, lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_local32, dim3(2 * nbox), dim3(64), lds, s, g, obox, pbox, nbox, seeds, K, f,
-                     bcv, beta, fac32, facp32, Pk, tr_u, tr_phi, tr_beta, pbar, ubar, pibar, tol,
-                     max_refine, iters, resid, flags);
-  return hipGetLastError();
+  if (form < 2) lds += kSeedTable;
+  auto go = [&](auto kern) -> hipError_t {
+    const hipError_t e = set_lds(kern, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(2 * nbox), dim3(kLocal32NT), lds, s, g, obox, pbox, nbox, seeds, K, f, bcv,
+                       beta, fac32, facp32, Pk, tr_u, tr_phi, tr_beta, pbar, ubar, pibar, tol, max_refine,
+                       iters, resid, flags);
+    return hipGetLastError();
+  };
+  return form == 0 ? go(k_local32<12, 12>) : form == 1 ? go(k_local32<16, 16>) : go(k_local32<16, 0>);
 }
 
 hipError_t launch_factor32_w(const Geo& g, const Box* obox, int nbox, const double* K, double beta,
@@ -258,7 +301,7 @@ hipError_t launch_factor32_w(const Geo& g, const Box* obox, int nbox, const doub
   if (nbox <= 0) return hipSuccess;
   hipError_t e = set_lds(k_factor32, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_factor32, dim3(nbox), dim3(64), lds, s, g, obox, K, beta, fac32, iters,
+  hipLaunchKernelGGL(k_factor32, dim3(nbox), dim3(kLocal32NT), lds, s, g, obox, K, beta, fac32, iters,
                      resid, flags);
   return hipGetLastError();
 }
@@ -267,25 +310,24 @@ hipError_t launch_smooth32_w(const Geo& g, const Box* boxes, int nmem,
                              const double* K, const double* f, const double* bcv, double beta,
                              const float* fac32, double* p, double* gflux, double tol,
                              int max_refine, int* iters, unsigned long long* resid, int* flags,
-                             size_t lds, int nt, hipStream_t s) {
+                             int form, size_t lds, int nt, hipStream_t s) {
   if (nmem <= 0) return hipSuccess;
-  hipError_t e;
-#define MRCM_SMOOTH32_NT(N)                                                                     \
-  e = set_lds(k_smooth32<N>, lds);                                                              \
-  if (e != hipSuccess) return e;                                                                \
-  hipLaunchKernelGGL(k_smooth32<N>, dim3(nmem), dim3(N), lds, s, g, boxes, K, f, bcv,           \
-                     beta, fac32, p, gflux, tol, max_refine, iters, resid, flags);
-  if (nt == 64) {
-    MRCM_SMOOTH32_NT(64)
-  } else if (nt == 128) {
-    MRCM_SMOOTH32_NT(128)
-  } else if (nt == 256) {
-    MRCM_SMOOTH32_NT(256)
-  } else {
-    return hipErrorInvalidValue;
-  }
-#undef MRCM_SMOOTH32_NT
-  return hipGetLastError();
+  auto go = [&](auto kern, int N) -> hipError_t {
+    const hipError_t e = set_lds(kern, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(nmem), dim3(N), lds, s, g, boxes, K, f, bcv, beta, fac32, p, gflux, tol,
+                       max_refine, iters, resid, flags);
+    return hipGetLastError();
+  };
+  // one wave per box holds no inverses in registers (both halves are its own)
+  if (nt == 64) return go(k_smooth32<64, 16, 0>, 64);
+  if (nt == 128)
+    return form == 0 ? go(k_smooth32<128, 12, 12>, 128)
+                     : form == 1 ? go(k_smooth32<128, 16, 16>, 128) : go(k_smooth32<128, 16, 0>, 128);
+  if (nt == 256)
+    return form == 0 ? go(k_smooth32<256, 12, 12>, 256)
+                     : form == 1 ? go(k_smooth32<256, 16, 16>, 256) : go(k_smooth32<256, 16, 0>, 256);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace mrcm

@@ -252,12 +252,14 @@ hipError_t launch_smooth3f(const Geo& g, const Box* boxes, int nmem, const doubl
 // FP32 factors with FP64 iterative refinement (local_wave32.hip)
 size_t wave32_lds_bytes(int m0, int m1, int nrhs, int nbrhs, int kc);
 size_t wave32_smooth_lds_bytes(int m0, int m1, int kc);
+// kernel class of boxes with up to nblk lines of nb cells
+int wave32_form(int nb, int nblk);
 hipError_t launch_local32_w(const Geo& g, const Box* obox, const Box* pbox, int nbox,
                             const Seed* seeds, const double* K, const double* f, const double* bcv,
                             double beta, float* fac32, float* facp32, double* Pk, double* tr_u,
                             double* tr_phi, double* tr_beta, double* pbar, double* ubar,
                             double* pibar, double tol, int max_refine, int* iters,
-                            unsigned long long* resid, int* flags, size_t lds, hipStream_t s);
+                            unsigned long long* resid, int* flags, int form, size_t lds, hipStream_t s);
 // Step 6 in the FP32 form: FP32 factors of the scaled oversampled boxes
 // with the smoothing Robin parameter (K must hold exp(log K))
 hipError_t launch_factor32_w(const Geo& g, const Box* obox, int nbox, const double* K, double beta,
@@ -267,7 +269,7 @@ hipError_t launch_smooth32_w(const Geo& g, const Box* boxes, int nmem,
                              const double* K, const double* f, const double* bcv, double beta,
                              const float* fac32, double* p, double* gflux, double tol,
                              int max_refine, int* iters, unsigned long long* resid, int* flags,
-                             size_t lds, int nt, hipStream_t s);
+                             int form, size_t lds, int nt, hipStream_t s);
 
 // interface system (iface.hip)
 // Where the moments go when the interface system is solved by block cyclic

@@ -1,13 +1,22 @@
-// FP32 solves with FP64 iterative refinement on the one-wavefront-per-box
-// 2-D layout, shared by the FP32 local kernels (local_wave32.hip) and the
-// FP32 form of the adjoint (adjoint.hip): LDS carve-up of a box with its
-// diagonal scaling, the FP32 block-tridiagonal factor of the scaled matrix
+// FP32 solves with FP64 iterative refinement on the wavefront-per-half 2-D
+// layout, shared by the FP32 local kernels (local_wave32.hip) and the FP32
+// form of the adjoint (adjoint.hip): LDS carve-up of a box with its diagonal
+// scaling, the FP32 block-tridiagonal factor of the scaled matrix
 // A^ = D^-1/2 A D^-1/2 as explicit block inverses, its sweeps, and the
 // refinement loop
 //     x = 0;  repeat  r = b - A x (FP64);  x += D^-1/2 solve32(D^-1/2 r)
 // until the componentwise backward error max_c |r_c| / (|A| |x| + |b|)_c
 // is at most tol.
+//
+// The factor is two-ended, as the FP64 one: forward inverses W_j of the
+// blocks below the meeting block m = nblk / 2, backward inverses above it,
+// Z_m at m, all in one array (nblk blocks, nb x nb row-major).  A solve runs
+// its halves on two waves, each holding the inverses of its half in
+// registers across all refinement sweeps where they fit (Rows32), and the
+// residuals and updates run on all threads of the box.
 #pragma once
+#include <type_traits>
+
 #include "wave_common.h"
 
 namespace mrcm {
@@ -23,7 +32,8 @@ struct BoxR {
   float* Wf;    // nrhs x ncell FP32 work vectors
   float* Txf;   // ncell scaled x couplings
   float* Tnf;   // ncell scaled block couplings
-  float* Zf;    // nrhs x NBW staging
+  double* red;  // the reductions' scratch (one value per wave), then T^R of
+                // the box-side faces where a kernel tables them (kSeedTable)
 };
 
 __host__ __device__ inline size_t boxr_bytes(int m0, int m1, int nrhs, int nbrhs, int kc = 1) {
@@ -52,7 +62,7 @@ __device__ __forceinline__ BoxR carve_r(double* base, const Box& B, int nrhs, in
   r.Wf = fb;
   r.Txf = r.Wf + (size_t)nrhs * nc;
   r.Tnf = r.Txf + nc;
-  r.Zf = align16(base, r.Tnf + nc);
+  r.red = reinterpret_cast<double*>(align16(base, r.Tnf + nc));
   return r;
 }
 
@@ -73,24 +83,24 @@ __device__ __forceinline__ void scale_box(const Box& B, BoxR& R) {
   bsync<NT>();
 }
 
-
-// Scaled S_j into w (column c, my half), w = W_{j-1} on entry when j > 0
-// (branch-free, as wbuild).
-__device__ __forceinline__ void wbuild32(int nb, int j, const BoxR& R, float w[HB]) {
+// Scaled Schur complement of block j into w (column c, my half): D_j -
+// t W t with the coupling t = Tnf row tpi to the previously eliminated block,
+// whose inverse W w holds on entry (tpi < 0: none); see wbuild_t.
+__device__ __forceinline__ void wbuild32(int nb, int j, int tpi, const BoxR& R, float w[HB]) {
   const int L = lane_id();
   const int c = L & 31, h = L >> 5;
   const int cc = c < nb ? c : 0;
   const float* Tx = R.Txf + j * nb;
-  const float* Tp = R.Tnf + (j - 1) * nb;  // read only when j > 0
-  const float txc = Tx[cc];
-  const float tc = j > 0 ? Tp[cc] : 0.0f;
+  const float* Tp = R.Tnf + (tpi >= 0 ? tpi : 0) * nb;
+  const float hpf = tpi >= 0 ? 1.0f : 0.0f;
+  const float txc = Tx[cc], tc = Tp[cc] * hpf;
   float tr[HB], tpr[HB];
 #pragma unroll
   for (int i = 0; i < HB; ++i) {
     const int r = HB * h + i;
     const int rr = r < nb ? r : 0;
     tr[i] = Tx[rr];
-    tpr[i] = j > 0 ? Tp[rr] : 0.0f;
+    tpr[i] = Tp[rr];
   }
 #pragma unroll
   for (int i = 0; i < HB; ++i) {
@@ -102,186 +112,333 @@ __device__ __forceinline__ void wbuild32(int nb, int j, const BoxR& R, float w[H
   }
 }
 
-__device__ __forceinline__ void wgj32(int nb, WaveSmemF& sm, float w[HB]) { wgj_blk<float>(nb, sm, w); }
-
-// W_j z with 128-bit LDS reads, two FMA chains and the half-wave swap sum.
-__device__ __forceinline__ float wgemv2f(const float w[HB], const float* z) {
-  const int h = lane_id() >> 5;
-  const float4* z4 = reinterpret_cast<const float4*>(z + HB * h);
-  float a0 = 0.0f, a1 = 0.0f;
+__device__ __forceinline__ void store32(int nb, float* Wj, const float w[HB]) {
+  const int L = lane_id();
+  const int c = L & 31, h = L >> 5;
 #pragma unroll
-  for (int i = 0; i < HB / 4; ++i) {
-    const float4 v = z4[i];
-    a0 = fmaf(w[4 * i], v.x, a0);
-    a1 = fmaf(w[4 * i + 1], v.y, a1);
-    a0 = fmaf(w[4 * i + 2], v.z, a0);
-    a1 = fmaf(w[4 * i + 3], v.w, a1);
+  for (int i = 0; i < HB; ++i) {
+    const int r = HB * h + i;
+    if (r < nb && c < nb) Wj[r * nb + c] = w[i];
   }
-  return half_sum_f(a0 + a1);
 }
 
-
-
-__device__ __forceinline__ void fwd32(int nb, int nc, int j, int nrhs, const BoxR& R, const float w[HB]) {
-  const int L = lane_id();
+// Two-ended factor of the box by NT threads (the halves on waves 0 and 1
+// when NT >= 128, else one after the other); the forward Schur complement of
+// the meeting block passes through that block's slot of Wg.  sm: one per
+// wave that factors.
+template <int NT>
+__device__ __forceinline__ void factor32(const Box& B, float* Wg, const BoxR& R, WaveSmemF* sm) {
+  const int L = lane_id(), wv = (int)(threadIdx.x % NT) >> 6;
   const int c = L & 31, h = L >> 5;
-  #pragma unroll 1
-  for (int e = L; e < nrhs * NBW; e += 64) {
-    const int k = e / NBW, r = e % NBW;
-    float v = 0.0f;
-    if (r < nb) {
-      v = R.Wf[k * nc + j * nb + r];
-      if (j > 0) v += R.Tnf[(j - 1) * nb + r] * R.Wf[k * nc + (j - 1) * nb + r];
-    }
-    R.Zf[k * NBW + r] = v;
-  }
-  wsync();
-  for (int k = 0; k < nrhs; ++k) {
-    const float y = wgemv2f(w, R.Zf + k * NBW);
-    if (h == 0 && c < nb) R.Wf[k * nc + j * nb + c] = y;
-  }
-  wsync();
-}
-
-__device__ __forceinline__ void bwd32(int nb, int nc, int j, int nrhs, const BoxR& R, const float w[HB]) {
-  const int L = lane_id();
-  const int c = L & 31, h = L >> 5;
-  #pragma unroll 1
-  for (int e = L; e < nrhs * NBW; e += 64) {
-    const int k = e / NBW, r = e % NBW;
-    R.Zf[k * NBW + r] = (r < nb) ? R.Tnf[j * nb + r] * R.Wf[k * nc + (j + 1) * nb + r] : 0.0f;
-  }
-  wsync();
-  for (int k = 0; k < nrhs; ++k) {
-    const float y = wgemv2f(w, R.Zf + k * NBW);
-    if (h == 0 && c < nb) R.Wf[k * nc + j * nb + c] += y;
-  }
-  wsync();
-}
-
-__device__ __forceinline__ void factor32(const Box& B, float* Wg, const BoxR& R, WaveSmemF& sm) {
-  const int L = lane_id();
-  const int c = L & 31, h = L >> 5;
-  const int nb = B.nb;
+  const int nb = B.nb, nblk = B.nblk, m = nblk / 2;
+  // blocks written by one wave and read by another
+  auto handover = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if constexpr (NT > 64) __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  };
+  const long long bs = (long long)nb * nb;
   float w[HB];
 #pragma unroll
   for (int i = 0; i < HB; ++i) w[i] = 0.0f;
-  for (int j = 0; j < B.nblk; ++j) {
-    wbuild32(nb, j, R, w);
-    wgj32(nb, sm, w);
-    float* Wj = Wg + (long long)j * nb * nb;
+  if (wv == 0) {
+    for (int j = 0; j < m; ++j) {
+      wbuild32(nb, j, j - 1, R, w);
+      wgj_blk<float>(nb, sm[0], w);
+      store32(nb, Wg + j * bs, w);
+    }
+    wbuild32(nb, m, m - 1, R, w);
+    store32(nb, Wg + m * bs, w);
+  }
+  constexpr int BW = NT >= 128 ? 1 : 0;  // the wave of the bottom half
+  if (wv == BW) {
+    for (int j = nblk - 1; j > m; --j) {
+      wbuild32(nb, j, j < nblk - 1 ? j : -1, R, w);
+      wgj_blk<float>(nb, sm[BW], w);
+      store32(nb, Wg + j * bs, w);
+    }
+  }
+  handover();
+  if (wv == BW) {
+    // Z_m = (S_m - t_m W'_{m+1} t_m)^{-1}; w holds W'_{m+1} when the bottom
+    // half is not empty
+    const float* Tm = R.Tnf + m * nb;
+    const bool low = m < nblk - 1;
+    const float tc = low && c < nb ? Tm[c] : 0.0f;
 #pragma unroll
     for (int i = 0; i < HB; ++i) {
       const int r = HB * h + i;
-      if (r < nb && c < nb) Wj[r * nb + c] = w[i];
+      const bool in = r < nb && c < nb;
+      const float smi = in ? Wg[m * bs + r * nb + c] : (r == c ? 1.0f : 0.0f);
+      const float tr = low && r < nb ? Tm[r] : 0.0f;
+      w[i] = low && in ? fmaf(-tr * tc, w[i], smi) : smi;
     }
+    wgj_blk<float>(nb, sm[BW], w);
+    store32(nb, Wg + m * bs, w);
   }
-  wsync();
+  handover();  // the sweeps read every block
 }
 
-// FP32 solve of the scaled system on every work vector in R.Wf.
-__device__ __forceinline__ void solve32(const Box& B, const float* Wg, int nrhs, const BoxR& R) {
-  const int nb = B.nb, nblk = B.nblk, nc = B.ncell;
-  const long long bs = (long long)nb * nb;
-  const BlockSrc<float> src = block_src(Wg, nb, nblk);
-  {
-    float w[RING][HB];
+// ------------------------------------------------------------- FP32 sweeps
+// Lanes of a block step, as LdsFac: lines in two parts of nh = (nb + 1) / 2
+// <= KN entries; lane (g, i) holds row nh (g % 2) + i and the columns of part
+// g / 2 of a block, and of a vector entry nh (g / 2) + i.
+template <int KN>
+struct Lane32 {
+  __amdgpu_buffer_rsrc_t rs;
+  int off[KN], bbytes;
+  int nb, nblk, zi, ci;
+  bool zv, cv, zo;
+};
+template <int KN>
+__device__ __forceinline__ Lane32<KN> lane32(const Box& B, const float* Wg) {
+  Lane32<KN> f;
+  const int nb = B.nb, nh = (nb + 1) / 2, L = lane_id(), i = L & 15, g = L >> 4;
+  const unsigned long long pa = reinterpret_cast<unsigned long long>(Wg);
+  const unsigned plo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)pa);
+  const unsigned phi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(pa >> 32));
+  const int bytes = __builtin_amdgcn_readfirstlane(B.nblk * nb * nb * (int)sizeof(float));
+  f.rs = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<float*>(((unsigned long long)phi << 32) | plo),
+                                           (short)0, bytes, 0x00020000);
+  f.bbytes = __builtin_amdgcn_readfirstlane(nb * nb * (int)sizeof(float));
+  f.nb = nb;
+  f.nblk = B.nblk;
+  const int rr = nh * (g & 1) + i, zz = nh * (g >> 1) + i;
+  const bool in = i < nh;
+  f.cv = in && rr < nb && g < 2;
+  f.zv = in && zz < nb;
+  f.zo = f.zv && !(g & 1);
+  f.ci = min(rr, nb - 1);
+  f.zi = min(zz, nb - 1);
 #pragma unroll
-    for (int q = 0; q < RING; ++q)
-      if (q < nblk) wload_block(src, q, w[q]);
-    for (int j0 = 0; j0 < nblk; j0 += RING) {
+  for (int k = 0; k < KN; ++k) {
+    // by symmetry the column of the lane's row: consecutive lanes read
+    // consecutive entries; an offset out of range reads zero
+    const int r = nh * (g >> 1) + k;
+    f.off[k] = (k < nh && r < nb && in && rr < nb) ? (r * nb + rr) * (int)sizeof(float) : bytes;
+  }
+  return f;
+}
+template <int KN>
+__device__ __forceinline__ void load32(const Lane32<KN>& f, int j, float w[KN]) {
 #pragma unroll
-      for (int q = 0; q < RING; ++q) {
-        const int j = j0 + q;
-        if (j < nblk) {
-          fwd32(nb, nc, j, nrhs, R, w[q]);
-          if (j + RING < nblk) wload_block(src, (j + RING), w[q]);
-        }
+  for (int k = 0; k < KN; ++k)
+    w[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+        f.rs, f.off[k], __builtin_amdgcn_readfirstlane(j * f.bbytes), 0));
+}
+
+// y of the lane's row (wgemv_rows in FP32 over KN columns)
+template <int KN>
+__device__ __forceinline__ float gemv32(const float w[KN], float z) {
+  float a0 = 0.0f, a1 = 0.0f;
+#define MRCM_P(I0, K0, I1, K1)                                                                     \
+  "v_fmac_f32_dpp %0, %2, %" #I0 " row_newbcast:" #K0 " row_mask:0xf bank_mask:0xf\n\t"            \
+  "v_fmac_f32_dpp %1, %2, %" #I1 " row_newbcast:" #K1 " row_mask:0xf bank_mask:0xf\n\t"
+#define MRCM_S12                                                                                   \
+  "s_nop 1\n\t" MRCM_P(3, 0, 4, 1) MRCM_P(5, 2, 6, 3) MRCM_P(7, 4, 8, 5) MRCM_P(9, 6, 10, 7)       \
+      MRCM_P(11, 8, 12, 9) MRCM_P(13, 10, 14, 11)
+#define MRCM_S16 MRCM_S12 MRCM_P(15, 12, 16, 13) MRCM_P(17, 14, 18, 15)
+#define MRCM_W12                                                                                   \
+  "v"(z), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]),    \
+      "v"(w[8]), "v"(w[9]), "v"(w[10]), "v"(w[11])
+  static_assert(KN == 12 || KN == 16, "products per block step");
+  if constexpr (KN == 12) asm(MRCM_S12 : "+v"(a0), "+v"(a1) : MRCM_W12);
+  if constexpr (KN == 16)
+    asm(MRCM_S16 : "+v"(a0), "+v"(a1) : MRCM_W12, "v"(w[12]), "v"(w[13]), "v"(w[14]), "v"(w[15]));
+#undef MRCM_P
+#undef MRCM_S12
+#undef MRCM_S16
+#undef MRCM_W12
+  return half_sum_f(a0 + a1);
+}
+__device__ __forceinline__ float to_rows_f(float y) {
+  const int u = __float_as_int(y);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return __int_as_float(lane_id() >= 32 ? a[1] : a[0]);
+}
+
+// The inverses of one half of a box in registers (block b away from its end
+// of the box in w[b], b < NBK) and, on the top half, Z_m; NBK = 0: none held,
+// blocks are loaded as the sweeps reach them.
+template <int KN, int NBK>
+struct Rows32 {
+  float w[NBK > 0 ? NBK : 1][KN], zm[KN];
+};
+template <int KN, int NBK>
+__device__ __forceinline__ void rows32(const Lane32<KN>& f, bool bottom, Rows32<KN, NBK>& r) {
+  const int m = f.nblk / 2, cnt = bottom ? f.nblk - 1 - m : m;
+#pragma unroll
+  for (int b = 0; b < NBK; ++b)
+    if (b < cnt) load32(f, bottom ? f.nblk - 1 - b : b, r.w[b]);
+  if (NBK > 0 && !bottom) load32(f, m, r.zm);
+}
+
+// An index the compiler recomputes where it is used: kept over the unrolled
+// steps and hoisted out of the refinement loop, the addresses alone would
+// take the registers of the inverses.
+__device__ __forceinline__ void keep_here(int& e) { asm volatile("" : "+v"(e)); }
+
+// Forward and back halves of the two-ended sweep of NR vectors (X + q nc).
+template <int KN, int NBK, int NR>
+__device__ __forceinline__ void fwd32(const Lane32<KN>& f, const Rows32<KN, NBK>& rw, const float* Tn,
+                                      float* X, int nc, bool bottom) {
+  const int nb = f.nb, m = f.nblk / 2, cnt = bottom ? f.nblk - 1 - m : m;
+  const int dj = bottom ? -1 : 1, j0 = bottom ? f.nblk - 1 : 0;
+  float yz[NR], tp = 0.0f;
+#pragma unroll
+  for (int q = 0; q < NR; ++q) yz[q] = 0.0f;
+  const int dt = bottom ? -nb : 0, dc = f.ci - f.zi;
+  int e = j0 * nb + f.zi;  // my entry of the step's block
+  float xv[NR];            // and its value, read a step ahead
+#pragma unroll
+  for (int q = 0; q < NR; ++q) xv[q] = X[q * nc + e];
+  auto step = [&](const float* w) {
+    keep_here(e);
+    float z[NR], y[NR];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) z[q] = f.zv ? fmaf(tp, yz[q], xv[q]) : 0.0f;
+    tp = Tn[max(e + dt, 0)];
+    // the half's last step reads the meeting block, which is in range
+#pragma unroll
+    for (int q = 0; q < NR; ++q) xv[q] = X[q * nc + e + dj * nb];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) y[q] = gemv32<KN>(w, z[q]);
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      yz[q] = to_rows_f(y[q]);
+      if (f.cv) X[q * nc + e + dc] = y[q];
+    }
+    e += dj * nb;
+  };
+  if constexpr (NBK > 0) {
+#pragma unroll
+    for (int t = 0; t < NBK; ++t)
+      if (t < cnt) step(rw.w[t]);
+  } else {
+    float wa[KN], wb[KN];
+    if (cnt > 0) load32(f, j0, wa);
+    for (int t = 0; t < cnt; t += 2) {
+      load32(f, j0 + dj * min(t + 1, cnt - 1), wb);
+      step(wa);
+      if (t + 1 < cnt) {
+        load32(f, j0 + dj * min(t + 2, cnt - 1), wa);
+        step(wb);
       }
     }
   }
-  {
-    float w[RING][HB];
+}
+
+template <int KN, int NBK, int NR>
+__device__ __forceinline__ void mid32(const Lane32<KN>& f, const Rows32<KN, NBK>& rw, const float* Tn,
+                                      float* X, int nc) {
+  const int nb = f.nb, m = f.nblk / 2;
+  int em = m * nb + f.zi;
+  keep_here(em);
+  float zl[KN];
+  if constexpr (NBK == 0) load32(f, m, zl);
 #pragma unroll
-    for (int q = 0; q < RING; ++q)
-      if (nblk - 2 - q >= 0) wload_block(src, (nblk - 2 - q), w[q]);
-    for (int t0 = 0; t0 <= nblk - 2; t0 += RING) {
+  for (int q = 0; q < NR; ++q) {
+    const float* Xq = X + q * nc;
+    float v = Xq[em];
+    if (m > 0) v = fmaf(Tn[em - nb], Xq[em - nb], v);
+    if (m + 1 < f.nblk) v = fmaf(Tn[em], Xq[em + nb], v);
+    const float y = gemv32<KN>(NBK > 0 ? rw.zm : zl, f.zv ? v : 0.0f);
+    if (f.cv) X[q * nc + em - f.zi + f.ci] = y;
+  }
+}
+
+template <int KN, int NBK, int NR>
+__device__ __forceinline__ void bwd32(const Lane32<KN>& f, const Rows32<KN, NBK>& rw, const float* Tn,
+                                      float* X, int nc, bool bottom) {
+  const int nb = f.nb, m = f.nblk / 2, cnt = bottom ? f.nblk - 1 - m : m;
+  const int dj = bottom ? -1 : 1, j0 = bottom ? f.nblk - 1 : 0;
+  float xn[NR];
 #pragma unroll
-      for (int q = 0; q < RING; ++q) {
-        const int j = nblk - 2 - (t0 + q);
-        if (j >= 0) {
-          bwd32(nb, nc, j, nrhs, R, w[q]);
-          if (j - RING >= 0) wload_block(src, (j - RING), w[q]);
-        }
+  for (int q = 0; q < NR; ++q) xn[q] = f.zv ? X[q * nc + m * nb + f.zi] : 0.0f;
+  // from the block beside the meeting one outwards
+  int e = (j0 + dj * (cnt - 1)) * nb + f.zi;
+  const int dt = bottom ? -nb : 0, nlast = (f.nblk - 1) * nb + f.zi;
+  float xv[NR], tv = 0.0f;  // the step's entries, read a step ahead
+  if (cnt > 0) tv = Tn[e + dt];
+#pragma unroll
+  for (int q = 0; q < NR; ++q) xv[q] = cnt > 0 ? X[q * nc + e] : 0.0f;
+  auto step = [&](const float* w) {
+    keep_here(e);
+    const float t = f.zv ? tv : 0.0f;
+    float y[NR], xc[NR];
+    const int en = min(max(e - dj * nb, f.zi), nlast);  // clamped after the last step
+    tv = Tn[max(en + dt, 0)];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      xc[q] = xv[q];
+      xv[q] = X[q * nc + en];
+    }
+#pragma unroll
+    for (int q = 0; q < NR; ++q) y[q] = gemv32<KN>(w, t * xn[q]);
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      xn[q] = xc[q] + to_rows_f(y[q]);
+      xn[q] = f.zv ? xn[q] : 0.0f;
+      if (f.zo) X[q * nc + e] = xn[q];
+    }
+    e -= dj * nb;
+  };
+  if constexpr (NBK > 0) {
+#pragma unroll
+    for (int b = NBK - 1; b >= 0; --b)
+      if (b < cnt) step(rw.w[b]);
+  } else {
+    float wa[KN], wb[KN];
+    if (cnt > 0) load32(f, j0 + dj * (cnt - 1), wa);
+    for (int b = cnt - 1; b >= 0; b -= 2) {
+      load32(f, j0 + dj * max(b - 1, 0), wb);
+      step(wa);
+      if (b > 0) {
+        load32(f, j0 + dj * max(b - 2, 0), wa);
+        step(wb);
       }
     }
   }
 }
 
-// Single right-hand side in R.Wf: forward and backward sweeps with the
-// previous block's values kept in registers (as the FP64 sweep).
-__device__ __forceinline__ void sweep1f(const Box& B, const float* Wg, const BoxR& R) {
-  const int L = lane_id();
-  const int c = L & 31, h = L >> 5;
-  const int nb = B.nb, nblk = B.nblk;
-  const bool cv = c < nb;
-  const long long bs = (long long)nb * nb;
-  const BlockSrc<float> src = block_src(Wg, nb, nblk);
-  float* X = R.Wf;
+// FP32 solve of the scaled system on the nrhs work vectors in R.Wf by the NT
+// threads of a box: the halves of a vector on the two waves of a pair (one
+// after the other when NT = 64), the vectors NR at a time dealt to the
+// pairs.  Ends with a barrier of the box.
+template <int NT, int KN, int NBK, int NR>
+__device__ __forceinline__ void solve32(const Lane32<KN>& f, const Rows32<KN, NBK>& rw, int nc, int nrhs,
+                                        const BoxR& R) {
+  constexpr int NP = NT >= 128 ? NT / 128 : 1;  // pairs
+  static_assert(NBK == 0 || NT >= 128, "one wave cannot hold both halves");
+  const int wv = (int)(threadIdx.x % NT) >> 6;
+  const int pair = NT >= 128 ? wv >> 1 : 0;
+  const bool top = NT < 128 || !(wv & 1), bot = NT < 128 || (wv & 1);
   const float* Tn = R.Tnf;
-  float* z = R.Zf;
-  {
-    float w[RING][HB];
-#pragma unroll
-    for (int q = 0; q < RING; ++q)
-      if (q < nblk) wload_block(src, q, w[q]);
-    float y = 0.0f, xn = cv ? X[c] : 0.0f, tp = 0.0f;
-    for (int j0 = 0; j0 < nblk; j0 += RING) {
-#pragma unroll
-      for (int q = 0; q < RING; ++q) {
-        const int j = j0 + q;
-        if (j < nblk) {
-          float* zb = z + (j & 1) * NBW;
-          if (h == 0) zb[c] = cv ? fmaf(tp, y, xn) : 0.0f;
-          __builtin_amdgcn_wave_barrier();
-          const bool more = j + 1 < nblk;
-          xn = (more && cv) ? X[(j + 1) * nb + c] : 0.0f;
-          tp = (more && cv) ? Tn[j * nb + c] : 0.0f;
-          y = wgemv2f(w[q], zb);
-          if (h == 0 && cv) X[j * nb + c] = y;
-          if (j + RING < nblk) wload_block(src, (j + RING), w[q]);
-        }
-      }
-    }
-  }
-  {
-    float w[RING][HB];
-#pragma unroll
-    for (int q = 0; q < RING; ++q)
-      if (nblk - 2 - q >= 0) wload_block(src, (nblk - 2 - q), w[q]);
-    __builtin_amdgcn_wave_barrier();
-    float xnext = cv ? X[(nblk - 1) * nb + c] : 0.0f;
-    float tj = (nblk >= 2 && cv) ? Tn[(nblk - 2) * nb + c] : 0.0f;
-    float wj = (nblk >= 2 && cv) ? X[(nblk - 2) * nb + c] : 0.0f;
-    for (int t0 = 0; t0 <= nblk - 2; t0 += RING) {
-#pragma unroll
-      for (int q = 0; q < RING; ++q) {
-        const int j = nblk - 2 - (t0 + q);
-        if (j >= 0) {
-          float* zb = z + (j & 1) * NBW;
-          if (h == 0) zb[c] = cv ? tj * xnext : 0.0f;
-          __builtin_amdgcn_wave_barrier();
-          const float wcur = wj;
-          tj = (j >= 1 && cv) ? Tn[(j - 1) * nb + c] : 0.0f;
-          wj = (j >= 1 && cv) ? X[(j - 1) * nb + c] : 0.0f;
-          xnext = wcur + wgemv2f(w[q], zb);
-          if (h == 0 && cv) X[j * nb + c] = xnext;
-          if (j - RING >= 0) wload_block(src, (j - RING), w[q]);
-        }
-      }
-    }
-  }
-  wsync();
+  // vectors [k0, k0 + NR) of this pair, the last group one by one
+  auto each = [&](auto&& go) {
+    int k = pair * NR;
+    for (; k + NR <= nrhs; k += NP * NR) go(k, std::integral_constant<int, NR>());
+    const int end = min(nrhs, k + NR);
+    for (; NR > 2 && k + 2 <= end; k += 2) go(k, std::integral_constant<int, 2>());
+    for (; k < end; ++k) go(k, std::integral_constant<int, 1>());
+  };
+  each([&](int k, auto n) {
+    constexpr int N = decltype(n)::value;
+    if (top) fwd32<KN, NBK, N>(f, rw, Tn, R.Wf + (size_t)k * nc, nc, false);
+    if (bot) fwd32<KN, NBK, N>(f, rw, Tn, R.Wf + (size_t)k * nc, nc, true);
+  });
+  bsync<NT>();
+  if (top)
+    each([&](int k, auto n) {
+      mid32<KN, NBK, decltype(n)::value>(f, rw, Tn, R.Wf + (size_t)k * nc, nc);
+    });
+  bsync<NT>();
+  each([&](int k, auto n) {
+    constexpr int N = decltype(n)::value;
+    if (top) bwd32<KN, NBK, N>(f, rw, Tn, R.Wf + (size_t)k * nc, nc, false);
+    if (bot) bwd32<KN, NBK, N>(f, rw, Tn, R.Wf + (size_t)k * nc, nc, true);
+  });
+  bsync<NT>();
 }
 
 template <int CTRL>
@@ -313,69 +470,108 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
-// Right-hand side of seed k at box cell loc (T^R times the seed on its side).
-__device__ __forceinline__ double seed_rhs(const Geo& g, const Box& B, const BoxR& R, const Seed& sd,
-                                           double beta, int loc) {
-  const int x = B.lo[0] + loc % R.b.m0, y = B.lo[1] + loc / R.b.m0;
-  const int a = sd.side >> 1, so = sd.side & 1;
-  const bool on = (a == 0) ? (x == (so ? B.hi[0] - 1 : B.lo[0])) : (y == (so ? B.hi[1] - 1 : B.lo[1]));
-  if (!on) return 0.0;
-  const int ox = x + (a == 0 ? (so ? 1 : -1) : 0), oy = y + (a == 1 ? (so ? 1 : -1) : 0);
-  const double kc = kat(R.b, B, x, y, a);
-  const double bt = robin_beta(g, a, kc, kat(R.b, B, ox, oy, a), beta);
-  const int c[3] = {x, y, 0};
-  return robin_T(g, kc, bt) * seed_value(g, sd, B.lo, B.hi, c);
+// The largest v over the NT threads of the box (red: NT / 64 doubles of LDS).
+template <int NT>
+__device__ __forceinline__ double box_max(double v, double* red) {
+  v = wave_max(v);
+  if constexpr (NT == 64) return v;
+  if (lane_id() == 0) red[(int)(threadIdx.x % NT) >> 6] = v;
+  bsync<NT>();
+#pragma unroll
+  for (int u = 0; u < NT / 64; ++u) v = fmax(v, red[u]);
+  bsync<NT>();
+  return v;
 }
 
-// Iterative refinement of nrhs systems A x_k = b_k; b from seeds (if
-// seeds != nullptr) or from R.Bv (nrhs x ncell).  Returns the number of
-// FP32 solves.
-template <bool ONE>
-__device__ __forceinline__ int refine(const Geo& g, const Box& B, const BoxR& R, const float* Wg, int nrhs,
-                      const Seed* seeds, double beta, double tol, int max_refine, double& omega_out,
-                      WaveSmemF& sm) {
-  const int L = lane_id();
+// T^R of box-side face u (side_off order), zero on the domain's boundary.
+__device__ __forceinline__ double seed_face(const Geo& g, const Box& B, const BoxR& R, double beta, int u) {
+  int t, x, y, ox, oy;
+  const int q = face_side(R.b.m0, R.b.m1, u, t), a = q >> 1;
+  face_cells(B.lo[0], B.lo[1], B.hi[0], B.hi[1], q, t, x, y, ox, oy);
+  if (off_domain(g, a, a == 0 ? x : y, a == 0 ? ox : oy)) return 0.0;
+  const double kc = kat(R.b, B, x, y, a);
+  return robin_T(g, kc, robin_beta(g, a, kc, kat(R.b, B, ox, oy, a), beta));
+}
+// The faces' T^R tabled in R.red + NT / 64 by kernels whose boxes have at
+// most 33 lines (LDS reserved by the host: kSeedTable bytes); longer boxes
+// compute it where it is needed, their table would grow with the box.
+constexpr int kSeedTable = (2 * (32 + 33) + 4) * (int)sizeof(double);
+template <int NT>
+__device__ __forceinline__ void seed_faces(const Geo& g, const Box& B, const BoxR& R, double beta) {
+#pragma unroll 1
+  for (int u = threadIdx.x % NT; u < 2 * (R.b.m0 + R.b.m1); u += NT)
+    R.red[NT / 64 + u] = seed_face(g, B, R, beta, u);
+}
+// Right-hand side of a seed at box cell (xl, yl): T^R times the seed on its
+// side (TRs: the table, or null).
+__device__ __forceinline__ double seed_rhs(const Geo& g, const Box& B, const BoxR& R, const Seed& sd,
+                                           const double* TRs, double beta, int xl, int yl) {
+  const int a = sd.side >> 1, so = sd.side & 1;
+  const bool on = a == 0 ? xl == (so ? R.b.m0 - 1 : 0) : yl == (so ? R.b.m1 - 1 : 0);
+  if (!on) return 0.0;
+  const int c[3] = {B.lo[0] + xl, B.lo[1] + yl, 0};
+  const int u = side_off(R.b, sd.side) + (a == 0 ? yl : xl);
+  return (TRs ? TRs[u] : seed_face(g, B, R, beta, u)) * seed_value(g, sd, B.lo, B.hi, c);
+}
+
+// Iterative refinement of nrhs systems A x_k = b_k by the NT threads of a
+// box; b from seeds (SEEDS; NBK > 0: after seed_faces) or from R.Bv (nrhs x
+// ncell).  Returns the number of FP32 solves.
+template <int NT, int KN, int NBK, int NR, bool SEEDS = false>
+__device__ __forceinline__ int refine(const Geo& g, const Box& B, const BoxR& R, const Lane32<KN>& f,
+                                      const Rows32<KN, NBK>& rw, int nrhs, const Seed* seeds,
+                                      double beta, double tol, int max_refine, double& omega_out,
+                                      int& flag) {
+  const int tid = threadIdx.x % NT;
   const int nc = B.ncell, m0 = R.b.m0, nb = B.nb;
-  for (int e = L; e < nrhs * nc; e += 64) R.b.X[e] = 0.0;
-  wsync();
+#pragma unroll 1
+  for (int e = tid; e < nrhs * nc; e += NT) R.b.X[e] = 0.0;
+  bsync<NT>();
   int it = 0;
   double omega = 0.0;
   while (true) {
-    // r = b - A x, scaled into the FP32 work vectors; componentwise backward error
-    omega = 0.0;
-    for (int k = 0; k < nrhs; ++k) {
-      const double* x = R.b.X + (size_t)k * nc;
-      double om = 0.0;
-      #pragma unroll 1
-      for (int loc = L; loc < nc; loc += 64) {
-        const double bv = seeds ? seed_rhs(g, B, R, seeds[B.seed0 + k], beta, loc) : R.Bv[(size_t)k * nc + loc];
-        const int xl = loc % m0;
-        const double xc = x[loc];
-        double ax = R.b.Dg[loc] * xc, aa = fabs(R.b.Dg[loc] * xc);
-        if (xl > 0) { const double t = R.b.Tx[loc - 1] * x[loc - 1]; ax -= t; aa += fabs(t); }
-        if (xl + 1 < m0) { const double t = R.b.Tx[loc] * x[loc + 1]; ax -= t; aa += fabs(t); }
-        if (loc >= nb) { const double t = R.b.Tn[loc - nb] * x[loc - nb]; ax -= t; aa += fabs(t); }
-        if (loc + nb < nc) { const double t = R.b.Tn[loc] * x[loc + nb]; ax -= t; aa += fabs(t); }
+    // r = b - A x, scaled into the FP32 work vectors; componentwise backward
+    // error.  A cell's couplings are read once for all vectors.
+    double om = 0.0;
+#pragma unroll 1
+    for (int loc = tid; loc < nc; loc += NT) {
+      const int yl = loc / m0, xl = loc - yl * m0;
+      const double dg = R.b.Dg[loc], sc = R.sd[loc];
+      const double txm = xl > 0 ? R.b.Tx[loc - 1] : 0.0, txp = xl + 1 < m0 ? R.b.Tx[loc] : 0.0;
+      const double tnm = loc >= nb ? R.b.Tn[loc - nb] : 0.0, tnp = loc + nb < nc ? R.b.Tn[loc] : 0.0;
+      const int im = xl > 0 ? loc - 1 : loc, ip = xl + 1 < m0 ? loc + 1 : loc;
+      const int jm = loc >= nb ? loc - nb : loc, jp = loc + nb < nc ? loc + nb : loc;
+#pragma unroll 1
+      for (int k = 0; k < nrhs; ++k) {
+        const double* x = R.b.X + (size_t)k * nc;
+        const double bv = SEEDS ? seed_rhs(g, B, R, seeds[B.seed0 + k], NBK > 0 ? R.red + NT / 64 : nullptr, beta, xl, yl)
+                                : R.Bv[(size_t)k * nc + loc];
+        const double d = dg * x[loc];
+        const double t0 = txm * x[im], t1 = txp * x[ip], t2 = tnm * x[jm], t3 = tnp * x[jp];
+        const double ax = (((d - t0) - t1) - t2) - t3;
+        const double aa = (((fabs(d) + fabs(t0)) + fabs(t1)) + fabs(t2)) + fabs(t3);
         const double r = bv - ax;
         const double den = aa + fabs(bv);
         // a non-finite residual or iterate never counts as converged (fmax
         // would drop a NaN ratio)
         if (!(r - r == 0.0 && den - den == 0.0)) om = INFINITY;
         else if (den > 0.0) om = fmax(om, fabs(r) / den);
-        R.Wf[(size_t)k * nc + loc] = (float)(R.sd[loc] * r);
+        R.Wf[(size_t)k * nc + loc] = (float)(sc * r);
       }
-      omega = fmax(omega, wave_max(om));
     }
-    wsync();
+    omega = box_max<NT>(om, R.red);
     if (it > 0 && omega <= tol) break;
     if (it > max_refine || !(omega <= 1e300)) {
-      if (L == 0) sm.flag |= kFlagNoConv;
+      if (tid == 0) flag |= kFlagNoConv;
       break;
     }
-    if (ONE) sweep1f(B, Wg, R);
-    else solve32(B, Wg, nrhs, R);
-    for (int e = L; e < nrhs * nc; e += 64) R.b.X[e] += R.sd[e % nc] * (double)R.Wf[e];
-    wsync();
+    solve32<NT, KN, NBK, NR>(f, rw, nc, nrhs, R);
+#pragma unroll 1
+    for (int loc = tid; loc < nc; loc += NT) {
+      const double sc = R.sd[loc];
+      for (int k = 0; k < nrhs; ++k) R.b.X[(size_t)k * nc + loc] += sc * (double)R.Wf[(size_t)k * nc + loc];
+    }
+    bsync<NT>();
     ++it;
   }
   omega_out = omega;
@@ -402,7 +598,7 @@ __device__ __forceinline__ BoxR carve_smooth_r(double* base, const SmoothLds& r)
   R.Wf = fb;
   R.Txf = R.Wf + nc;
   R.Tnf = R.Txf + nc;
-  R.Zf = align16(base, R.Tnf + nc);
+  R.red = reinterpret_cast<double*>(align16(base, R.Tnf + nc));
   return R;
 }
 
