@@ -6,10 +6,10 @@
 // line is shorter): lane L holds rows 16h .. 16h+15 of column c, with
 // c = L & 31 and h = L >> 5, so all 64 lanes carry work.
 //
-// The block inverse is computed by in-place Gauss-Jordan elimination (no
-// pivoting: the pivots of an SPD matrix are positive).  Each step broadcasts
-// pivot row and column through LDS; no cross-lane reduction and no barrier
-// beyond the single wave.
+// The block inverse takes 16 pivots at a time in registers (no pivoting: the
+// pivots of an SPD matrix are positive) and joins the two halves of the
+// block by FP64 matrix instructions (winv); no barrier beyond the single
+// wave.
 //
 // Solves use the block LDL^T recurrences of the block-tridiagonal matrix
 // (see local.hip): forward w_j = W_j (b_j + t_{j-1} .* w_{j-1}), backward
@@ -36,13 +36,17 @@ using namespace wave;
 
 // Store the nb x nb block held in the register layout w to Wj.
 __device__ __forceinline__ void store_block(int nb, double* Wj, const double w[HB]) {
-  // lower triangle, row-major (the layout block_src reads)
-  const int L = lane_id();
-  const int c = L & 31, h = L >> 5;
+  // lower triangle, row-major (the layout block_src reads); entries outside
+  // it get an offset out of the buffer's range: dropped
+  const int L = lane_id(), c = L & 31, h = L >> 5;
+  const auto rs = uniform_buffer(Wj, packed_elems(nb) * (int)sizeof(double));
+  const int lo = max(c - HB * h, 0), n = nb - HB * h;  // my rows
 #pragma unroll
   for (int i = 0; i < HB; ++i) {
-    const int r = HB * h + i;
-    if (r < nb && c <= r) Wj[r * (r + 1) / 2 + c] = w[i];
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    // r (r + 1) / 2 + c for r = 16 h + i
+    const int off = 8 * (c + h * (136 + 16 * i) + i * (i + 1) / 2);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, w[i]), rs, i >= lo && i < n ? off : 1 << 28, 0, 0);
   }
 }
 
@@ -62,7 +66,7 @@ __device__ __forceinline__ void factor_forward(const Box& B, double* Wg, double*
   for (int i = 0; i < HB; ++i) w[i] = 0.0;
   for (int j = 0; j < B.nblk; ++j) {
     wbuild(nb, j, s, w);
-    wgj(nb, sm, w);
+    winv(nb, sm, w);
     store_block(nb, fblock(Wg, nb, j), w);
     fwd_step(nb, B.ncell, j, nrhs, s, w);
   }
@@ -104,7 +108,7 @@ __device__ __forceinline__ void basis_box(const Geo& g, const Box& B, const Seed
                                           const double* __restrict__ bcv, const SmoothStatic& st,
                                           double* dsm, WaveSmem* sm) {
   const int L = lane_id();
-  const int tid = threadIdx.x, wv = tid >> 6;
+  const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nrhs = FO ? 0 : B.nrhs;
   BoxLds s = carve(dsm, B, nrhs, g.kc);
   double* Z1 = s.Z + nrhs * NBW;
@@ -143,26 +147,25 @@ __device__ __forceinline__ void basis_box(const Geo& g, const Box& B, const Seed
   double w[HB];
 #pragma unroll
   for (int i = 0; i < HB; ++i) w[i] = 0.0;
-  if (wv == 0) {
-    for (int j = 0; j < m; ++j) {
-      wbuild(nb, j, s, w);
-      wgj(nb, sm[0], w);
-      store_block(nb, fblock(Wf, nb, j), w);
-      fwd_step_d(nb, nc, j, j - 1, j > 0, nrhs, s, s.Z, w);
+  {
+    const bool bot = wv == 1;
+    const int cnt = bot ? nblk - 1 - m : m;
+#pragma unroll 1
+    for (int t = 0; t < cnt; ++t) {
+      const int j = bot ? nblk - 1 - t : t, jp = bot ? j + 1 : j - 1;
+      wbuild_t(nb, j, t > 0 ? (bot ? j : jp) : -1, s, w);
+      winv(nb, sm[wv], w);
+      store_block(nb, fblock(bot ? Wt : Wf, nb, j), w);
+      fwd_step_d(nb, nc, j, jp, t > 0, nrhs, s, bot ? Z1 : s.Z, w);
     }
+  }
+  if (wv == 0) {
     wbuild(nb, m, s, w);  // S_m
     const int c = L & 31, h = L >> 5;
 #pragma unroll
     for (int i = 0; i < HB; ++i) {
       const int r = HB * h + i;
       if (r < nb && c < nb) Sm[r * nb + c] = w[i];
-    }
-  } else {
-    for (int j = nblk - 1; j > m; --j) {
-      wbuild_t(nb, j, j < nblk - 1 ? j : -1, s, w);
-      wgj(nb, sm[1], w);
-      store_block(nb, fblock(Wt, nb, j), w);
-      fwd_step_d(nb, nc, j, j + 1, j < nblk - 1, nrhs, s, Z1, w);
     }
   }
   __syncthreads();
@@ -180,7 +183,7 @@ __device__ __forceinline__ void basis_box(const Geo& g, const Box& B, const Seed
       const double tr = (m < nblk - 1 && r < nb) ? Tm[r] : 0.0;
       w[i] = (m < nblk - 1 && r < nb && c < nb) ? fma(-tr * tc, w[i], smi) : smi;
     }
-    wgj(nb, sm[1], w);
+    winv(nb, sm[1], w);
     store_block(nb, fblock(Wt, nb, m), w);
     if (!FO) mid_step(nb, nc, m, nblk, nrhs, s, Z1, w);
   }

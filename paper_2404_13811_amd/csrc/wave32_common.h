@@ -22,7 +22,7 @@
 namespace mrcm {
 namespace wave {
 
-using WaveSmemF = GjSmem<float>;
+using WaveSmemF = InvSmem<float>;
 
 // LDS of one box for the refinement kernels.
 struct BoxR {
@@ -83,79 +83,58 @@ __device__ __forceinline__ void scale_box(const Box& B, BoxR& R) {
   bsync<NT>();
 }
 
-// Scaled Schur complement of block j into w (column c, my half): D_j -
-// t W t with the coupling t = Tnf row tpi to the previously eliminated block,
-// whose inverse W w holds on entry (tpi < 0: none); see wbuild_t.
+// Scaled Schur complement of block j, see wbuild_t.
 __device__ __forceinline__ void wbuild32(int nb, int j, int tpi, const BoxR& R, float w[HB]) {
-  const int L = lane_id();
-  const int c = L & 31, h = L >> 5;
-  const int cc = c < nb ? c : 0;
-  const float* Tx = R.Txf + j * nb;
-  const float* Tp = R.Tnf + (tpi >= 0 ? tpi : 0) * nb;
-  const float hpf = tpi >= 0 ? 1.0f : 0.0f;
-  const float txc = Tx[cc], tc = Tp[cc] * hpf;
-  float tr[HB], tpr[HB];
-#pragma unroll
-  for (int i = 0; i < HB; ++i) {
-    const int r = HB * h + i;
-    const int rr = r < nb ? r : 0;
-    tr[i] = Tx[rr];
-    tpr[i] = Tp[rr];
-  }
-#pragma unroll
-  for (int i = 0; i < HB; ++i) {
-    const int r = HB * h + i;
-    const int d = r - c;
-    float v = d == 0 ? 1.0f : d == -1 ? -tr[i] : d == 1 ? -txc : 0.0f;
-    v = fmaf(-tpr[i] * tc, w[i], v);
-    w[i] = (r < nb && c < nb) ? v : (d == 0 ? 1.0f : 0.0f);
-  }
+  schur_block<float>(nb, nullptr, R.Txf + j * nb, tpi >= 0 ? R.Tnf + tpi * nb : nullptr, w);
 }
 
+// Entries outside the block get an offset out of the buffer's range: dropped.
 __device__ __forceinline__ void store32(int nb, float* Wj, const float w[HB]) {
-  const int L = lane_id();
-  const int c = L & 31, h = L >> 5;
+  const int L = lane_id(), c = L & 31, h = L >> 5;
+  const auto rs = uniform_buffer(Wj, nb * nb * (int)sizeof(float));
+  const int n = c < nb ? nb - HB * h : 0;  // my rows
+  int off = (HB * h * nb + c) * (int)sizeof(float);
 #pragma unroll
   for (int i = 0; i < HB; ++i) {
-    const int r = HB * h + i;
-    if (r < nb && c < nb) Wj[r * nb + c] = w[i];
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(w[i]), rs, i < n ? off : 1 << 28, 0, 0);
+    off += nb * (int)sizeof(float);
   }
 }
 
-// Two-ended factor of the box by NT threads (the halves on waves 0 and 1
-// when NT >= 128, else one after the other); the forward Schur complement of
+// Two-ended factor of the box by NT threads, the halves on waves 0 and 1;
+// the forward Schur complement of
 // the meeting block passes through that block's slot of Wg.  sm: one per
 // wave that factors.
 template <int NT>
 __device__ __forceinline__ void factor32(const Box& B, float* Wg, const BoxR& R, WaveSmemF* sm) {
-  const int L = lane_id(), wv = (int)(threadIdx.x % NT) >> 6;
+  const int L = lane_id(), wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x % NT) >> 6);
   const int c = L & 31, h = L >> 5;
   const int nb = B.nb, nblk = B.nblk, m = nblk / 2;
   // blocks written by one wave and read by another
   auto handover = [] {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    if constexpr (NT > 64) __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   };
   const long long bs = (long long)nb * nb;
   float w[HB];
 #pragma unroll
   for (int i = 0; i < HB; ++i) w[i] = 0.0f;
-  if (wv == 0) {
-    for (int j = 0; j < m; ++j) {
-      wbuild32(nb, j, j - 1, R, w);
-      wgj_blk<float>(nb, sm[0], w);
+  static_assert(NT >= 128, "a wave per half");
+  constexpr int BW = 1;  // the wave of the bottom half
+  if (wv < 2) {
+    const bool bot = wv == BW;
+    const int cnt = bot ? nblk - 1 - m : m;
+#pragma unroll 1
+    for (int t = 0; t < cnt; ++t) {
+      const int j = bot ? nblk - 1 - t : t;
+      wbuild32(nb, j, t > 0 ? (bot ? j : j - 1) : -1, R, w);
+      winv(nb, sm[wv], w);
       store32(nb, Wg + j * bs, w);
     }
-    wbuild32(nb, m, m - 1, R, w);
-    store32(nb, Wg + m * bs, w);
-  }
-  constexpr int BW = NT >= 128 ? 1 : 0;  // the wave of the bottom half
-  if (wv == BW) {
-    for (int j = nblk - 1; j > m; --j) {
-      wbuild32(nb, j, j < nblk - 1 ? j : -1, R, w);
-      wgj_blk<float>(nb, sm[BW], w);
-      store32(nb, Wg + j * bs, w);
+    if (!bot) {
+      wbuild32(nb, m, m - 1, R, w);
+      store32(nb, Wg + m * bs, w);
     }
   }
   handover();
@@ -173,7 +152,7 @@ __device__ __forceinline__ void factor32(const Box& B, float* Wg, const BoxR& R,
       const float tr = low && r < nb ? Tm[r] : 0.0f;
       w[i] = low && in ? fmaf(-tr * tc, w[i], smi) : smi;
     }
-    wgj_blk<float>(nb, sm[BW], w);
+    winv(nb, sm[BW], w);
     store32(nb, Wg + m * bs, w);
   }
   handover();  // the sweeps read every block
@@ -194,12 +173,8 @@ template <int KN>
 __device__ __forceinline__ Lane32<KN> lane32(const Box& B, const float* Wg) {
   Lane32<KN> f;
   const int nb = B.nb, nh = (nb + 1) / 2, L = lane_id(), i = L & 15, g = L >> 4;
-  const unsigned long long pa = reinterpret_cast<unsigned long long>(Wg);
-  const unsigned plo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)pa);
-  const unsigned phi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(pa >> 32));
   const int bytes = __builtin_amdgcn_readfirstlane(B.nblk * nb * nb * (int)sizeof(float));
-  f.rs = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<float*>(((unsigned long long)phi << 32) | plo),
-                                           (short)0, bytes, 0x00020000);
+  f.rs = uniform_buffer(Wg, bytes);
   f.bbytes = __builtin_amdgcn_readfirstlane(nb * nb * (int)sizeof(float));
   f.nb = nb;
   f.nblk = B.nblk;

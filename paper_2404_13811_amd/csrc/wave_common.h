@@ -4,7 +4,7 @@
 // geometry helpers.  See local_wave.hip for the algorithm.
 #pragma once
 #include "local_common.h"
-#include "pivot4.h"
+#include "gj16.h"
 
 namespace mrcm {
 namespace wave {
@@ -13,17 +13,22 @@ constexpr int NBW = 32;
 constexpr int HB = 16;
 constexpr int RING = 4;
 
-constexpr int GJB = 4;  // pivots per Gauss-Jordan step (one 4 x 4 pivot block)
-
-// Pivot rows and columns of one Gauss-Jordan step (two alternating buffers):
-// rowb[c * GJB + m] = A[k + m][c], colb[m * NBW + r] = A[r][k + m].
+// Two tiles of the block inverse (winv) and the kernel's error flags.
 template <typename T>
-struct __align__(16) GjSmem {
-  T rowb[2][NBW * GJB];
-  T colb[2][GJB * NBW];
+struct InvSmem;
+template <>
+struct __align__(16) InvSmem<double> {
+  using V = dbl4;
+  double t[2][kTile];
   int flag;
 };
-using WaveSmem = GjSmem<double>;
+template <>
+struct __align__(16) InvSmem<float> {
+  using V = flt4;
+  float t[2][kTileF];
+  int flag;
+};
+using WaveSmem = InvSmem<double>;
 
 // Dynamic LDS carve-up of one box.
 struct BoxLds {
@@ -112,18 +117,23 @@ struct BlockSrc {
   int bbytes;
 };
 
+// Buffer of a wave-uniform base and size, kept in scalar registers so that
+// accesses need no per-lane resource; offsets past it read zero and store
+// nothing.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_buffer(const void* p, int bytes) {
+  const unsigned long long pa = reinterpret_cast<unsigned long long>(p);
+  const unsigned plo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)pa);
+  const unsigned phi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(pa >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(((unsigned long long)phi << 32) | plo), (short)0,
+                                           __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+
 template <typename T>
 __device__ __forceinline__ BlockSrc<T> block_src(const T* Wg, int nb, int nblk) {
   BlockSrc<T> b;
-  // the base and size are wave-uniform: keep them in scalar registers so
-  // that the loads need no per-lane resource
-  const unsigned long long pa = reinterpret_cast<unsigned long long>(Wg);
-  const unsigned plo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)pa);
-  const unsigned phi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(pa >> 32));
-  T* pu = reinterpret_cast<T*>(((unsigned long long)phi << 32) | plo);
   const int bsz = block_elems<T>(nb);
-  const int bytes = __builtin_amdgcn_readfirstlane(nblk * bsz * (int)sizeof(T));
-  b.rs = __builtin_amdgcn_make_buffer_rsrc(pu, (short)0, bytes, 0x00020000);
+  const int bytes = nblk * bsz * (int)sizeof(T);
+  b.rs = uniform_buffer(Wg, bytes);
   const int c = threadIdx.x & 31, h = (threadIdx.x >> 5) & 1;
 #pragma unroll
   for (int i = 0; i < HB; ++i) {
@@ -326,40 +336,49 @@ __device__ __forceinline__ void coef_box(const Geo& g, const Box& B, double beta
   bsync<NT>();
 }
 
-// Schur complement of block j (column c, my half) into w: D_j - t W t with
-// the coupling t = Tn row tpi to the previously eliminated block, whose
-// inverse W w holds on entry (tpi < 0: no previous block, S = D_j).  The
-// forward elimination uses tpi = j - 1, the backward one tpi = j.
-// Branch-free: every LDS read is unconditional (the addresses stay inside
-// the box arrays) and selects pick the tridiagonal entries, so the reads of
-// a block issue back to back.
+// d += a(lane K of the row) b
+template <int K>
+__device__ __forceinline__ void fmac_bcast(double& d, double a, double b) {
+  asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(a), "v"(b), "n"(K));
+}
+template <int K>
+__device__ __forceinline__ void fmac_bcast(float& d, float a, float b) {
+  asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(a), "v"(b), "n"(K));
+}
+// row entries of the Schur complement: w <- band entry - th(row) (tc w)
+template <int I, typename T>
+__device__ __forceinline__ void schur_rows(T w[HB], int ic, T dc, T xl, T xr, T th, T ntc) {
+  if constexpr (I < HB) {
+    T e = I == ic ? dc : I == ic - 1 ? xl : I == ic + 1 ? xr : T(0);
+    fmac_bcast<I>(e, th, ntc * w[I]);
+    w[I] = e;
+    schur_rows<I + 1>(w, ic, dc, xl, xr, th, ntc);
+  }
+}
+// Schur complement (column c, my half) into w: the tridiagonal line with
+// diagonal D (null: ones) and couplings Tx, less t W t with the coupling t =
+// Tp (null: no previous block) to the block eliminated before, whose inverse
+// W w holds on entry.  A lane reads the entries of its own column and one of
+// t, which the others of its 16-lane row take by row broadcast.
+template <typename T>
+__device__ __forceinline__ void schur_block(int nb, const T* D, const T* Tx, const T* Tp, T w[HB]) {
+  const int L = lane_id(), c = L & 31, h = L >> 5;
+  const int r = HB * h + (L & 15);
+  const bool in = c < nb, lower = Tp != nullptr;
+  const int cc = in ? c : 0, rc = r < nb ? r : 0;
+  const T* Tq = lower ? Tp : Tx;
+  const T dv = D ? D[cc] : T(1), x0 = Tx[cc > 0 ? cc - 1 : 0], x1 = Tx[cc], t0 = Tq[cc], t1 = Tq[rc];
+  const T dc = in ? dv : T(1);
+  const T xl = in && c > 0 ? -x0 : T(0), xr = in && c + 1 < nb ? -x1 : T(0);
+  const T ntc = in && lower ? -t0 : T(0);
+  T th = r < nb ? t1 : T(0);
+  asm("s_nop 1" : "+v"(th));  // a DPP operand: two wait states after its write
+  schur_rows<0>(w, c - HB * h, dc, xl, xr, th, ntc);
+}
+// Block j of a box; tpi: line of Tn that couples it to the block eliminated
+// before (forward elimination j - 1, backward j), negative: none.
 __device__ __forceinline__ void wbuild_t(int nb, int j, int tpi, const BoxLds& s, double w[HB]) {
-  const int L = lane_id();
-  const int c = L & 31, h = L >> 5;
-  const int cc = c < nb ? c : 0;
-  // Unconditional, contiguous reads (paired by the compiler); a missing
-  // previous block is a zero factor, not a select on the loads.  Rows past
-  // nb read on into the next LDS array of the box and are discarded below.
-  const double hpf = tpi >= 0 ? 1.0 : 0.0;
-  const double* D = s.Dg + j * nb;
-  const double* Tx = s.Tx + j * nb;
-  const double* Tp = s.Tn + (tpi >= 0 ? tpi : 0) * nb;
-  const double dc = D[cc], txc = Tx[cc];
-  const double tc = Tp[cc] * hpf;
-  double tr[HB], tpr[HB];
-#pragma unroll
-  for (int i = 0; i < HB; ++i) {
-    tr[i] = Tx[HB * h + i];
-    tpr[i] = Tp[HB * h + i];
-  }
-#pragma unroll
-  for (int i = 0; i < HB; ++i) {
-    const int r = HB * h + i;
-    const int d = r - c;
-    double v = d == 0 ? dc : d == -1 ? -tr[i] : d == 1 ? -txc : 0.0;
-    v = fma(-tpr[i] * tc, w[i], v);
-    w[i] = (r < nb && c < nb) ? v : (d == 0 ? 1.0 : 0.0);
-  }
+  schur_block<double>(nb, s.Dg + j * nb, s.Tx + j * nb, tpi >= 0 ? s.Tn + tpi * nb : nullptr, w);
 }
 
 // S_j of the forward elimination; w holds W_{j-1} on entry when j > 0.
@@ -367,72 +386,76 @@ __device__ __forceinline__ void wbuild(int nb, int j, const BoxLds& s, double w[
   wbuild_t(nb, j, j - 1, s, w);
 }
 
-// In-place Gauss-Jordan inversion of the block held in w, GJB pivots per
-// step (block Gauss-Jordan without pivoting).  For the pivot set K with
-// block P = A[K][K], rows R = A[K][:] and columns C = A[:][K], one step
-// replaces A[K][j] by P^{-1} A[K][j], A[i][K] by -A[i][K] P^{-1}, A[K][K] by
-// P^{-1} and the rest by A - C P^{-1} R: the result of GJB single pivots.
-// Lane (c, h) forms v = P^{-1} r with r = A[K][c] (or the unit vector of c
-// when c is in K), then updates its 16 rows with the columns C from LDS.
-// The owning half writes the pivot rows and the lanes of the pivot columns
-// write those columns: one LDS round trip per GJB pivots.  Lines shorter than
-// NBW carry identity padding, which a pivot step leaves unchanged.
+// In-place inverse of the block held in w (symmetric, identity padding
+// outside nb x nb), 16 pivots at a time.  The 16-lane rows of the wave hold
+// the quarters of the block as the rows of 00, 10, 01 and 11, so 00 is ready
+// for the in-register inverse P; with U = block 01 and Z = P U follow
+//   S = A11 - U^T Z,  Q = S^{-1},  W10 = -Q Z^T,  W00 = P - Z W10,  W11 = Q
+// on the matrix instructions, the operands through two tiles of LDS (X^T Y
+// of accumulator layouts needs no transposition, Z^T takes one).
+// Bound: the two chains of pivots (16 and nb - 16, about 120 cycles each in
+// FP64) and the LDS round trips between them, 7,300 cycles at 24 cells.
+// Measured against four pivots per step on the vector unit with an LDS round
+// trip each (boxes of 24 x 24 cells, all of Steps 1-2 and 4): 256 boxes with
+// eight seeds 155 -> 136 us, 4096 with four 1226 -> 942 us; FP32 222 ->
+// 206 us and 1643 -> 1506 us.
 template <typename T>
-__device__ __forceinline__ void wgj_blk(int nb, GjSmem<T>& sm, T w[HB]) {
-  const int L = lane_id();
-  const int c = L & 31, h = L >> 5;
+__device__ __forceinline__ void winv(int nb, InvSmem<T>& sm, T w[HB]) {
+  using V = typename InvSmem<T>::V;
+  const int rho = lane_id() >> 4;
   bool bad = false;
-  for (int k0 = 0; k0 < NBW; k0 += HB) {
-    if (k0 >= nb) break;
-    const bool own_half = h == (k0 >> 4);
+  T a[HB];
 #pragma unroll
-    for (int kb = 0; kb < HB; kb += GJB) {
-      const int k = k0 + kb;
-      if (k >= nb) break;
-      T* rb = sm.rowb[(kb / GJB) & 1];
-      T* cb = sm.colb[(kb / GJB) & 1];
-      const int ck = c - k;
-      const bool pc = ck >= 0 && ck < GJB;
-      if (own_half) {
-#pragma unroll
-        for (int m = 0; m < GJB; ++m) rb[GJB * c + m] = w[kb + m];
-      }
-      if (pc) {
-#pragma unroll
-        for (int i = 0; i < HB; ++i) cb[ck * NBW + HB * h + i] = w[i];
-      }
-      wsync();
-      T P[GJB][GJB], r[GJB], v[GJB];
-#pragma unroll
-      for (int j = 0; j < GJB; ++j)
-#pragma unroll
-        for (int m = 0; m < GJB; ++m) P[m][j] = rb[GJB * (k + j) + m];
-      // r = unit vector (pivot-column lanes) or A[K][c], formed arithmetically:
-      // a select here becomes a branch per load, each with a full LDS wait
-#pragma unroll
-      for (int m = 0; m < GJB; ++m)
-        r[m] = fma(rb[GJB * c + m], pc ? T(0) : T(1), (pc && ck == m) ? T(1) : T(0));
-      const PivBlock<T> q = piv_block(P);
-      bad |= !(q.d0 > T(0) && q.da > T(0) && q.s0 > T(0) && q.ds > T(0));
-      piv_apply(q, r, v);
-#pragma unroll
-      for (int i = 0; i < HB; ++i) {
-        T acc = pc ? T(0) : w[i];
-#pragma unroll
-        for (int m = 0; m < GJB; ++m) acc = fma(-cb[m * NBW + HB * h + i], v[m], acc);
-        w[i] = acc;
-      }
-      if (own_half) {
-#pragma unroll
-        for (int m = 0; m < GJB; ++m) w[kb + m] = v[m];
-      }
-    }
+  for (int i = 0; i < HB; ++i) a[i] = w[i];
+  V u, d;
+  if (nb > 16) {
+    if (rho & 1) tile_put_row(sm.t[rho >> 1], w);
+    wave_lds_sync();
+    u = tile_get_t(sm.t[0]);
+    d = tile_get(sm.t[1]);
   }
-  if (bad && L == 0) sm.flag |= kFlagNotPD;
-  wsync();
+  inv16<true>(a, bad, nb);
+  bad = bad && rho == 0;  // the other rows invert what they hold
+  if (nb <= 16) {
+    if (rho == 0) {
+#pragma unroll
+      for (int i = 0; i < HB; ++i) w[i] = a[i];
+    }
+  } else {
+    const V zero = {T(0), T(0), T(0), T(0)};
+    wave_lds_sync();
+    if (rho == 0) tile_put_row(sm.t[0], a);
+    wave_lds_sync();
+    const V p = tile_get(sm.t[0]);
+    const V z = mfma16(p, u, zero);
+    const V s = mfma16(-u, z, d);
+    wave_lds_sync();
+    tile_put(sm.t[0], z);
+    tile_put(sm.t[1], s);
+    wave_lds_sync();
+    const V zt = tile_get_t(sm.t[0]);
+    tile_get_rows(sm.t[1], a);
+    inv16<true>(a, bad, nb - 16);
+    wave_lds_sync();
+    tile_put_rows(sm.t[1], a);
+    wave_lds_sync();
+    const V q = tile_get(sm.t[1]);
+    const V w10 = mfma16(-q, zt, zero, nb - 16);
+    const V w00 = mfma16(-zt, w10, p, nb - 16);
+    wave_lds_sync();
+    tile_put(sm.t[0], w00);
+    tile_put(sm.t[1], w10);
+    wave_lds_sync();
+    if (rho < 2) tile_get_rows(sm.t[rho], w);
+    else if (rho == 2) tile_get_column(sm.t[1], w);
+    else {
+#pragma unroll
+      for (int i = 0; i < HB; ++i) w[i] = a[i];
+    }
+    wave_lds_sync();
+  }
+  if (bad) atomicOr(&sm.flag, kFlagNotPD);
 }
-
-__device__ __forceinline__ void wgj(int nb, WaveSmem& sm, double w[HB]) { wgj_blk<double>(nb, sm, w); }
 
 __device__ __forceinline__ void womega(const Geo& g, int sub, int lo[3], int hi[3]) {
   const int ix = sub % g.M[0], iy = sub / g.M[0];
