@@ -14,7 +14,13 @@
 // Solves use the block LDL^T recurrences of the block-tridiagonal matrix
 // (see local.hip): forward w_j = W_j (b_j + t_{j-1} .* w_{j-1}), backward
 // x_j = w_j + W_j (t_j .* x_{j+1}).  A block product is a 16-term dot
-// product per lane followed by one exchange between the two half-waves.
+// product per lane, its vector entries taken by row broadcast, followed by
+// one exchange between the two half-waves (block_products).
+// Measured against products staged through LDS and Schur complements built
+// with branches (24 x 24 cells, all of Steps 1-2 and 4): 256 boxes with eight
+// seeds 136 -> 111 us, 4096 with four 942 -> 801 us.  What bounds a box now:
+// 13 line inverses of 7,700 cycles in a chain, 12,000 cycles per step with
+// the products of eight seeds, and 40,000 cycles of back-substitution.
 //
 // Everything a sweep touches between block steps lives in LDS: the box's
 // permeabilities (with a one-cell halo), its diagonal and couplings, and
@@ -68,16 +74,18 @@ __device__ __forceinline__ void factor_forward(const Box& B, double* Wg, double*
     wbuild(nb, j, s, w);
     winv(nb, sm, w);
     store_block(nb, fblock(Wg, nb, j), w);
-    fwd_step(nb, B.ncell, j, nrhs, s, w);
+    fwd_step_d(nb, B.ncell, j, j - 1, j > 0, nrhs, s, w);
   }
 }
 
 
 // ------------------------------------------------------------------ kernels
 
-// LDS of a basis box: the box arrays with its right-hand sides (the Z
-// scratch of BoxLds serves wave 0), the Z scratch of wave 1, and the forward
-// Schur complement of the meeting block (nb x nb, nb = m0, row-major).
+// LDS of a basis box: the box arrays with its right-hand sides, then from
+// BoxLds::Z on the forward Schur complement of the meeting block (nb x nb,
+// nb = m0, row-major).  The size decides which boxes the wave kernels take
+// and counts two vectors of NBW per right-hand side besides, as it always
+// has.
 __host__ __device__ inline size_t basis_lds_doubles(int m0, int m1, int nrhs, int kc = 1) {
   return box_lds_doubles(m0, m1, nrhs, kc) + (size_t)nrhs * NBW + (size_t)m0 * m0 + 2;
 }
@@ -111,8 +119,7 @@ __device__ __forceinline__ void basis_box(const Geo& g, const Box& B, const Seed
   const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nrhs = FO ? 0 : B.nrhs;
   BoxLds s = carve(dsm, B, nrhs, g.kc);
-  double* Z1 = s.Z + nrhs * NBW;
-  double* Sm = Z1 + nrhs * NBW;
+  double* Sm = s.Z;
   const int nc = B.ncell;
   // set-up by both waves: box arrays (K from log K), seed right-hand
   // sides, couplings
@@ -156,7 +163,7 @@ __device__ __forceinline__ void basis_box(const Geo& g, const Box& B, const Seed
       wbuild_t(nb, j, t > 0 ? (bot ? j : jp) : -1, s, w);
       winv(nb, sm[wv], w);
       store_block(nb, fblock(bot ? Wt : Wf, nb, j), w);
-      fwd_step_d(nb, nc, j, jp, t > 0, nrhs, s, bot ? Z1 : s.Z, w);
+      fwd_step_d(nb, nc, j, jp, t > 0, nrhs, s, w);
     }
   }
   if (wv == 0) {
@@ -185,12 +192,12 @@ __device__ __forceinline__ void basis_box(const Geo& g, const Box& B, const Seed
     }
     winv(nb, sm[1], w);
     store_block(nb, fblock(Wt, nb, m), w);
-    if (!FO) mid_step(nb, nc, m, nblk, nrhs, s, Z1, w);
+    if (!FO) mid_step(nb, nc, m, nblk, nrhs, s, w);
   }
   if (FO) return;
   __syncthreads();
-  if (wv == 0) twist_back_cached(B, Wf, nrhs, s, s.Z, false);
-  else twist_back_cached(B, Wt, nrhs, s, Z1, true);
+  if (wv == 0) twist_back_cached(B, Wf, nrhs, s, false);
+  else twist_back_cached(B, Wt, nrhs, s, true);
   __syncthreads();
   int olo[3], ohi[3];
   womega(g, B.sub, olo, ohi);

@@ -85,7 +85,7 @@ __device__ __forceinline__ void scale_box(const Box& B, BoxR& R) {
 
 // Scaled Schur complement of block j, see wbuild_t.
 __device__ __forceinline__ void wbuild32(int nb, int j, int tpi, const BoxR& R, float w[HB]) {
-  schur_block<float>(nb, nullptr, R.Txf + j * nb, tpi >= 0 ? R.Tnf + tpi * nb : nullptr, w);
+  schur_block<float>(nb, nullptr, R.Txf + j * nb, R.Tnf + max(tpi, 0) * nb, tpi >= 0, w);
 }
 
 // Entries outside the block get an offset out of the buffer's range: dropped.
@@ -248,11 +248,6 @@ __device__ __forceinline__ void rows32(const Lane32<KN>& f, bool bottom, Rows32<
   if (NBK > 0 && !bottom) load32(f, m, r.zm);
 }
 
-// An index the compiler recomputes where it is used: kept over the unrolled
-// steps and hoisted out of the refinement loop, the addresses alone would
-// take the registers of the inverses.
-__device__ __forceinline__ void keep_here(int& e) { asm volatile("" : "+v"(e)); }
-
 // Forward and back halves of the two-ended sweep of NR vectors (X + q nc).
 template <int KN, int NBK, int NR>
 __device__ __forceinline__ void fwd32(const Lane32<KN>& f, const Rows32<KN, NBK>& rw, const float* Tn,
@@ -263,7 +258,10 @@ __device__ __forceinline__ void fwd32(const Lane32<KN>& f, const Rows32<KN, NBK>
 #pragma unroll
   for (int q = 0; q < NR; ++q) yz[q] = 0.0f;
   const int dt = bottom ? -nb : 0, dc = f.ci - f.zi;
-  int e = j0 * nb + f.zi;  // my entry of the step's block
+  // my entry of the step's block (kept as one running index: the addresses
+  // of all steps, hoisted out of the refinement loop, would take the
+  // registers of the inverses)
+  int e = j0 * nb + f.zi;
   float xv[NR];            // and its value, read a step ahead
 #pragma unroll
   for (int q = 0; q < NR; ++q) xv[q] = X[q * nc + e];

@@ -336,6 +336,10 @@ __device__ __forceinline__ void coef_box(const Geo& g, const Box& B, double beta
   bsync<NT>();
 }
 
+// An index the compiler recomputes where it is used instead of keeping what
+// it derives from it in registers over unrolled steps and loops.
+__device__ __forceinline__ void keep_here(int& e) { asm volatile("" : "+v"(e)); }
+
 // d += a(lane K of the row) b
 template <int K>
 __device__ __forceinline__ void fmac_bcast(double& d, double a, double b) {
@@ -349,25 +353,27 @@ __device__ __forceinline__ void fmac_bcast(float& d, float a, float b) {
 template <int I, typename T>
 __device__ __forceinline__ void schur_rows(T w[HB], int ic, T dc, T xl, T xr, T th, T ntc) {
   if constexpr (I < HB) {
-    T e = I == ic ? dc : I == ic - 1 ? xl : I == ic + 1 ? xr : T(0);
+    keep_here(ic);  // (the comparisons of all rows at once spill to branches)
+    T e = ic == I ? dc : T(0);
+    e = ic == I + 1 ? xl : e;
+    e = ic == I - 1 ? xr : e;
     fmac_bcast<I>(e, th, ntc * w[I]);
     w[I] = e;
     schur_rows<I + 1>(w, ic, dc, xl, xr, th, ntc);
   }
 }
 // Schur complement (column c, my half) into w: the tridiagonal line with
-// diagonal D (null: ones) and couplings Tx, less t W t with the coupling t =
-// Tp (null: no previous block) to the block eliminated before, whose inverse
-// W w holds on entry.  A lane reads the entries of its own column and one of
+// diagonal D (null: ones, FP32) and couplings Tx, less t W t with the coupling t =
+// Tp (lower; else any line that can be read) to the block eliminated before,
+// whose inverse W w holds on entry.  A lane reads the entries of its own column and one of
 // t, which the others of its 16-lane row take by row broadcast.
 template <typename T>
-__device__ __forceinline__ void schur_block(int nb, const T* D, const T* Tx, const T* Tp, T w[HB]) {
+__device__ __forceinline__ void schur_block(int nb, const T* D, const T* Tx, const T* Tp, bool lower, T w[HB]) {
   const int L = lane_id(), c = L & 31, h = L >> 5;
   const int r = HB * h + (L & 15);
-  const bool in = c < nb, lower = Tp != nullptr;
+  const bool in = c < nb;
   const int cc = in ? c : 0, rc = r < nb ? r : 0;
-  const T* Tq = lower ? Tp : Tx;
-  const T dv = D ? D[cc] : T(1), x0 = Tx[cc > 0 ? cc - 1 : 0], x1 = Tx[cc], t0 = Tq[cc], t1 = Tq[rc];
+  const T dv = D ? D[cc] : T(1), x0 = Tx[cc > 0 ? cc - 1 : 0], x1 = Tx[cc], t0 = Tp[cc], t1 = Tp[rc];
   const T dc = in ? dv : T(1);
   const T xl = in && c > 0 ? -x0 : T(0), xr = in && c + 1 < nb ? -x1 : T(0);
   const T ntc = in && lower ? -t0 : T(0);
@@ -378,7 +384,7 @@ __device__ __forceinline__ void schur_block(int nb, const T* D, const T* Tx, con
 // Block j of a box; tpi: line of Tn that couples it to the block eliminated
 // before (forward elimination j - 1, backward j), negative: none.
 __device__ __forceinline__ void wbuild_t(int nb, int j, int tpi, const BoxLds& s, double w[HB]) {
-  schur_block<double>(nb, s.Dg + j * nb, s.Tx + j * nb, tpi >= 0 ? s.Tn + tpi * nb : nullptr, w);
+  schur_block<double>(nb, s.Dg + j * nb, s.Tx + j * nb, s.Tn + max(tpi, 0) * nb, tpi >= 0, w);
 }
 
 // S_j of the forward elimination; w holds W_{j-1} on entry when j > 0.
@@ -812,126 +818,89 @@ __device__ __forceinline__ double to_rows(double y) {
   return __hiloint2double(h ? b[1] : b[0], h ? a[1] : a[0]);
 }
 
+// Products of the block in w with a vector per right-hand side, four at a
+// time so that their chains overlap: zf(k) gives the lane's entry zi = 16 h +
+// lane % 16 of vector k (zero past nb), of(k, y) takes entry lane % 32 of the
+// product.  Entries and results live in LDS, no staging between them.
+template <typename Zf, typename Of>
+__device__ __forceinline__ void block_products(int nrhs, const double w[HB], Zf&& zf, Of&& of) {
+  wsync();
+  int k = 0;
+#pragma unroll 1
+  for (; k + 4 <= nrhs; k += 4) {
+    double z[4], y[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) z[q] = zf(k + q);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) y[q] = wgemv_rows(w, z[q]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) of(k + q, y[q]);
+  }
+#pragma unroll 1
+  for (; k < nrhs; ++k) of(k, wgemv_rows(w, zf(k)));
+  wsync();
+}
+
 // Forward step of block j for all right-hand sides, inverse in w, with jp
 // the block eliminated just before j (j - 1 going down the box, j + 1 going
 // up; has_prev false for the first block of a chain):
 // X_j <- W (X_j + t .* X_jp), t the coupling of j and jp (Tn row min(j, jp)).
-// Z: nrhs x NBW doubles of LDS scratch of the calling wave.
 __device__ __forceinline__ void fwd_step_d(int nb, int ncell, int j, int jp, bool has_prev,
-                                           int nrhs, const BoxLds& s, double* Z,
-                                           const double w[HB]) {
-  const int L = lane_id();
-  const int c = L & 31, h = L >> 5;
-  const int ti = jp < j ? jp : j;
-  #pragma unroll 4
-  for (int e = L; e < nrhs * NBW; e += 64) {
-    const int k = e / NBW, r = e % NBW;
-    double v = 0.0;
-    if (r < nb) {
-      v = s.X[k * ncell + j * nb + r];
-      if (has_prev) v += s.Tn[ti * nb + r] * s.X[k * ncell + jp * nb + r];
-    }
-    Z[k * NBW + r] = v;
-  }
-  wsync();
-  // four right-hand sides at a time: independent product chains overlap
-  for (int k0 = 0; k0 < nrhs; k0 += 4) {
-    double y[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) y[q] = wgemv2(w, Z + min(k0 + q, nrhs - 1) * NBW);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (k0 + q < nrhs && h == 0 && c < nb) s.X[(k0 + q) * ncell + j * nb + c] = y[q];
-  }
-  wsync();
-}
-
-__device__ __forceinline__ void fwd_step(int nb, int ncell, int j, int nrhs, const BoxLds& s,
-                                         const double w[HB]) {
-  fwd_step_d(nb, ncell, j, j - 1, j > 0, nrhs, s, s.Z, w);
+                                           int nrhs, const BoxLds& s, const double w[HB]) {
+  const int L = lane_id(), c = L & 31, zi = HB * (L >> 5) + (L & 15);
+  const bool zv = zi < nb, cv = L < 32 && c < nb;
+  const int zc = zv ? zi : 0;
+  const double t = has_prev ? s.Tn[min(j, jp) * nb + zc] : 0.0;
+  const double* Xj = s.X + j * nb + zc;
+  const double* Xp = s.X + (has_prev ? jp : j) * nb + zc;
+  double* Xo = s.X + j * nb + c;
+  block_products(
+      nrhs, w, [&](int k) { return zv ? fma(t, Xp[k * ncell], Xj[k * ncell]) : 0.0; },
+      [&](int k, double y) {
+        if (cv) Xo[k * ncell] = y;
+      });
 }
 
 // Back-substitution step of block j towards block jn (the block solved just
 // before it): X_j <- X_j + W (t .* X_jn), t the coupling of j and jn.
 __device__ __forceinline__ void bwd_step_d(int nb, int ncell, int j, int jn, int nrhs,
-                                           const BoxLds& s, double* Z, const double w[HB]) {
-  const int L = lane_id();
-  const int c = L & 31, h = L >> 5;
-  const int ti = jn < j ? jn : j;
-  #pragma unroll 4
-  for (int e = L; e < nrhs * NBW; e += 64) {
-    const int k = e / NBW, r = e % NBW;
-    Z[k * NBW + r] = (r < nb) ? s.Tn[ti * nb + r] * s.X[k * ncell + jn * nb + r] : 0.0;
-  }
-  wsync();
-  for (int k0 = 0; k0 < nrhs; k0 += 4) {
-    double y[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) y[q] = wgemv2(w, Z + min(k0 + q, nrhs - 1) * NBW);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (k0 + q < nrhs && h == 0 && c < nb) s.X[(k0 + q) * ncell + j * nb + c] += y[q];
-  }
-  wsync();
-}
-
-// Backward step of the one-ended solve: X_j <- X_j + W_j (t_j .* X_{j+1}).
-__device__ __forceinline__ void bwd_step(int nb, int ncell, int j, int nrhs, const BoxLds& s,
-                                         const double w[HB]) {
-  bwd_step_d(nb, ncell, j, j + 1, nrhs, s, s.Z, w);
+                                           const BoxLds& s, const double w[HB]) {
+  const int L = lane_id(), c = L & 31, zi = HB * (L >> 5) + (L & 15);
+  const bool zv = zi < nb, cv = L < 32 && c < nb;
+  const int zc = zv ? zi : 0;
+  const double t = s.Tn[min(j, jn) * nb + zc];
+  const double* Xn = s.X + jn * nb + zc;
+  double* Xo = s.X + j * nb + c;
+  block_products(
+      nrhs, w, [&](int k) { return zv ? t * Xn[k * ncell] : 0.0; },
+      [&](int k, double y) {
+        if (cv) Xo[k * ncell] += y;
+      });
 }
 
 // Meeting block of the two-ended solve, all right-hand sides, Z_m in w:
 // X_m <- Z_m (X_m + t_{m-1} .* X_{m-1} + t_m .* X_{m+1}).
 __device__ __forceinline__ void mid_step(int nb, int ncell, int m, int nblk, int nrhs,
-                                         const BoxLds& s, double* Z, const double w[HB]) {
-  const int L = lane_id();
-  const int c = L & 31, h = L >> 5;
-  #pragma unroll 4
-  for (int e = L; e < nrhs * NBW; e += 64) {
-    const int k = e / NBW, r = e % NBW;
-    double v = 0.0;
-    if (r < nb) {
-      const double* X = s.X + k * ncell;
-      v = X[m * nb + r];
-      if (m > 0) v = fma(s.Tn[(m - 1) * nb + r], X[(m - 1) * nb + r], v);
-      if (m + 1 < nblk) v = fma(s.Tn[m * nb + r], X[(m + 1) * nb + r], v);
-    }
-    Z[k * NBW + r] = v;
-  }
-  wsync();
-  for (int k0 = 0; k0 < nrhs; k0 += 4) {
-    double y[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) y[q] = wgemv2(w, Z + min(k0 + q, nrhs - 1) * NBW);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (k0 + q < nrhs && h == 0 && c < nb) s.X[(k0 + q) * ncell + m * nb + c] = y[q];
-  }
-  wsync();
+                                         const BoxLds& s, const double w[HB]) {
+  const int L = lane_id(), c = L & 31, zi = HB * (L >> 5) + (L & 15);
+  const bool zv = zi < nb, cv = L < 32 && c < nb;
+  const int e = m * nb + (zv ? zi : 0), up = m > 0 ? nb : 0, dn = m + 1 < nblk ? nb : 0;
+  const double tu = up ? s.Tn[e - up] : 0.0, td = dn ? s.Tn[e] : 0.0;
+  double* Xo = s.X + m * nb + c;
+  block_products(
+      nrhs, w,
+      [&](int k) {
+        const double* X = s.X + k * ncell + e;
+        const double v = fma(td, X[dn], fma(tu, X[-up], X[0]));
+        return zv ? v : 0.0;
+      },
+      [&](int k, double y) {
+        if (cv) Xo[k * ncell] = y;
+      });
 }
 
-// Sweeps with the cached inverses streamed from memory, RING blocks ahead.
-__device__ __forceinline__ void forward_cached(const Box& B, const double* Wg, int nrhs, const BoxLds& s) {
-  const int nb = B.nb, nblk = B.nblk;
-  const long long bs = (long long)nb * nb;
-  const BlockSrc<double> src = block_src(Wg, nb, nblk);
-  double w[RING][HB];
-#pragma unroll
-  for (int q = 0; q < RING; ++q)
-    if (q < nblk) wload_block(src, q, w[q]);
-  for (int j0 = 0; j0 < nblk; j0 += RING) {
-#pragma unroll
-    for (int q = 0; q < RING; ++q) {
-      const int j = j0 + q;
-      if (j < nblk) {
-        fwd_step(nb, B.ncell, j, nrhs, s, w[q]);
-        if (j + RING < nblk) wload_block(src, (j + RING), w[q]);
-      }
-    }
-  }
-}
-
+// Back-substitution of the one-ended solve, X_j <- X_j + W_j (t_j .*
+// X_{j+1}), with the cached inverses streamed from memory, RING blocks ahead.
 __device__ __forceinline__ void backward_cached(const Box& B, const double* Wg, int nrhs, const BoxLds& s) {
   const int nb = B.nb, nblk = B.nblk;
   const long long bs = (long long)nb * nb;
@@ -946,7 +915,7 @@ __device__ __forceinline__ void backward_cached(const Box& B, const double* Wg, 
     for (int q = 0; q < RING; ++q) {
       const int j = nblk - 2 - (t0 + q);
       if (j >= 0) {
-        bwd_step(nb, B.ncell, j, nrhs, s, w[q]);
+        bwd_step_d(nb, B.ncell, j, j + 1, nrhs, s, w[q]);
         if (j - RING >= 0) wload_block(src, (j - RING), w[q]);
       }
     }
@@ -960,7 +929,7 @@ __device__ __forceinline__ void backward_cached(const Box& B, const double* Wg, 
 // from its end of the box towards m; the back-substitution from m outwards.
 // The inverses stream from memory RING blocks ahead of their use.
 __device__ __forceinline__ void twist_fwd_cached(const Box& B, const double* Wg, int nrhs,
-                                                 const BoxLds& s, double* Z, bool bottom) {
+                                                 const BoxLds& s, bool bottom) {
   const int nb = B.nb, nblk = B.nblk, m = nblk / 2;
   const int cnt = bottom ? nblk - 1 - m : m;
   const int j0 = bottom ? nblk - 1 : 0, dj = bottom ? -1 : 1;
@@ -976,7 +945,7 @@ __device__ __forceinline__ void twist_fwd_cached(const Box& B, const double* Wg,
       const int t = t0 + q;
       if (t < cnt) {
         const int j = j0 + dj * t;
-        fwd_step_d(nb, B.ncell, j, j - dj, t > 0, nrhs, s, Z, w[q]);
+        fwd_step_d(nb, B.ncell, j, j - dj, t > 0, nrhs, s, w[q]);
         if (t + RING < cnt) wload_block(src, j0 + dj * (t + RING), w[q]);
       }
     }
@@ -984,7 +953,7 @@ __device__ __forceinline__ void twist_fwd_cached(const Box& B, const double* Wg,
 }
 
 __device__ __forceinline__ void twist_back_cached(const Box& B, const double* Wg, int nrhs,
-                                                  const BoxLds& s, double* Z, bool bottom) {
+                                                  const BoxLds& s, bool bottom) {
   const int nb = B.nb, nblk = B.nblk, m = nblk / 2;
   const int cnt = bottom ? nblk - 1 - m : m;
   const int dj = bottom ? 1 : -1;  // direction away from m
@@ -1000,7 +969,7 @@ __device__ __forceinline__ void twist_back_cached(const Box& B, const double* Wg
       const int t = t0 + q;
       if (t < cnt) {
         const int j = m + dj * (t + 1);
-        bwd_step_d(nb, B.ncell, j, j - dj, nrhs, s, Z, w[q]);
+        bwd_step_d(nb, B.ncell, j, j - dj, nrhs, s, w[q]);
         if (t + RING < cnt) wload_block(src, m + dj * (t + RING + 1), w[q]);
       }
     }
@@ -1013,13 +982,13 @@ __device__ __forceinline__ void twist_back_cached(const Box& B, const double* Wg
 __device__ __forceinline__ void twisted_cached(const Box& B, const double* Wf, const double* Wt,
                                                int nrhs, const BoxLds& s) {
   const int m = B.nblk / 2;
-  twist_fwd_cached(B, Wf, nrhs, s, s.Z, false);
-  twist_fwd_cached(B, Wt, nrhs, s, s.Z, true);
+  twist_fwd_cached(B, Wf, nrhs, s, false);
+  twist_fwd_cached(B, Wt, nrhs, s, true);
   double zm[HB];
   wload_block(block_src(Wt, B.nb, B.nblk), m, zm);
-  mid_step(B.nb, B.ncell, m, B.nblk, nrhs, s, s.Z, zm);
-  twist_back_cached(B, Wf, nrhs, s, s.Z, false);
-  twist_back_cached(B, Wt, nrhs, s, s.Z, true);
+  mid_step(B.nb, B.ncell, m, B.nblk, nrhs, s, zm);
+  twist_back_cached(B, Wf, nrhs, s, false);
+  twist_back_cached(B, Wt, nrhs, s, true);
 }
 
 // Forward and backward sweeps of one right-hand side in s.X with the cached
