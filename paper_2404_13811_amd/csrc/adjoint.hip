@@ -84,7 +84,7 @@ __device__ __forceinline__ void box_matrix_adjoint(const Geo& g, const Box& B, c
   const int m0 = s.m0, m1 = s.m1, nc = m0 * m1;
   const int tid = threadIdx.x % NT;
   // interior faces, gathered by cell: one atomic add per cell instead of two
-  // per face (those to memory bound the batched reverse pass)
+  // per face (smoothing phases of 2048 boxes of 20 x 20 cells 117 -> 111 us)
 #pragma unroll 1
   for (int c = tid; c < nc; c += NT) {
     const int yl = c / m0, xl = c - yl * m0;
@@ -232,10 +232,10 @@ __host__ __device__ inline size_t adj_res_off(int m0, int m1) {
 // inverses above it and Z_m): the same arithmetic as the forward smoothing
 // step, so the reverse pass recomputes the forward state exactly.
 __device__ __forceinline__ void box_solve(const Box& B, const double* Wf, const double* Wt,
-                                          const BoxLds& s, double* z) {
+                                          const BoxLds& s) {
   double w[RING][HB], zm[HB];
   wload_block(block_src(Wt, B.nb, B.nblk), B.nblk / 2, zm);
-  sweep_twisted<64>(B, Wf, Wt, s, z, w, zm);
+  sweep_twisted<64>(B, Wf, Wt, s, w, zm);
 }
 
 // One colour phase in reverse.  p_in / gf_in: the state before the phase.
@@ -244,7 +244,9 @@ __device__ __forceinline__ void box_solve(const Box& B, const double* Wf, const 
 // factors resident in LDS (lds_sweep, the halves on two waves) instead of
 // streamed by one wave: the form of every box whose LDS fits.  Measured per
 // phase: 64 boxes of 20 x 20 cells 41.6 -> 22.5 us, 2048 boxes 211 ->
-// 117 us.
+// 117 us.  LDS decides how many boxes share a CU: with the arrays that the
+// resident form does not need folded away, three of 20 x 20 cells instead of
+// two, 2048 boxes 111 -> 90 us.
 template <bool F32, bool RES>
 __global__ void __launch_bounds__(kAdjNT) k_adj_smooth(Geo g, const Box* __restrict__ boxes,
                                                        const int* __restrict__ members,
@@ -305,7 +307,7 @@ __global__ void __launch_bounds__(kAdjNT) k_adj_smooth(Geo g, const Box* __restr
       staged_wait<NT>();
       lds_sweep<NT>(B, img, r.b.Tn, r.b.X);
     } else if (tid < 64) {
-      box_solve(B, fac + B.fac, fact + B.fac, r.b, r.b.Z);
+      box_solve(B, fac + B.fac, fact + B.fac, r.b);
     }
   }
   __syncthreads();
@@ -382,7 +384,7 @@ __global__ void __launch_bounds__(kAdjNT) k_adj_smooth(Geo g, const Box* __restr
     BoxLds sm = r.b;
     sm.X = mu;
     if constexpr (RES) lds_sweep<NT>(B, img, r.b.Tn, mu);
-    else if (tid < 64) box_solve(B, fac + B.fac, fact + B.fac, sm, r.b.Z);
+    else if (tid < 64) box_solve(B, fac + B.fac, fact + B.fac, sm);
   }
   __syncthreads();
   // (d) K terms of the box matrix and right-hand side; lambda_bar of the
@@ -553,7 +555,7 @@ __global__ void k_adj_moments(Geo g, const Iface* __restrict__ ifc, const Seed* 
 // solve with the cached inverses and accumulate the K terms.  F32: the
 // FP32 form (fac and fact unused).
 // (Registers held to two waves per SIMD: 4096 boxes with four seeds 1050 ->
-// 960 us with the products by row broadcast.)
+// 932 us with the products by row broadcast.)
 template <bool F32>
 __global__ void __launch_bounds__(64, 2) k_adj_basis(Geo g, const Box* __restrict__ boxes,
                                                   const Seed* __restrict__ seeds,

@@ -1203,10 +1203,10 @@ __device__ __forceinline__ void twist_back(const Box& B, const TwistHalf& hf, co
 // block (zm), before staging, so that their memory latency is hidden.  With
 // NT = 64 one wave runs the halves one after the other and loads as it
 // goes.  The arithmetic is the same in both cases, and so is the result.
-// Wf: forward inverses, Wt: backward inverses and Z_m; z: 4 x NBW doubles.
+// Wf: forward inverses, Wt: backward inverses and Z_m.
 template <int NT>
 __device__ __forceinline__ void sweep_twisted(const Box& B, const double* Wf, const double* Wt,
-                                              const BoxLds& s, double* z, double w[RING][HB],
+                                              const BoxLds& s, double w[RING][HB],
                                               const double zm[HB]) {
   const int wv = threadIdx.x >> 6;
   const int m = B.nblk / 2;
