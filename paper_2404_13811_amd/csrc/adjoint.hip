@@ -819,6 +819,26 @@ __global__ void __launch_bounds__(64) k_adj_particular(Geo g, const Box* __restr
   }
 }
 
+// State before a smoothing phase into its checkpoint: pressure and Gamma
+// fluxes in one launch, four loads in flight per thread.  Bound: launches on
+// small grids (two copies of 2.3 us each before), memory on large ones.
+constexpr int kCkNT = 256, kCkPer = 4;
+__global__ void __launch_bounds__(kCkNT) k_checkpoint(const double* __restrict__ p, double* __restrict__ ck_p,
+                                                      long long np, const double* __restrict__ gf,
+                                                      double* __restrict__ ck_g, long long ng, int gp) {
+  const bool isp = (int)blockIdx.x < gp;  // workgroups of the pressure first
+  const double* src = isp ? p : gf;
+  double* dst = isp ? ck_p : ck_g;
+  const long long n = isp ? np : ng;
+  const long long i0 = (long long)(blockIdx.x - (isp ? 0 : gp)) * (kCkNT * kCkPer) + threadIdx.x;
+  double v[kCkPer];
+#pragma unroll
+  for (int q = 0; q < kCkPer; ++q) v[q] = i0 + q * kCkNT < n ? src[i0 + q * kCkNT] : 0.0;
+#pragma unroll
+  for (int q = 0; q < kCkPer; ++q)
+    if (i0 + q * kCkNT < n) dst[i0 + q * kCkNT] = v[q];
+}
+
 __global__ void k_adj_logk(const double* __restrict__ K, const double* __restrict__ Kb, int n,
                            double* __restrict__ out) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -969,6 +989,15 @@ hipError_t launch_adj_particular(const Geo& g, const Box* boxes, int nbox, const
     hipLaunchKernelGGL(k_adj_particular<false>, dim3(nbox), dim3(64), lds, s, g, boxes, K, bcv, beta, fac,
                        rf, pbar, pb, ubarb, pibarb, Kb);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_checkpoint(const double* p, double* ck_p, size_t np, const double* gf, double* ck_g, size_t ng,
+                             hipStream_t s) {
+  const size_t per = (size_t)kCkNT * kCkPer, gp = (np + per - 1) / per, gg = (ng + per - 1) / per;
+  if (gp + gg == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_checkpoint, dim3((unsigned)(gp + gg)), dim3(kCkNT), 0, s, p, ck_p, (long long)np, gf, ck_g,
+                     (long long)ng, (int)gp);
   return hipGetLastError();
 }
 

@@ -1407,8 +1407,7 @@ mrcm_status sweep(mrcm_ctx* c, hipStream_t s, int nt, double* p, double* gflux, 
     const int m0 = c->member_off[col], m1 = c->member_off[col + 1];
     if (ck) {
       // state before this phase, for the reverse pass
-      HIPCHK(c, hipMemcpyAsync(c->ck_p + c->n_ck * np, p, np * sizeof(double), hipMemcpyDeviceToDevice, s));
-      HIPCHK(c, hipMemcpyAsync(c->ck_g + c->n_ck * ng, gflux, ng * sizeof(double), hipMemcpyDeviceToDevice, s));
+      HIPCHK(c, launch_checkpoint(p, c->ck_p + c->n_ck * np, np, gflux, c->ck_g + c->n_ck * ng, ng, s));
       ++c->n_ck;
     }
     const bool own = c->beta_sm != c->beta_mbf;  // Step 6 factors

@@ -428,6 +428,9 @@ hipError_t launch_adj_particular(const Geo& g, const Box* boxes, int nbox, const
                                  const double* bcv, double beta, const double* fac, const Adj32* f32,
                                  const double* pbar, const double* pb, const double* ubarb,
                                  const double* pibarb, double* Kb, size_t lds, hipStream_t s);
+// p and the Gamma fluxes into a checkpoint
+hipError_t launch_checkpoint(const double* p, double* ck_p, size_t np, const double* gf, double* ck_g, size_t ng,
+                             hipStream_t s);
 hipError_t launch_adj_logk(const double* K, const double* Kb, int n, double* out, hipStream_t s);
 hipError_t launch_bcr_scatter_t(const double* RB, const double* rhs, int n, int kl, int ku,
                                 const int* row_lvl, const int* row_loc, const int* col_lvl,
