@@ -443,11 +443,15 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
-// The largest v over the NT threads of the box (red: NT / 64 doubles of LDS).
+// The largest v over the NT threads of the box (red: NT / 64 doubles of LDS);
+// a barrier of the box as well.
 template <int NT>
 __device__ __forceinline__ double box_max(double v, double* red) {
   v = wave_max(v);
-  if constexpr (NT == 64) return v;
+  if constexpr (NT == 64) {
+    bsync<NT>();
+    return v;
+  }
   if (lane_id() == 0) red[(int)(threadIdx.x % NT) >> 6] = v;
   bsync<NT>();
 #pragma unroll

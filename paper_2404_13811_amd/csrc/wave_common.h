@@ -1,6 +1,6 @@
-// Shared pieces of the one-wavefront-per-box 2-D local kernels (FP64 and
+// Shared pieces of the 2-D local kernels, a wave per half of a box (FP64 and
 // FP32-with-refinement forms): LDS layout of a box, coefficient loading,
-// the Gauss-Jordan block inverse in the two-half-wave register layout, and
+// the block inverse in the two-half-wave register layout, and
 // geometry helpers.  See local_wave.hip for the algorithm.
 #pragma once
 #include "local_common.h"
