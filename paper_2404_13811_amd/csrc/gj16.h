@@ -153,7 +153,8 @@ __device__ __forceinline__ void tile_put_rows(double* t, const double a[16]) {
   double v[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const double lo = g & 1 ? a[4 + j] : a[j], hi = g & 1 ? a[12 + j] : a[8 + j];
+    const double a0 = a[j], a1 = a[4 + j], a2 = a[8 + j], a3 = a[12 + j];
+    const double lo = g & 1 ? a1 : a0, hi = g & 1 ? a3 : a2;
     v[j] = g & 2 ? hi : lo;
   }
   *reinterpret_cast<double2*>(t + tile_at(row, 4 * g)) = make_double2(v[0], v[1]);
@@ -203,7 +204,10 @@ __device__ __forceinline__ void tile_put_rows(float* t, const float a[16]) {
   flt4 v;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const float lo = g & 1 ? a[4 + j] : a[j], hi = g & 1 ? a[12 + j] : a[8 + j];
+    // (values: a select between entries of the array is one of addresses,
+    // and the array then lives in scratch memory)
+    const float a0 = a[j], a1 = a[4 + j], a2 = a[8 + j], a3 = a[12 + j];
+    const float lo = g & 1 ? a1 : a0, hi = g & 1 ? a3 : a2;
     v[j] = g & 2 ? hi : lo;
   }
   *reinterpret_cast<flt4*>(t + 20 * (l & 15) + 4 * g) = v;

@@ -242,7 +242,12 @@ __device__ __forceinline__ BoxLds carve(double* base, const Box& B, int nrhs, in
 }
 
 // The halo tile of axis a's permeability entries.
-__device__ __forceinline__ const double* ktile(const BoxLds& s, int a) { return a == 0 ? s.Kt : s.Ky; }
+// (Values: a select between fields is one of addresses, and the struct then
+// lives in scratch memory.)
+__device__ __forceinline__ const double* ktile(const BoxLds& s, int a) {
+  const double *kx = s.Kt, *ky = s.Ky;
+  return a == 0 ? kx : ky;
+}
 
 // K along axis a at global cell (x, y), which must lie in the box or its
 // halo.
