@@ -98,6 +98,7 @@ struct mrcm_ctx {
   SmoothArrays sarr{nullptr, nullptr, nullptr, 0};
   size_t lds32_basis = 0, lds32_part = 0, lds32_smooth = 0;
   int form32 = 0;  // their kernel class (wave32_form of the largest box)
+  int nrhs32 = 1;  // most seeds of a box
   float *fac32 = nullptr, *facp32 = nullptr;
   int* d_iters = nullptr;
   unsigned long long* d_resid = nullptr;
@@ -707,7 +708,9 @@ mrcm_status make_plan(mrcm_ctx* c) {
     c->wave = false;
   if (!c->wave || c->lds_smooth_res > 150 * 1024) c->lds_smooth_res = 0;
   int nb32 = 1, nblk32 = 1;
+  c->nrhs32 = 1;
   for (const Box& B : c->obox) {
+    c->nrhs32 = std::max(c->nrhs32, B.nrhs);
     nb32 = std::max(nb32, B.nb);
     nblk32 = std::max(nblk32, B.nblk);
   }
@@ -1250,7 +1253,7 @@ mrcm_status mrcm_build_basis(mrcm_ctx* c) {
                                c->bcv, c->beta_mbf, c->fac32, c->facp32, c->Pk, c->tr_u, c->tr_phi,
                                c->tr_beta, c->pbar, c->ubar, c->pibar, c->tol, c->max_refine,
                                c->d_iters, c->d_resid, c->flags,
-                               c->form32, std::max(c->lds32_basis, c->lds32_part), s));
+                               c->form32, c->nrhs32, std::max(c->lds32_basis, c->lds32_part), s));
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[9], s));
   } else if (c->wave) {
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[8], s));

@@ -13,7 +13,8 @@
 // or max_refine corrections have been applied (flag MRCM_ENOCONV).  The
 // interface system and every reduction stay in FP64.
 //
-// A box is solved by four waves (Steps 1-2, 4) or one to four (smoothing):
+// A box is solved by four waves (Steps 1-2, 4; two where many boxes wait,
+// see two_waves32), two (Step 6) or one to four (smoothing):
 // the factor and every sweep from both ends on a pair of waves, residuals
 // and updates on all threads.  The kernels come in classes by the largest
 // box (wave32_form): <KN, NBK> with KN products per block step (half a line)
@@ -28,6 +29,8 @@
 // (64 boxes), 140 -> 66 us (1024 boxes).
 #include "wave32_common.h"
 
+#include <algorithm>
+
 namespace mrcm {
 namespace {
 
@@ -35,10 +38,9 @@ using namespace wave;
 
 // ------------------------------------------------------------------ kernels
 
-constexpr int kLocal32NT = 256;
-
-// Steps 1-2 on an oversampled box: FP32 factor, seeds refined to tol.
-template <int KN, int NBK>
+// Steps 1-2 on an oversampled box by NT threads: FP32 factor, seeds refined
+// to tol (TAB: the seeds' T^R from a table, see kSeedTable).
+template <int NT, int KN, int NBK, bool TAB>
 __device__ __forceinline__ void basis32_box(const Geo& g, const Box& B, const Seed* __restrict__ seeds,
                                             const double* __restrict__ K, double beta,
                                             float* __restrict__ fac32, double* __restrict__ Pk,
@@ -46,13 +48,12 @@ __device__ __forceinline__ void basis32_box(const Geo& g, const Box& B, const Se
                                             double* __restrict__ tr_beta, double tol, int max_refine,
                                             int* iters, unsigned long long* resid, double* dsm,
                                             WaveSmemF* sm) {
-  constexpr int NT = kLocal32NT;
   const int L = threadIdx.x;
   const int nrhs = B.nrhs;
   BoxR R = carve_r(dsm, B, max(nrhs, 1), 0, g.kc);
   load_box<NT>(g, B, K, beta, R.b);
   scale_box<NT>(B, R);
-  if (NBK > 0 && nrhs > 0) seed_faces<NT>(g, B, R, beta);
+  if (TAB && nrhs > 0) seed_faces<NT>(g, B, R, beta);
   float* Wg = fac32 + B.fac;
   factor32<NT>(B, Wg, R, sm);
   double omega = 0.0;
@@ -61,7 +62,7 @@ __device__ __forceinline__ void basis32_box(const Geo& g, const Box& B, const Se
     const Lane32<KN> f = lane32<KN>(B, Wg);
     Rows32<KN, NBK> rw;
     rows32<KN, NBK>(f, (threadIdx.x >> 6) & 1, rw);
-    it = refine<NT, KN, NBK, 4, true>(g, B, R, f, rw, nrhs, seeds, beta, tol, max_refine, omega, sm[0].flag);
+    it = refine<NT, KN, NBK, 4, true, TAB>(g, B, R, f, rw, nrhs, seeds, beta, tol, max_refine, omega, sm[0].flag);
   }
   if (L < 64) record_refine(it, omega, iters, resid);
   const BoxLds& s = R.b;
@@ -112,7 +113,7 @@ __device__ __forceinline__ void basis32_box(const Geo& g, const Box& B, const Se
 }
 
 // Step 4 on a subdomain: FP32 factor, particular solution refined to tol.
-template <int KN, int NBK>
+template <int NT, int KN, int NBK>
 __device__ __forceinline__ void particular32_box(const Geo& g, const Box& B, const double* __restrict__ K,
                                                  const double* __restrict__ f,
                                                  const double* __restrict__ bcv, double beta,
@@ -121,7 +122,6 @@ __device__ __forceinline__ void particular32_box(const Geo& g, const Box& B, con
                                                  double tol, int max_refine, int* iters,
                                                  unsigned long long* resid, double* dsm,
                                                  WaveSmemF* sm) {
-  constexpr int NT = kLocal32NT;
   const int L = threadIdx.x;
   BoxR R = carve_r(dsm, B, 1, 1, g.kc);
   load_box<NT>(g, B, K, beta, R.b);
@@ -165,8 +165,8 @@ __device__ __forceinline__ void particular32_box(const Geo& g, const Box& B, con
 // Steps 1-2 and 4 in one launch: workgroups [0, nbox) take the oversampled
 // boxes, workgroups [nbox, 2 nbox) the particular problems.  The two sets are
 // independent and run side by side.
-template <int KN, int NBK>
-__global__ void __launch_bounds__(kLocal32NT, KN == 12 ? 2 : 1) k_local32(Geo g, const Box* __restrict__ obox,
+template <int NT, int KN, int NBK, bool TAB>
+__global__ void __launch_bounds__(NT, NT == 128 ? 4 : KN == 12 ? 2 : 1) k_local32(Geo g, const Box* __restrict__ obox,
                                                 const Box* __restrict__ pbox, int nbox,
                                                 const Seed* __restrict__ seeds,
                                                 const double* __restrict__ K,
@@ -190,11 +190,11 @@ __global__ void __launch_bounds__(kLocal32NT, KN == 12 ? 2 : 1) k_local32(Geo g,
   const int b = blockIdx.x;
   if (b < nbox) {
     const Box B = obox[b];
-    basis32_box<KN, NBK>(g, B, seeds, K, beta, fac32, Pk, tr_u, tr_phi, tr_beta, tol, max_refine, iters,
+    basis32_box<NT, KN, NBK, TAB>(g, B, seeds, K, beta, fac32, Pk, tr_u, tr_phi, tr_beta, tol, max_refine, iters,
                 resid, dsm, sm);
   } else {
     const Box B = pbox[b - nbox];
-    particular32_box<KN, NBK>(g, B, K, f, bcv, beta, facp32, pbar, ubar, pibar, tol, max_refine, iters,
+    particular32_box<NT, KN, NBK>(g, B, K, f, bcv, beta, facp32, pbar, ubar, pibar, tol, max_refine, iters,
                      resid, dsm, sm);
   }
   __syncthreads();
@@ -203,8 +203,9 @@ __global__ void __launch_bounds__(kLocal32NT, KN == 12 ? 2 : 1) k_local32(Geo g,
 
 // Algorithm 1, Step 6 in the FP32 form: the oversampled boxes factored
 // again (FP32, diagonally scaled) with the smoothing Robin parameter; no
-// right-hand side is solved.
-__global__ void __launch_bounds__(kLocal32NT) k_factor32(Geo g, const Box* __restrict__ obox,
+// right-hand side is solved, so a wave per half is all it takes.
+constexpr int kFactor32NT = 128;
+__global__ void __launch_bounds__(kFactor32NT) k_factor32(Geo g, const Box* __restrict__ obox,
                                                  const double* __restrict__ K, double beta,
                                                  float* __restrict__ fac32, int* iters,
                                                  unsigned long long* resid, int* flags) {
@@ -214,7 +215,7 @@ __global__ void __launch_bounds__(kLocal32NT) k_factor32(Geo g, const Box* __res
   __syncthreads();
   Box B = obox[blockIdx.x];
   B.nrhs = 0;
-  basis32_box<16, 0>(g, B, nullptr, K, beta, fac32, nullptr, nullptr, nullptr, nullptr, 1.0, 0, iters,
+  basis32_box<kFactor32NT, 16, 0, false>(g, B, nullptr, K, beta, fac32, nullptr, nullptr, nullptr, nullptr, 1.0, 0, iters,
               resid, dsm, sm);
   __syncthreads();
   if (threadIdx.x == 0 && (sm[0].flag | sm[1].flag)) atomicOr(flags, sm[0].flag | sm[1].flag);
@@ -276,23 +277,47 @@ int wave32_form(int nb, int nblk) { return nblk > 33 ? 2 : nb <= 24 && nblk <= 2
 
 size_t wave32_smooth_lds_bytes(int m0, int m1, int kc) { return smooth32_lds_bytes(m0, m1, kc); }
 
+// Steps 1-2 and 4 by two waves per box that stream the inverses (128
+// registers, up to eight boxes per CU) instead of four that hold them (form
+// 0: two boxes per CU, form 1: one)?  A box alone takes 1.15 times as long
+// with up to four seeds, 1.5 times with more (they go four at a time to a
+// pair of waves), so two waves pay where enough boxes wait and LDS lets more
+// of them share a CU.  Measured, four waves against two, all of Steps 1-2
+// and 4: 4096 boxes of 6 x 6 cells and four seeds 410 and 162 us, 14 x 14
+// 617 and 322 us, 20 x 20 991 and 811 us, 24 x 24 1395 and 1585 us; 1024
+// boxes of 10 x 10 with eight seeds 180 and 124 us, 16 x 16 234 and 258 us;
+// 256 boxes of 14 x 14 with four seeds 61 and 67 us.
+static bool two_waves32(int form, int nbox, int nrhs, size_t lds, int ncu) {
+  const size_t box = lds + 2 * sizeof(WaveSmemF);
+  const double fit = std::max<double>(1.0, (double)(size_t)(160 * 1024 / box));
+  auto rounds = [&](double per_cu) { return std::max(1.0, nbox / (std::min(per_cu, fit) * ncu)); };
+  return rounds(8.0) * (nrhs <= 4 ? 1.15 : 1.5) < rounds(form == 0 ? 2.0 : 1.0);
+}
+
 hipError_t launch_local32_w(const Geo& g, const Box* obox, const Box* pbox, int nbox,
                             const Seed* seeds, const double* K, const double* f, const double* bcv,
                             double beta, float* fac32, float* facp32, double* Pk, double* tr_u,
                             double* tr_phi, double* tr_beta, double* pbar, double* ubar,
                             double* pibar, double tol, int max_refine, int* iters,
-                            unsigned long long* resid, int* flags, int form, size_t lds, hipStream_t s) {
+                            unsigned long long* resid, int* flags, int form, int nrhs, size_t lds,
+                            hipStream_t s) {
   if (nbox <= 0) return hipSuccess;
   if (form < 2) lds += kSeedTable;
-  auto go = [&](auto kern) -> hipError_t {
-    const hipError_t e = set_lds(kern, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(2 * nbox), dim3(kLocal32NT), lds, s, g, obox, pbox, nbox, seeds, K, f, bcv,
+  int dev = 0, ncu = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
+  auto go = [&](auto kern, int nt) -> hipError_t {
+    const hipError_t er = set_lds(kern, lds);
+    if (er != hipSuccess) return er;
+    hipLaunchKernelGGL(kern, dim3(2 * nbox), dim3(nt), lds, s, g, obox, pbox, nbox, seeds, K, f, bcv,
                        beta, fac32, facp32, Pk, tr_u, tr_phi, tr_beta, pbar, ubar, pibar, tol, max_refine,
                        iters, resid, flags);
     return hipGetLastError();
   };
-  return form == 0 ? go(k_local32<12, 12>) : form == 1 ? go(k_local32<16, 16>) : go(k_local32<16, 0>);
+  if (form == 2) return go(k_local32<256, 16, 0, false>, 256);
+  if (two_waves32(form, nbox, nrhs, lds, ncu)) return go(k_local32<128, 16, 0, true>, 128);
+  return form == 0 ? go(k_local32<256, 12, 12, true>, 256) : go(k_local32<256, 16, 16, true>, 256);
 }
 
 hipError_t launch_factor32_w(const Geo& g, const Box* obox, int nbox, const double* K, double beta,
@@ -301,7 +326,7 @@ hipError_t launch_factor32_w(const Geo& g, const Box* obox, int nbox, const doub
   if (nbox <= 0) return hipSuccess;
   hipError_t e = set_lds(k_factor32, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_factor32, dim3(nbox), dim3(kLocal32NT), lds, s, g, obox, K, beta, fac32, iters,
+  hipLaunchKernelGGL(k_factor32, dim3(nbox), dim3(kFactor32NT), lds, s, g, obox, K, beta, fac32, iters,
                      resid, flags);
   return hipGetLastError();
 }

@@ -249,7 +249,8 @@ hipError_t launch_smooth3f(const Geo& g, const Box* boxes, int nmem, const doubl
                            double tol, int max_refine, int* iters, unsigned long long* resid, int* flags,
                            size_t lds, int nw, int cached, hipStream_t s);
 
-// FP32 factors with FP64 iterative refinement (local_wave32.hip)
+// FP32 factors with FP64 iterative refinement (local_wave32.hip); form: the
+// kernel class of the largest box, nrhs: its seeds
 size_t wave32_lds_bytes(int m0, int m1, int nrhs, int nbrhs, int kc);
 size_t wave32_smooth_lds_bytes(int m0, int m1, int kc);
 // kernel class of boxes with up to nblk lines of nb cells
@@ -259,7 +260,8 @@ hipError_t launch_local32_w(const Geo& g, const Box* obox, const Box* pbox, int 
                             double beta, float* fac32, float* facp32, double* Pk, double* tr_u,
                             double* tr_phi, double* tr_beta, double* pbar, double* ubar,
                             double* pibar, double tol, int max_refine, int* iters,
-                            unsigned long long* resid, int* flags, int form, size_t lds, hipStream_t s);
+                            unsigned long long* resid, int* flags, int form, int nrhs, size_t lds,
+                            hipStream_t s);
 // Step 6 in the FP32 form: FP32 factors of the scaled oversampled boxes
 // with the smoothing Robin parameter (K must hold exp(log K))
 hipError_t launch_factor32_w(const Geo& g, const Box* obox, int nbox, const double* K, double beta,

@@ -492,9 +492,9 @@ __device__ __forceinline__ double seed_rhs(const Geo& g, const Box& B, const Box
 }
 
 // Iterative refinement of nrhs systems A x_k = b_k by the NT threads of a
-// box; b from seeds (SEEDS; NBK > 0: after seed_faces) or from R.Bv (nrhs x
+// box; b from seeds (SEEDS; TAB: after seed_faces) or from R.Bv (nrhs x
 // ncell).  Returns the number of FP32 solves.
-template <int NT, int KN, int NBK, int NR, bool SEEDS = false>
+template <int NT, int KN, int NBK, int NR, bool SEEDS = false, bool TAB = (NBK > 0)>
 __device__ __forceinline__ int refine(const Geo& g, const Box& B, const BoxR& R, const Lane32<KN>& f,
                                       const Rows32<KN, NBK>& rw, int nrhs, const Seed* seeds,
                                       double beta, double tol, int max_refine, double& omega_out,
@@ -521,7 +521,7 @@ __device__ __forceinline__ int refine(const Geo& g, const Box& B, const BoxR& R,
 #pragma unroll 1
       for (int k = 0; k < nrhs; ++k) {
         const double* x = R.b.X + (size_t)k * nc;
-        const double bv = SEEDS ? seed_rhs(g, B, R, seeds[B.seed0 + k], NBK > 0 ? R.red + NT / 64 : nullptr, beta, xl, yl)
+        const double bv = SEEDS ? seed_rhs(g, B, R, seeds[B.seed0 + k], TAB ? R.red + NT / 64 : nullptr, beta, xl, yl)
                                 : R.Bv[(size_t)k * nc + loc];
         const double d = dg * x[loc];
         const double t0 = txm * x[im], t1 = txp * x[ip], t2 = tnm * x[jm], t3 = tnp * x[jp];
