@@ -90,6 +90,7 @@ struct mrcm_ctx {
   // the same in the FP32 form (local3f.hip)
   size_t lds3f_basis = 0, lds3f_part = 0, lds3f_smooth = 0;
   int nw3_box = 4, nw3_part = 4;  // wavefronts per 3-D box (oversampled, subdomain)
+  int nt3_box = 4, nt3_part = 4;  // the same for the FP64 factors
   size_t lds_basis = 0, lds_part = 0, lds_smooth = 0;
   // 2-D smoothing with the factors of a box resident in LDS: its LDS bytes
   // (0: some box does not fit, the factors are streamed) and what it keeps
@@ -742,6 +743,8 @@ mrcm_status make_plan(mrcm_ctx* c) {
     c->d3 = false;
   c->nw3_box = box3_waves(nb3_box);
   c->nw3_part = box3_waves(nb3_part);
+  c->nt3_box = box3_tile_waves(nb3_box);
+  c->nt3_part = box3_tile_waves(nb3_part);
 
   // interfaces and their test functions
   c->ifc.clear();
@@ -1265,11 +1268,11 @@ mrcm_status mrcm_build_basis(mrcm_ctx* c) {
   } else if (c->d3) {
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[8], s));
     HIPCHK(c, launch_basis3(c->geo, c->d_obox, c->geo.nsub, c->d_seeds, c->logk, c->beta_mbf, c->fac,
-                            c->Pk, c->tr_u, c->tr_phi, c->tr_beta, 0, c->flags, c->lds3_basis, c->nw3_box, s));
+                            c->Pk, c->tr_u, c->tr_phi, c->tr_beta, 0, c->flags, c->lds3_basis, c->nt3_box, s));
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[9], s));
     HIPCHK(c, launch_particular3(c->geo, c->d_pbox, c->geo.nsub, c->logk, c->K, c->f, c->bcv,
                                  c->beta_mbf, c->facp, c->pbar, c->ubar, c->pibar, c->flags,
-                                 c->lds3_part, c->nw3_part, s));
+                                 c->lds3_part, c->nt3_part, s));
   } else {
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[8], s));
     HIPCHK(c, launch_basis(c->geo, c->d_obox, c->geo.nsub, c->d_seeds, c->K, c->beta_mbf, c->fac,
@@ -1303,7 +1306,7 @@ mrcm_status mrcm_build_basis(mrcm_ctx* c) {
       HIPCHK(c, grow(c->facs, c->fac_n));
       HIPCHK(c, launch_basis3(c->geo, c->d_obox, c->geo.nsub, c->d_seeds, c->logk, c->beta_sm,
                               c->facs, c->Pk, c->tr_u, c->tr_phi, c->tr_beta, 1, c->flags,
-                              c->lds3_basis, c->nw3_box, s));
+                              c->lds3_basis, c->nt3_box, s));
     } else {
       HIPCHK(c, grow(c->facs, c->fac_n));
       HIPCHK(c, launch_basis(c->geo, c->d_obox, c->geo.nsub, c->d_seeds, c->K, c->beta_sm, c->facs,

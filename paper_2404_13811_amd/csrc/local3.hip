@@ -102,13 +102,14 @@ __device__ __forceinline__ void build3(const Geo& g, const Box& B, const Box3& s
   lsync<NW>();
 }
 
-// Pivot tile -> its inverse, in sm.buf[3], by the wave that holds it.
-__device__ __forceinline__ void pivot3(Gj3& sm, const dbl4& t, bool& bad) {
+// Pivot tile -> its inverse, in sm.buf[3], by the wave that holds it; n: the
+// block's cells from the tile's first on (eight pivots do for up to eight).
+__device__ __forceinline__ void pivot3(Gj3& sm, const dbl4& t, int n, bool& bad) {
   double a[16];
   tile_put(sm.buf[3], t);
   wave_lds_sync();
   tile_get_rows(sm.buf[3], a);
-  inv16<true>(a, bad);
+  inv16<true>(a, bad, n);
   wave_lds_sync();
   tile_put_rows(sm.buf[3], a);
 }
@@ -146,9 +147,12 @@ __device__ __forceinline__ void publish3(Gj3& sm, const dbl4 T[NW]) {
 // six seeds 5.92 -> 4.84 ms, 18 seeds (4,480 boxes) 2.00 -> 1.46 ms, the
 // particular problems of 4 x 4 x 4 cells 0.37 -> 0.25 ms.
 template <int NW, int P>
-__device__ __forceinline__ void sweep3_step(int np, Gj3& sm, dbl4 T[NW], bool& bad) {
+__device__ __forceinline__ void sweep3_step(int nb, Gj3& sm, dbl4 T[NW], bool& bad) {
   if constexpr (P < NW) {
-    if (P < np) {
+    if (16 * P < nb) {
+      const bool more = 16 * (P + 1) < nb;
+      // pivots of the step: eight or fewer take half the instructions
+      const int nk = P + 1 < NW ? 16 : nb - 16 * P;
       const dbl4 zero = {0.0, 0.0, 0.0, 0.0};
       const int wv = wave3();
       const dbl4 qa = tile_get_t(sm.buf[3]), qb = tile_get(sm.buf[3]);
@@ -156,7 +160,7 @@ __device__ __forceinline__ void sweep3_step(int np, Gj3& sm, dbl4 T[NW], bool& b
         lsync<NW>();
 #pragma unroll
         for (int w = 0; w < NW; ++w)
-          if (w != P) T[w] = mfma16(qa, T[w], zero);
+          if (w != P) T[w] = mfma16(qa, T[w], zero, nk);
         T[P] = -qb;
       } else {
         dbl4 rv, r[NW];
@@ -170,21 +174,21 @@ __device__ __forceinline__ void sweep3_step(int np, Gj3& sm, dbl4 T[NW], bool& b
             for (int c = 0; c < 4; ++c) r[w][c] = sm.buf[w < P ? w : w - 1][64 * c + lane3()];
           }
         lsync<NW>();
-        const dbl4 u = -mfma16(qa, rv, zero);
+        const dbl4 u = -mfma16(qa, rv, zero, nk);
         if constexpr (P + 1 < NW) T[P + 1] = mfma16(u, r[P + 1], T[P + 1]);
-        T[P] = mfma16(rv, qb, zero);
+        T[P] = mfma16(rv, qb, zero, nk);
         if constexpr (P + 1 < NW) {
-          if (wv == P + 1 && P + 1 < np) pivot3(sm, T[P + 1], bad);
+          if (wv == P + 1 && more) pivot3(sm, T[P + 1], nb - 16 * (P + 1), bad);
         }
 #pragma unroll
         for (int w = 0; w < NW; ++w)
-          if (w != P && w != P + 1) T[w] = mfma16(u, r[w], T[w]);
+          if (w != P && w != P + 1) T[w] = mfma16(u, r[w], T[w], nk);
         if constexpr (P + 1 < NW) {
-          if (wv == P + 1 && P + 1 < np) publish3<NW, P + 1>(sm, T);
+          if (wv == P + 1 && more) publish3<NW, P + 1>(sm, T);
         }
       }
       lsync<NW>();
-      sweep3_step<NW, P + 1>(np, sm, T, bad);
+      sweep3_step<NW, P + 1>(nb, sm, T, bad);
     }
   }
 }
@@ -193,11 +197,11 @@ template <int NW>
 __device__ __forceinline__ void sweep3(int nb, Gj3& sm, dbl4 T[NW]) {
   bool bad = false;
   if (wave3() == 0) {
-    pivot3(sm, T[0], bad);
+    pivot3(sm, T[0], nb, bad);
     publish3<NW, 0>(sm, T);
   }
   lsync<NW>();
-  sweep3_step<NW, 0>((nb + 15) / 16, sm, T, bad);
+  sweep3_step<NW, 0>(nb, sm, T, bad);
   if (bad) atomicOr(&sm.flag, kFlagNotPD);
 }
 
@@ -237,11 +241,44 @@ __device__ __forceinline__ void store_tiles3(double* Wj, int nb, int w, const db
   }
 }
 
+// v summed over the four 16-lane rows of the wave, in every lane.
+__device__ __forceinline__ double rows_sum3(double v) {
+  {
+    const auto a = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = __hiloint2double(b[0], a[0]) + __hiloint2double(b[1], a[1]);
+  }
+  const auto a = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(b[0], a[0]) + __hiloint2double(b[1], a[1]);
+}
+
 // X_j (+)= W_j Z for the nrhs vectors staged in s.Z (entry i of vector k at
-// Z[nrhs i + k]), 16 right-hand sides per pass of matrix instructions.
-template <int NW, bool ACC>
+// Z[nrhs i + k]), 16 right-hand sides per pass of matrix instructions.  ONE:
+// a single vector, by dot products on the vector unit (16 multiply-adds of 4
+// cycles per lane against 16 matrix instructions of 64; particular problems
+// of 3072 boxes of 7 x 7 x 4 cells 430 -> 376 us).
+template <int NW, bool ACC, bool ONE>
 __device__ __forceinline__ void apply3(const Box3& s, int nb, int j, int nrhs, const dbl4 wa[NW]) {
   const int lc = lane3() & 15, lg = lane3() >> 4;
+  if constexpr (ONE) {
+    double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+#pragma unroll
+      for (int c = 0; c < 4; c += 2) {
+        a0 = fma(wa[w][c], s.Z[16 * w + 4 * c + lg], a0);
+        a1 = fma(wa[w][c + 1], s.Z[16 * w + 4 * c + 4 + lg], a1);
+      }
+    const double y = rows_sum3(a0 + a1);
+    const int i = 16 * wave3() + lc;
+    if (lg == 0 && i < nb) {
+      double* x = s.X + j * nb + i;
+      *x = ACC ? *x + y : y;
+    }
+    lsync<NW>();
+    return;
+  }
   for (int k0 = 0; k0 < nrhs; k0 += 16) {
     const int k = k0 + lc, kk = min(k, nrhs - 1);
     dbl4 acc = {0.0, 0.0, 0.0, 0.0};
@@ -267,7 +304,7 @@ __device__ __forceinline__ void apply3(const Box3& s, int nb, int j, int nrhs, c
 }
 
 // Forward step of block j for all right-hand sides.
-template <int NW>
+template <int NW, bool ONE>
 __device__ __forceinline__ void fwd_tiles3(const Box3& s, int nb, int j, int nrhs, const dbl4 wa[NW]) {
   for (int e = threadIdx.x; e < nrhs * 16 * NW; e += 64 * NW) {
     const int k = e / (16 * NW), i = e % (16 * NW);
@@ -279,18 +316,18 @@ __device__ __forceinline__ void fwd_tiles3(const Box3& s, int nb, int j, int nrh
     s.Z[i * nrhs + k] = v;
   }
   lsync<NW>();
-  apply3<NW, false>(s, nb, j, nrhs, wa);
+  apply3<NW, false, ONE>(s, nb, j, nrhs, wa);
 }
 
 // Backward step of block j: x_j += W_j (t_j .* x_{j+1}).
-template <int NW>
+template <int NW, bool ONE>
 __device__ __forceinline__ void bwd_tiles3(const Box3& s, int nb, int j, int nrhs, const dbl4 wa[NW]) {
   for (int e = threadIdx.x; e < nrhs * 16 * NW; e += 64 * NW) {
     const int k = e / (16 * NW), i = e % (16 * NW);
     s.Z[i * nrhs + k] = i < nb ? s.Tz[j * nb + i] * s.X[k * s.nc + (j + 1) * nb + i] : 0.0;
   }
   lsync<NW>();
-  apply3<NW, true>(s, nb, j, nrhs, wa);
+  apply3<NW, true, ONE>(s, nb, j, nrhs, wa);
 }
 
 // The lane's share of y = W z for the staged vector z (64 values in LDS):
@@ -387,8 +424,8 @@ __device__ __forceinline__ void load3(const double* Wj, int nb, double w[R3]) {
 }
 
 // Factor of the box fused with the forward sweep of nrhs right-hand sides
-// already in X; inverses to Wg.
-template <int NW>
+// already in X (ONE: one); inverses to Wg.
+template <int NW, bool ONE>
 __device__ __forceinline__ void factor3(const Geo& g, const Box& B, const Box3& s, double* Wg, int nrhs,
                                         Gj3& sm) {
   const int nb = s.m0 * s.m1;
@@ -403,14 +440,14 @@ __device__ __forceinline__ void factor3(const Geo& g, const Box& B, const Box3& 
     if (nrhs > 0) {
       dbl4 wa[NW];
       operand3<NW>(sm, T, wa);
-      fwd_tiles3<NW>(s, nb, j, nrhs, wa);
+      fwd_tiles3<NW, ONE>(s, nb, j, nrhs, wa);
     }
   }
 }
 
 // Back substitution; the next plane's inverse is loaded while the current
 // one is applied.
-template <int NW>
+template <int NW, bool ONE>
 __device__ __forceinline__ void backward3(const Box3& s, const double* Wg, int nrhs) {
   const int nb = s.m0 * s.m1;
   // the stored inverses are read back by other lanes than wrote them
@@ -423,10 +460,10 @@ __device__ __forceinline__ void backward3(const Box3& s, const double* Wg, int n
   if (j >= 0) load_operand3<NW>(Wg + j * bs, nb, w0);
   for (; j >= 0; j -= 2) {
     if (j > 0) load_operand3<NW>(Wg + (j - 1) * bs, nb, w1);
-    bwd_tiles3<NW>(s, nb, j, nrhs, w0);
+    bwd_tiles3<NW, ONE>(s, nb, j, nrhs, w0);
     if (j > 0) {
       if (j > 1) load_operand3<NW>(Wg + (j - 2) * bs, nb, w0);
-      bwd_tiles3<NW>(s, nb, j - 1, nrhs, w1);
+      bwd_tiles3<NW, ONE>(s, nb, j - 1, nrhs, w1);
     }
   }
 }
@@ -448,9 +485,9 @@ __device__ __forceinline__ void basis3(const Geo& g, const Box& B, const Seed* _
   seed_rhs3<NW>(g, B, s, seeds, beta, nrhs, s.X);
   bsync<NW>();
   double* Wg = fac + B.fac;
-  factor3<NW>(g, B, s, Wg, nrhs, sm);
+  factor3<NW, false>(g, B, s, Wg, nrhs, sm);
   if (FO) return;
-  backward3<NW>(s, Wg, nrhs);
+  backward3<NW, false>(s, Wg, nrhs);
   basis_out3<NW>(g, B, s, seeds, beta, nrhs, Pk, tr_u, tr_phi, tr_beta);
 }
 
@@ -470,8 +507,8 @@ __device__ __forceinline__ void particular3(const Geo& g, const Box& B,
   physical3<NW>(g, B, s, f, bcv, s.X);
   bsync<NW>();
   double* Wg = fac + B.fac;
-  factor3<NW>(g, B, s, Wg, 1, sm);
-  backward3<NW>(s, Wg, 1);
+  factor3<NW, true>(g, B, s, Wg, 1, sm);
+  backward3<NW, true>(s, Wg, 1);
   part_out3<NW>(g, B, s, beta, pbar, ubar, pibar);
 }
 
@@ -574,23 +611,29 @@ size_t box3_lds_bytes(int m0, int m1, int m2, int nrhs, int kc) {
 }
 
 int box3_waves(int nb) { return nb <= R3 ? 1 : nb <= 2 * R3 ? 2 : 4; }
+int box3_tile_waves(int nb) { return (nb + 15) / 16; }
 
-// waves per box, and the scalar or the tensor form of K
-#define MRCM_NW_SWITCH(nw, CALL)                   \
-  if (g.kc > 1) {                                  \
-    switch (nw) {                                  \
-      case 1: CALL(1, true); break;                \
-      case 2: CALL(2, true); break;                \
-      case 4: CALL(4, true); break;                \
-      default: return hipErrorInvalidValue;        \
-    }                                              \
-  } else {                                         \
-    switch (nw) {                                  \
-      case 1: CALL(1, false); break;               \
-      case 2: CALL(2, false); break;               \
-      case 4: CALL(4, false); break;               \
-      default: return hipErrorInvalidValue;        \
-    }                                              \
+// waves per box (F3: three among them), and the scalar or the tensor form
+// of K
+#define MRCM_NW_CASES(nw, CALL, TS, F3)    \
+  switch (nw) {                            \
+    case 1: CALL(1, TS); break;            \
+    case 2: CALL(2, TS); break;            \
+    F3                                     \
+    case 4: CALL(4, TS); break;            \
+    default: return hipErrorInvalidValue;  \
+  }
+#define MRCM_NW_SWITCH(nw, CALL)           \
+  if (g.kc > 1) {                          \
+    MRCM_NW_CASES(nw, CALL, true, )        \
+  } else {                                 \
+    MRCM_NW_CASES(nw, CALL, false, )       \
+  }
+#define MRCM_TILE_SWITCH(nw, CALL)                                   \
+  if (g.kc > 1) {                                                    \
+    MRCM_NW_CASES(nw, CALL, true, case 3: CALL(3, true); break;)     \
+  } else {                                                           \
+    MRCM_NW_CASES(nw, CALL, false, case 3: CALL(3, false); break;)   \
   }
 
 hipError_t launch_basis3(const Geo& g, const Box* boxes, int nbox, const Seed* seeds,
@@ -604,7 +647,7 @@ hipError_t launch_basis3(const Geo& g, const Box* boxes, int nbox, const Seed* s
   if (e != hipSuccess) return e;                                                                      \
   hipLaunchKernelGGL((k_basis3<NW, TS>), dim3(nbox), dim3(64 * NW), lds, s, g, boxes, seeds, logK, beta, fac, \
                      Pk, tr_u, tr_phi, tr_beta, factor_only, flags)
-  MRCM_NW_SWITCH(nw, MRCM_CALL)
+  MRCM_TILE_SWITCH(nw, MRCM_CALL)
 #undef MRCM_CALL
   return hipGetLastError();
 }
@@ -620,7 +663,7 @@ hipError_t launch_particular3(const Geo& g, const Box* boxes, int nbox, const do
   if (e != hipSuccess) return e;                                                                     \
   hipLaunchKernelGGL((k_particular3<NW, TS>), dim3(nbox), dim3(64 * NW), lds, s, g, boxes, logK, K, f, bcv, \
                      beta, fac, pbar, ubar, pibar, flags)
-  MRCM_NW_SWITCH(nw, MRCM_CALL)
+  MRCM_TILE_SWITCH(nw, MRCM_CALL)
 #undef MRCM_CALL
   return hipGetLastError();
 }
@@ -640,6 +683,8 @@ hipError_t launch_smooth3(const Geo& g, const Box* boxes, int nmem, const double
   return hipGetLastError();
 }
 
+#undef MRCM_TILE_SWITCH
 #undef MRCM_NW_SWITCH
+#undef MRCM_NW_CASES
 
 }  // namespace mrcm

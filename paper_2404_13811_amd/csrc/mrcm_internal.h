@@ -206,9 +206,14 @@ hipError_t launch_smooth_grid(const Geo& g, const Box* boxes, const SmoothPhases
 
 // one-wavefront-per-box 3-D kernels (local3.hip), plane blocks of <= 64 cells
 size_t box3_lds_bytes(int m0, int m1, int m2, int nrhs, int kc);
-// wavefronts per box for plane blocks of nb cells (1, 2 or 4)
+// wavefronts per box for plane blocks of nb cells (1, 2 or 4), and for the
+// FP64 factors, which work on 16 x 16 tiles (1 to 4: planes of 33 to 48 cells
+// would pay for 64 with four waves; 3072 boxes of 6 x 6 x 6 cells, all of
+// Steps 1-2 and 4, 590 -> 463 us)
 int box3_waves(int nb);
-// Steps 1-2 (factor_only: Step 6) on oversampled boxes; reads log K
+int box3_tile_waves(int nb);
+// Steps 1-2 (factor_only: Step 6) on oversampled boxes; reads log K; nw, here
+// and in launch_particular3: box3_tile_waves
 hipError_t launch_basis3(const Geo& g, const Box* boxes, int nbox, const Seed* seeds,
                          const double* logK, double beta, double* fac, double* Pk, double* tr_u,
                          double* tr_phi, double* tr_beta, int factor_only, int* flags, size_t lds,
