@@ -235,7 +235,7 @@ __device__ __forceinline__ void box_solve(const Box& B, const double* Wf, const 
                                           const BoxLds& s) {
   double w[RING][HB], zm[HB];
   wload_block(block_src(Wt, B.nb, B.nblk), B.nblk / 2, zm);
-  sweep_twisted<64>(B, Wf, Wt, s, w, zm);
+  sweep_twisted<64>(B, Wf, Wt, s, s.Z, w, zm);
 }
 
 // One colour phase in reverse.  p_in / gf_in: the state before the phase.

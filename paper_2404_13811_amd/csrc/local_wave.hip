@@ -393,7 +393,7 @@ __device__ __forceinline__ void smooth_box(const Geo& g, const Box& B, const dou
   bsync<NT>();
   smooth_rhs<NT>(g, B, r, beta, r.b.X);
   bsync<NT>();
-  sweep_twisted<NT>(B, Wf, Wt, r.b, w, zm);
+  sweep_twisted<NT>(B, Wf, Wt, r.b, r.b.Z, w, zm);
   smooth_out<NT>(g, B, r, r.b.X, beta, p, gflux);
 }
 

@@ -1112,29 +1112,30 @@ __device__ __forceinline__ void twist_preload(const TwistHalf& hf, double w[RING
 
 // Forward half (ring preloaded); z_j replaces b_j in s.X.
 __device__ __forceinline__ void twist_fwd(const Box& B, const TwistHalf& hf, const BoxLds& s,
-                                          bool bottom, double w[RING][HB]) {
+                                          double* z, bool bottom, double w[RING][HB]) {
   const int L = lane_id();
-  const int c = L & 31, h = L >> 5, zi = HB * h + (L & 15);
+  const int c = L & 31, h = L >> 5;
   const int nb = B.nb;
-  const bool cv = c < nb, zv = zi < nb;
+  const bool cv = c < nb;
   const int cnt = hf.cnt;
   if (cnt <= 0) return;
-  double yz = 0.0, tp = 0.0;
-  double xn = zv ? s.X[hf.j0 * nb + zi] : 0.0;
+  double y = 0.0, tp = 0.0;
+  double xn = cv ? s.X[hf.j0 * nb + c] : 0.0;
   for (int v0 = 0; v0 < cnt + hf.o; v0 += RING) {
 #pragma unroll
     for (int q = 0; q < RING; ++q) {
       const int t = v0 + q - hf.o;
       if (t >= 0 && t < cnt) {
         const int j = hf.j0 + hf.dj * t;
-        const double z = fma(tp, yz, xn);
+        double* zb = z + (t & 1) * NBW;
+        if (h == 0) zb[c] = cv ? fma(tp, y, xn) : 0.0;
+        __builtin_amdgcn_wave_barrier();
         const bool more = t + 1 < cnt;
         const int jn = j + hf.dj;             // next block of this half
         const int ti = bottom ? jn : j;       // coupling between j and jn
-        xn = (more && zv) ? s.X[jn * nb + zi] : 0.0;
-        tp = (more && zv) ? s.Tn[ti * nb + zi] : 0.0;
-        const double y = wgemv_rows(w[q], z);
-        yz = to_rows(y);
+        xn = (more && cv) ? s.X[jn * nb + c] : 0.0;
+        tp = (more && cv) ? s.Tn[ti * nb + c] : 0.0;
+        y = wgemv2(w[q], zb);
         if (h == 0 && cv) s.X[j * nb + c] = y;
         if (t + RING < cnt) wload_block(hf.src, hf.j0 + hf.dj * (t + RING), w[q]);
       }
@@ -1144,29 +1145,33 @@ __device__ __forceinline__ void twist_fwd(const Box& B, const TwistHalf& hf, con
 
 // Meeting block: x_m from b_m and the neighbouring z of both halves; zm
 // holds Z_m in the block register layout.
-__device__ __forceinline__ void twist_mid(const Box& B, const double zm[HB], const BoxLds& s, int m) {
+__device__ __forceinline__ void twist_mid(const Box& B, const double zm[HB], const BoxLds& s,
+                                          double* z, int m) {
   const int L = lane_id();
-  const int c = L & 31, h = L >> 5, zi = HB * h + (L & 15);
+  const int c = L & 31, h = L >> 5;
   const int nb = B.nb, nblk = B.nblk;
+  const bool cv = c < nb;
   double v = 0.0;
-  if (zi < nb) {
-    v = s.X[m * nb + zi];
-    if (m > 0) v = fma(s.Tn[(m - 1) * nb + zi], s.X[(m - 1) * nb + zi], v);
-    if (m + 1 < nblk) v = fma(s.Tn[m * nb + zi], s.X[(m + 1) * nb + zi], v);
+  if (cv) {
+    v = s.X[m * nb + c];
+    if (m > 0) v = fma(s.Tn[(m - 1) * nb + c], s.X[(m - 1) * nb + c], v);
+    if (m + 1 < nblk) v = fma(s.Tn[m * nb + c], s.X[(m + 1) * nb + c], v);
   }
-  const double y = wgemv_rows(zm, v);
-  if (h == 0 && c < nb) s.X[m * nb + c] = y;
+  if (h == 0) z[c] = v;
+  __builtin_amdgcn_wave_barrier();
+  const double y = wgemv2(zm, z);
+  if (h == 0 && cv) s.X[m * nb + c] = y;
 }
 
 // Back-substitution half, outwards from the meeting block.  With
 // have_ring the ring is the one the forward pass of this half left behind.
-__device__ __forceinline__ void twist_back(const Box& B, const TwistHalf& hf, const BoxLds& s, int m,
-                                           bool bottom, bool have_ring, double w[RING][HB]) {
+__device__ __forceinline__ void twist_back(const Box& B, const TwistHalf& hf, const BoxLds& s,
+                                           double* z, int m, bool bottom, bool have_ring,
+                                           double w[RING][HB]) {
   const int L = lane_id();
-  const int h = L >> 5, zi = HB * h + (L & 15);
+  const int c = L & 31, h = L >> 5;
   const int nb = B.nb;
-  const bool zv = zi < nb;
-  const bool own = zv && !(L & 16);  // one lane per index
+  const bool cv = c < nb;
   const int cnt = hf.cnt;
   if (cnt <= 0) return;
   if (!have_ring) {
@@ -1177,9 +1182,9 @@ __device__ __forceinline__ void twist_back(const Box& B, const TwistHalf& hf, co
     }
   }
   const int jf = hf.j0 + hf.dj * (cnt - 1);  // first block of the back pass (next to m)
-  double xnext = zv ? s.X[m * nb + zi] : 0.0;
-  double tj = zv ? s.Tn[(bottom ? jf - 1 : jf) * nb + zi] : 0.0;
-  double wj = zv ? s.X[jf * nb + zi] : 0.0;
+  double xnext = cv ? s.X[m * nb + c] : 0.0;
+  double tj = cv ? s.Tn[(bottom ? jf - 1 : jf) * nb + c] : 0.0;
+  double wj = cv ? s.X[jf * nb + c] : 0.0;
   for (int v0 = 0; v0 < cnt; v0 += RING) {
 #pragma unroll
     for (int q = 0; q < RING; ++q) {
@@ -1187,14 +1192,16 @@ __device__ __forceinline__ void twist_back(const Box& B, const TwistHalf& hf, co
       if (t < cnt) {
         const int b = cnt - 1 - t;
         const int j = hf.j0 + hf.dj * b;
-        const double z = tj * xnext;
+        double* zb = z + (t & 1) * NBW;
+        if (h == 0) zb[c] = cv ? tj * xnext : 0.0;
+        __builtin_amdgcn_wave_barrier();
         const double wcur = wj;
         const bool more = t + 1 < cnt;
         const int jn = j - hf.dj;             // next block, away from m
-        tj = (more && zv) ? s.Tn[(bottom ? jn - 1 : jn) * nb + zi] : 0.0;
-        wj = (more && zv) ? s.X[jn * nb + zi] : 0.0;
-        xnext = wcur + to_rows(wgemv_rows(w[RING - 1 - q], z));
-        if (own) s.X[j * nb + zi] = xnext;
+        tj = (more && cv) ? s.Tn[(bottom ? jn - 1 : jn) * nb + c] : 0.0;
+        wj = (more && cv) ? s.X[jn * nb + c] : 0.0;
+        xnext = wcur + wgemv2(w[RING - 1 - q], zb);
+        if (h == 0 && cv) s.X[j * nb + c] = xnext;
         if (b - RING >= 0) wload_block(hf.src, hf.j0 + hf.dj * (b - RING), w[RING - 1 - q]);
       }
     }
@@ -1208,35 +1215,37 @@ __device__ __forceinline__ void twist_back(const Box& B, const TwistHalf& hf, co
 // block (zm), before staging, so that their memory latency is hidden.  With
 // NT = 64 one wave runs the halves one after the other and loads as it
 // goes.  The arithmetic is the same in both cases, and so is the result.
-// Wf: forward inverses, Wt: backward inverses and Z_m.
+// Wf: forward inverses, Wt: backward inverses and Z_m; z: 4 x NBW doubles.
 template <int NT>
 __device__ __forceinline__ void sweep_twisted(const Box& B, const double* Wf, const double* Wt,
-                                              const BoxLds& s, double w[RING][HB],
+                                              const BoxLds& s, double* z, double w[RING][HB],
                                               const double zm[HB]) {
   const int wv = threadIdx.x >> 6;
   const int m = B.nblk / 2;
+  double* za = z;
+  double* zb = z + 2 * NBW;
   const TwistHalf top = twist_half(B, Wf, m, false);
   const TwistHalf bot = twist_half(B, Wt, m, true);
   if (NT == 64) {
     twist_preload(top, w);
-    twist_fwd(B, top, s, false, w);
+    twist_fwd(B, top, s, za, false, w);
     twist_preload(bot, w);
-    twist_fwd(B, bot, s, true, w);
+    twist_fwd(B, bot, s, zb, true, w);
   } else if (wv == 0) {
-    twist_fwd(B, top, s, false, w);
+    twist_fwd(B, top, s, za, false, w);
   } else if (wv == 1) {
-    twist_fwd(B, bot, s, true, w);
+    twist_fwd(B, bot, s, zb, true, w);
   }
   bsync<NT>();
-  if (wv == 0) twist_mid(B, zm, s, m);
+  if (wv == 0) twist_mid(B, zm, s, za, m);
   bsync<NT>();
   if (NT == 64) {
-    twist_back(B, top, s, m, false, false, w);
-    twist_back(B, bot, s, m, true, false, w);
+    twist_back(B, top, s, za, m, false, false, w);
+    twist_back(B, bot, s, zb, m, true, false, w);
   } else if (wv == 0) {
-    twist_back(B, top, s, m, false, true, w);
+    twist_back(B, top, s, za, m, false, true, w);
   } else if (wv == 1) {
-    twist_back(B, bot, s, m, true, true, w);
+    twist_back(B, bot, s, zb, m, true, true, w);
   }
   bsync<NT>();
 }
