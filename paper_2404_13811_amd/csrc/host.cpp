@@ -1462,11 +1462,9 @@ mrcm_status tune_smoothing(mrcm_ctx* c, hipStream_t s) {
   HIPCHK(c, hipEventRecord(c->ev[10], s));
   float best = 0.f;
   int best_nt = 256, best_var = 8;
-  // with resident factors one wave per box is never the fastest (1024 boxes
-  // of 24 x 24 cells: 38 us per phase against 27 and 29)
-  const std::vector<int> cand = f3 ? std::vector<int>{8, 4, 2, 0}
-                                : c->prec == MRCM_FP64 && c->lds_smooth_res ? std::vector<int>{256, 128}
-                                                                            : std::vector<int>{64, 128, 256};
+  // (each is the fastest somewhere, with resident factors: 1024 boxes of 24
+  // x 24 cells 38, 29 and 27 us per phase, 1024 of 3 x 3 5.9, 6.1 and 6.6)
+  const std::vector<int> cand = f3 ? std::vector<int>{8, 4, 2, 0} : std::vector<int>{64, 128, 256};
   for (int v : cand) {
     const int nt = f3 ? 256 : v;
     if (f3) c->smooth_cached = v;
