@@ -1201,6 +1201,7 @@ mrcm_status mrcm_set_precision(mrcm_ctx* c, mrcm_precision prec, double tol, int
   if (prec != MRCM_FP64 && prec != MRCM_FP32_REFINE) return fail(c, MRCM_EINVAL, "bad precision");
   if (prec == MRCM_FP32_REFINE && (!(tol > 0.0) || max_refine < 0))
     return fail(c, MRCM_EINVAL, "refinement needs tol > 0 and max_refine >= 0");
+  if (prec != c->prec) c->smooth_nt = 0;  // each form has its own fastest variant
   c->prec = prec;
   c->tol = tol;
   c->max_refine = max_refine;
