@@ -94,9 +94,9 @@ struct mrcm_ctx {
   size_t lds_basis = 0, lds_part = 0, lds_smooth = 0;
   // 2-D smoothing with the factors of a box resident in LDS: its LDS bytes
   // (0: some box does not fit, the factors are streamed) and what it keeps
-  // per box
+  // per box (FP64 contexts only)
   size_t lds_smooth_res = 0;
-  SmoothArrays sarr{nullptr, nullptr, nullptr, 0};
+  SmoothArrays sarr{nullptr, nullptr, nullptr, 0, 0};
   size_t lds32_basis = 0, lds32_part = 0, lds32_smooth = 0;
   int form32 = 0;  // their kernel class (wave32_form of the largest box)
   int nrhs32 = 1;  // most seeds of a box
@@ -215,6 +215,13 @@ template <typename T>
 void dfree(T*& p) {
   if (p) (void)hipFree(p);
   p = nullptr;
+}
+
+// count elements where nothing is allocated yet
+template <typename T>
+hipError_t grow(T*& p, long long count) {
+  if (p) return hipSuccess;
+  return hipMalloc((void**)&p, std::max<long long>(count, 1) * sizeof(T));
 }
 
 void drop_graph(mrcm_ctx* c);
@@ -708,13 +715,16 @@ mrcm_status make_plan(mrcm_ctx* c) {
   if (c->lds_basis > 150 * 1024 || c->lds_smooth > 150 * 1024 || 2 * c->lds_part + 16 > 150 * 1024)
     c->wave = false;
   if (!c->wave || c->lds_smooth_res > 150 * 1024) c->lds_smooth_res = 0;
-  int nb32 = 1, nblk32 = 1;
+  int nb32 = 1, nblk32 = 1, ncell = 1;
   c->nrhs32 = 1;
   for (const Box& B : c->obox) {
     c->nrhs32 = std::max(c->nrhs32, B.nrhs);
     nb32 = std::max(nb32, B.nb);
     nblk32 = std::max(nblk32, B.nblk);
+    ncell = std::max(ncell, B.ncell);
   }
+  c->sarr.bstride = (ncell + 1) / 2 * 2;
+  c->sarr.fstride = 4 * (c->S[0] + c->S[1] + 4 * c->l);
   c->form32 = wave32_form(nb32, nblk32);
   // 3-D boxes: one wave per box with plane blocks of at most 64 cells
   c->d3 = c->d == 3;
@@ -825,12 +835,6 @@ mrcm_status make_plan(mrcm_ctx* c) {
   ALLOC(c->facp, c->facp_n);
   ALLOC(c->scr, c->scr_n);
   ALLOC(c->tco, c->scro_n);
-  if (c->lds_smooth_res) {
-    c->sarr.fstride = 4 * (g.S[0] + g.S[1] + 4 * c->l);
-    ALLOC(c->sarr.b0, c->scro_n);
-    ALLOC(c->sarr.fc, (long long)nsub * c->sarr.fstride);
-    ALLOC(c->sarr.gc, (long long)nsub * g.gstride);
-  }
   ALLOC(c->tcp, c->scrp_n);
   ALLOC(c->fac32, c->fac_n);
   ALLOC(c->facp32, c->facp_n);
@@ -1260,6 +1264,11 @@ mrcm_status mrcm_build_basis(mrcm_ctx* c) {
                                c->form32, c->nrhs32, std::max(c->lds32_basis, c->lds32_part), s));
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[9], s));
   } else if (c->wave) {
+    if (c->lds_smooth_res) {
+      HIPCHK(c, grow(c->sarr.b0, (long long)c->geo.nsub * c->sarr.bstride));
+      HIPCHK(c, grow(c->sarr.fc, (long long)c->geo.nsub * c->sarr.fstride));
+      HIPCHK(c, grow(c->sarr.gc, (long long)c->geo.nsub * c->geo.gstride));
+    }
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[8], s));
     HIPCHK(c, launch_local_w(c->geo, c->d_obox, c->d_pbox, c->geo.nsub, c->d_seeds, c->logk, c->K, c->f,
                              c->bcv, c->beta_mbf, c->fac, c->tco, c->facp, c->tcp, c->Pk, c->tr_u,
@@ -1285,10 +1294,6 @@ mrcm_status mrcm_build_basis(mrcm_ctx* c) {
   if (c->beta_sm != c->beta_mbf) {
     // Step 6: the smoothing Robin parameter differs, so the oversampled
     // boxes are factored once more with it
-    auto grow = [&](auto*& ptr, long long count) -> hipError_t {
-      if (ptr) return hipSuccess;
-      return hipMalloc((void**)&ptr, std::max<long long>(count, 1) * sizeof(*ptr));
-    };
     if (r32 && c->d3) {
       HIPCHK(c, grow(c->fac32s, c->fac_n));
       HIPCHK(c, launch_basis3f(c->geo, c->d_obox, c->geo.nsub, c->d_seeds, c->logk, c->beta_sm, c->fac32s,
