@@ -37,9 +37,6 @@ namespace {
 
 using namespace wave;
 
-
-
-
 // Store the nb x nb block held in the register layout w to Wj.
 __device__ __forceinline__ void store_block(int nb, double* Wj, const double w[HB]) {
   // lower triangle, row-major (the layout block_src reads); entries outside
@@ -58,7 +55,7 @@ __device__ __forceinline__ void store_block(int nb, double* Wj, const double w[H
 
 // Block j of the cached FP64 factors of a box
 __device__ __forceinline__ double* fblock(double* Wg, int nb, int j) {
-  return Wg + (long long)j * block_elems<double>(nb);
+  return Wg + (long long)j * packed_elems(nb);
 }
 
 // Factorisation fused with the forward sweep; inverses to Wg, couplings to Tg.

@@ -75,8 +75,6 @@ __device__ __forceinline__ void bsync() {
   else __syncthreads();
 }
 
-__device__ __forceinline__ double half_swap(double v) { return __shfl_xor(v, 32); }
-
 // v(lane c) + v(lane c + 32) in every lane of column c, by two half-wave
 // swaps of the 32-bit words (no LDS); both halves add in the same order.
 __device__ __forceinline__ double half_sum(double v) {
@@ -95,22 +93,14 @@ __device__ __forceinline__ float half_sum_f(float v) {
 // Cached block inverses of one box read through a buffer resource: per lane
 // the byte offsets of its 16 entries (row 16h + i, column c) within a block,
 // and the buffer size for the padding entries, which the range check turns
-// into zeros; the block index goes into the scalar offset.  FP64 blocks are
+// into zeros; the block index goes into the scalar offset.  The blocks are
 // the inverses of symmetric Schur complements and are stored as their lower
 // triangle, row-major (entry (r, c), r >= c, at r (r + 1) / 2 + c; both
 // (r, c) and (c, r) read it): half the bytes of a full block, padded to an
-// even number so that every block starts at a 16-byte boundary.  FP32 blocks
-// are stored whole (nb x nb row-major).
-template <typename T>
-__host__ __device__ constexpr bool packed_blocks() { return sizeof(T) == 8; }
-
+// even number so that every block starts at a 16-byte boundary.  (The FP32
+// form's blocks are stored whole, see Lane32.)
 __host__ __device__ inline int packed_elems(int nb) { return (nb * (nb + 1) / 2 + 1) / 2 * 2; }
 
-template <typename T>
-__host__ __device__ inline int block_elems(int nb) {
-  return packed_blocks<T>() ? packed_elems(nb) : nb * nb;
-}
-template <typename T>
 struct BlockSrc {
   __amdgpu_buffer_rsrc_t rs;
   int off[HB];
@@ -128,35 +118,26 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_buffer(const void* p, 
                                            __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
 }
 
-template <typename T>
-__device__ __forceinline__ BlockSrc<T> block_src(const T* Wg, int nb, int nblk) {
-  BlockSrc<T> b;
-  const int bsz = block_elems<T>(nb);
-  const int bytes = nblk * bsz * (int)sizeof(T);
+__device__ __forceinline__ BlockSrc block_src(const double* Wg, int nb, int nblk) {
+  BlockSrc b;
+  const int bsz = packed_elems(nb);
+  const int bytes = nblk * bsz * (int)sizeof(double);
   b.rs = uniform_buffer(Wg, bytes);
   const int c = threadIdx.x & 31, h = (threadIdx.x >> 5) & 1;
 #pragma unroll
   for (int i = 0; i < HB; ++i) {
     const int r = HB * h + i;
     const int hi = r > c ? r : c, lo = r > c ? c : r;
-    const int idx = packed_blocks<T>() ? hi * (hi + 1) / 2 + lo : r * nb + c;
-    b.off[i] = (r < nb && c < nb) ? idx * (int)sizeof(T) : bytes;
+    b.off[i] = (r < nb && c < nb) ? (hi * (hi + 1) / 2 + lo) * (int)sizeof(double) : bytes;
   }
-  b.bbytes = __builtin_amdgcn_readfirstlane(bsz * (int)sizeof(T));
+  b.bbytes = __builtin_amdgcn_readfirstlane(bsz * (int)sizeof(double));
   return b;
 }
 
-__device__ __forceinline__ void wload_block(const BlockSrc<double>& b, int j, double w[HB]) {
+__device__ __forceinline__ void wload_block(const BlockSrc& b, int j, double w[HB]) {
 #pragma unroll
   for (int i = 0; i < HB; ++i)
     w[i] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
-        b.rs, b.off[i], __builtin_amdgcn_readfirstlane(j * b.bbytes), 0));
-}
-
-__device__ __forceinline__ void wload_block(const BlockSrc<float>& b, int j, float w[HB]) {
-#pragma unroll
-  for (int i = 0; i < HB; ++i)
-    w[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
         b.rs, b.off[i], __builtin_amdgcn_readfirstlane(j * b.bbytes), 0));
 }
 
@@ -908,8 +889,7 @@ __device__ __forceinline__ void mid_step(int nb, int ncell, int m, int nblk, int
 // X_{j+1}), with the cached inverses streamed from memory, RING blocks ahead.
 __device__ __forceinline__ void backward_cached(const Box& B, const double* Wg, int nrhs, const BoxLds& s) {
   const int nb = B.nb, nblk = B.nblk;
-  const long long bs = (long long)nb * nb;
-  const BlockSrc<double> src = block_src(Wg, nb, nblk);
+  const BlockSrc src = block_src(Wg, nb, nblk);
   double w[RING][HB];
   // block j = nblk - 2 - t uses ring slot t % RING
 #pragma unroll
@@ -939,7 +919,7 @@ __device__ __forceinline__ void twist_fwd_cached(const Box& B, const double* Wg,
   const int cnt = bottom ? nblk - 1 - m : m;
   const int j0 = bottom ? nblk - 1 : 0, dj = bottom ? -1 : 1;
   if (cnt <= 0) return;
-  const BlockSrc<double> src = block_src(Wg, nb, nblk);
+  const BlockSrc src = block_src(Wg, nb, nblk);
   double w[RING][HB];
 #pragma unroll
   for (int q = 0; q < RING; ++q)
@@ -963,7 +943,7 @@ __device__ __forceinline__ void twist_back_cached(const Box& B, const double* Wg
   const int cnt = bottom ? nblk - 1 - m : m;
   const int dj = bottom ? 1 : -1;  // direction away from m
   if (cnt <= 0) return;
-  const BlockSrc<double> src = block_src(Wg, nb, nblk);
+  const BlockSrc src = block_src(Wg, nb, nblk);
   double w[RING][HB];
 #pragma unroll
   for (int q = 0; q < RING; ++q)
@@ -1006,8 +986,7 @@ __device__ __forceinline__ void sweep1(const Box& B, const double* Wg, const Box
   const int c = L & 31, h = L >> 5;
   const int nb = B.nb, nblk = B.nblk;
   const bool cv = c < nb;
-  const long long bs = (long long)nb * nb;
-  const BlockSrc<double> src = block_src(Wg, nb, nblk);
+  const BlockSrc src = block_src(Wg, nb, nblk);
   {
     double w[RING][HB];
 #pragma unroll
@@ -1086,7 +1065,7 @@ __device__ __forceinline__ void sweep1(const Box& B, const double* Wg, const Box
 // in place (slot RING-1-q for its q-th block) and the slot of every block
 // stays a compile-time index.
 struct TwistHalf {
-  BlockSrc<double> src;
+  BlockSrc src;
   int cnt, j0, dj, o;
 };
 
