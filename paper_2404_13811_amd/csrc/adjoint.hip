@@ -229,8 +229,10 @@ __host__ __device__ inline size_t adj_res_off(int m0, int m1) {
 
 // One right-hand side in s.X solved by one wave with the two-ended sweep of
 // the cached factors (forward inverses below the meeting block, backward
-// inverses above it and Z_m): the same arithmetic as the forward smoothing
-// step, so the reverse pass recomputes the forward state exactly.
+// inverses above it and Z_m).  The reverse pass recomputes the forward state
+// to rounding, not bit for bit: the forward phase with resident factors forms
+// its Robin terms from stored coefficients, the reverse one from K, and each
+// side streams or holds the factors by its own LDS need.
 __device__ __forceinline__ void box_solve(const Box& B, const double* Wf, const double* Wt,
                                           const BoxLds& s) {
   double w[RING][HB], zm[HB];
@@ -240,7 +242,9 @@ __device__ __forceinline__ void box_solve(const Box& B, const double* Wf, const 
 
 // One colour phase in reverse.  p_in / gf_in: the state before the phase.
 // F32: the FP32 form (fac, fact and tcoup unused; the FP32 factors and the
-// refinement settings in rf).  RES (FP64): both solves with the box's
+// refinement settings in rf); it streams its inverses in both solves, as the
+// forward kernel's register forms would take the whole register file beside
+// what the reverse phase keeps.  RES (FP64): both solves with the box's
 // factors resident in LDS (lds_sweep, the halves on two waves) instead of
 // streamed by one wave: the form of every box whose LDS fits.  Measured per
 // phase: 64 boxes of 20 x 20 cells 41.6 -> 22.5 us, 2048 boxes 211 ->
@@ -287,8 +291,7 @@ __global__ void __launch_bounds__(kAdjNT) k_adj_smooth(Geo g, const Box* __restr
   const int tid = threadIdx.x;
   if (F32 && tid == 0) flag32 = 0;
   if constexpr (RES) stage_factors<NT>(B, fac + B.fac, fact + B.fac, img);
-  // (a) forward solution of this box from the checkpointed state (the
-  // forward smoothing step's arithmetic)
+  // (a) forward solution of this box from the checkpointed state
   if (F32) {
     stage_smooth<NT>(g, B, r, K, p_in, f, gf_in, bcv, nullptr);
     __syncthreads();
@@ -554,8 +557,9 @@ __global__ void k_adj_moments(Geo g, const Iface* __restrict__ ifc, const Seed* 
 // right-hand sides (Omega_i restriction and Gamma traces u, phi, beta),
 // solve with the cached inverses and accumulate the K terms.  F32: the
 // FP32 form (fac and fact unused).
-// (Registers held to two waves per SIMD: 4096 boxes with four seeds 1050 ->
-// 932 us with the products by row broadcast.)
+// (Registers held to two waves per SIMD, at 34 spilled registers of the FP64
+// form: 4096 boxes with four seeds 1050 -> 932 us with the products by row
+// broadcast.)
 template <bool F32>
 __global__ void __launch_bounds__(64, 2) k_adj_basis(Geo g, const Box* __restrict__ boxes,
                                                   const Seed* __restrict__ seeds,

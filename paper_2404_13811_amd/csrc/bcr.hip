@@ -26,9 +26,9 @@ namespace {
 
 // ------------------------------------------------------------------ inverse
 // In-place Gauss-Jordan inversion of one n x n block (n = 16 NW <= 128) per
-// workgroup of NW waves, 16 pivots per step, no pivoting.  Wave v holds rows 16 v .. 16 v + 15 as NW 16 x 16
-// tiles in the accumulator layout of the FP64 matrix instructions.  Step p,
-// with P the pivot block, R the pivot rows and C a wave's pivot columns:
+// workgroup of NW waves, 16 pivots per step, no pivoting.  Wave v holds rows
+// 16 v .. 16 v + 15 as NW 16 x 16 tiles in the accumulator layout of the FP64
+// matrix instructions.  Step p, with P the pivot block, R the pivot rows and C a wave's pivot columns:
 //   P <- P^{-1},  R <- P^{-1} R,  C <- -C P^{-1},  A <- A - C P^{-1} R.
 // The old pivot rows are in LDS in operand B's layout (the accumulators as
 // they are), P^{-1} in LDS too, so a wave needs only its own pivot-column
@@ -41,9 +41,11 @@ namespace {
 // per step would not stay in the instruction cache.
 //
 // Bound: FP64 matrix instructions of one CU (2 n^3 flop: 14 us for n = 128
-// at 128 flop per cycle) plus, on the SIMD of the wave that looks ahead, the
-// pivot block's inversion, which uses the same FP64 units (8600 cycles per
-// step there, 5000 on the other SIMDs).  Measured per launch, against four
+// at 128 flop per cycle; 32 of 64 cycles per wave and step, two waves per
+// SIMD) plus, on the SIMD of the wave that looks ahead, the pivot block's
+// inversion, which uses the same FP64 units (16 pivots of about 120 cycles),
+// and the LDS round trips before and after it: 9,000 cycles per step
+// measured, of which the other SIMDs work 4,100.  Measured per launch, against four
 // pivots per step on the vector unit with two to one barriers: n = 128
 // 50.5 -> 30.9 us, n = 96 with 66 pivots 30.7 -> 16.5 us, n = 32 7.7 ->
 // 4.2 us.  Matrix instructions interleaved with the inversion's pivots were

@@ -420,10 +420,9 @@ bool bcr_plan(mrcm_ctx* c, std::vector<int>& row_lvl, std::vector<int>& row_loc,
                       const std::vector<int>& s2) {
     const int nb = (int)blk.size();
     if (nb == 0) return;
-    // pivots a block's inverse needs: its layer's size rounded up to the
-    // four pivots of a step (the padding beyond is identity, which a pivot
-    // step leaves unchanged)
-    auto piv = [](int nn) { return nn <= 0 ? 0 : (nn + 3) / 4 * 4; };
+    // pivots a block's inverse needs: its layer's size (the padding beyond is
+    // identity, which the steps of 16 pivots leave unchanged)
+    auto piv = [](int nn) { return std::max(nn, 0); };
     if (bp <= kBcrInvMax) {
       const int o = (int)inv.size();
       for (int b : blk) {

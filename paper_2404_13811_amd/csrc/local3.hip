@@ -540,8 +540,9 @@ __device__ __forceinline__ void smooth3(const Geo& g, const Box& B, const double
   smooth_out3<NW>(g, B, s, p, gflux, beta);
 }
 
-// Register budget for three resident boxes per CU (their LDS allows no
-// more): at most 168 registers per lane.
+// Register budget for three resident boxes of four waves per CU (their LDS
+// allows no more): at most 168 registers per lane, which costs the kernels of
+// four waves 20 to 27 spilled registers and those of three 8 to 12.
 template <int NW, bool TS>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3))) k_basis3(Geo g, const Box* __restrict__ boxes,
                                                     const Seed* __restrict__ seeds,

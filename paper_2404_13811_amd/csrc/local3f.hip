@@ -8,9 +8,9 @@
 // functions on Omega_i), Step 4 (particular problems), Step 6 (factor only)
 // and one colour phase of the smoothing sweep (Steps 6-7).
 //
-// Layout as the FP64 kernels (local3.hip): one workgroup of NW wavefronts
-// per box, lane c of wave v holding rows 16v .. 16v + 15 of column c of the
-// padded 64 x 64 plane block, here in FP32; the block LDL^T recurrence
+// Layout: one workgroup of NW wavefronts per box, lane c of wave v holding
+// rows 16v .. 16v + 15 of column c of the padded 64 x 64 plane block, in FP32
+// (the FP64 kernels hold tiles of 16 x 16); the block LDL^T recurrence
 // S_j = D_j - t_{j-1} W_{j-1} t_{j-1} with W_j = S_j^{-1} formed in place by
 // four-pivot Gauss-Jordan elimination with look-ahead.  The sweeps run on
 // row blocks of the inverses (local3_common.h: one quad-reduced dot
@@ -31,10 +31,11 @@ namespace {
 constexpr int JC = 8;   // plane inverses held in registers (most)
 constexpr int JCB = 2;  // those the basis kernel holds (three boxes per CU)
 
-// Pivot data of one elimination step (two alternating buffers), as Gj3 of
-// the FP64 kernels in FP32; vb and rs (1024 floats) also hold the per-wave
-// partial sums of the block-vector products.  red: the waves' maxima of
-// the backward error.
+// Pivot data of one elimination step in two alternating buffers: vb the four
+// pivot rows multiplied by the pivot block's inverse, rs the pivot columns
+// of every row, pb the pivot block (vb also stages a wave's tile when an
+// inverse is turned into row blocks).  red: the waves' maxima of the backward
+// error.
 struct __align__(16) Gj3f {
   float vb[2][G3 * P3];
   float rs[2][P3 * G3];
@@ -124,8 +125,15 @@ __device__ __forceinline__ void build3f(const Geo& g, const Box& B, const Box3F&
   }
 }
 
-// Four-pivot Gauss-Jordan inverse with look-ahead in FP32: the steps of
-// gj3_pivot / gj3_rows / gj3_step of the FP64 kernels, on floats.
+// Gauss-Jordan inverse of the plane block, four pivots K .. K + 3 per step
+// and one barrier, no pivoting.  gj3f_pivot, by the wave that holds the pivot
+// rows: the pivot block P and the pivot columns (of every row, from the rows
+// by symmetry; the sign that eliminated columns carry taken out) to LDS,
+// v = P^{-1} (row entries) per column, with unit vectors in the columns K.
+// gj3f_rows: rank-4 update of rows R0 .. R1 - 1, A[i][c] -= A[i][K] v[c] (zero
+// base in the columns K).  gj3f_step: the wave that holds the next pivot rows
+// updates those first, factors and publishes them (look-ahead), then its
+// other rows; the owners of rows K take v.
 template <int NW, int K>
 __device__ __forceinline__ void gj3f_pivot(Gj3f& sm, float w[R3], bool& bad) {
   constexpr int RI = K % R3;

@@ -24,8 +24,10 @@
 //
 // Everything a sweep touches between block steps lives in LDS: the box's
 // permeabilities (with a one-cell halo), its diagonal and couplings, and
-// the right-hand sides / solutions.  The cached block inverses are streamed
-// from memory four blocks ahead of their use.
+// the right-hand sides / solutions.  The back-substitution of Steps 1-2 and
+// 4 reads the block inverses from memory four blocks ahead of their use;
+// smoothing copies them into LDS first, except for boxes that do not fit
+// there, which stream them in the same way.
 #include "wave_common.h"
 
 #include <hip/hip_cooperative_groups.h>
@@ -80,9 +82,9 @@ __device__ __forceinline__ void factor_forward(const Box& B, double* Wg, double*
 
 // LDS of a basis box: the box arrays with its right-hand sides, then from
 // BoxLds::Z on the forward Schur complement of the meeting block (nb x nb,
-// nb = m0, row-major).  The size decides which boxes the wave kernels take
-// and counts two vectors of NBW per right-hand side besides, as it always
-// has.
+// nb = m0, row-major).  The size decides which boxes the wave kernels take;
+// it counts two vectors of NBW per right-hand side that only products staged
+// through LDS need, so that the set of those boxes stays what it was.
 __host__ __device__ inline size_t basis_lds_doubles(int m0, int m1, int nrhs, int kc = 1) {
   return box_lds_doubles(m0, m1, nrhs, kc) + (size_t)nrhs * NBW + (size_t)m0 * m0 + 2;
 }

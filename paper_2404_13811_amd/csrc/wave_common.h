@@ -385,8 +385,8 @@ __device__ __forceinline__ void wbuild(int nb, int j, const BoxLds& s, double w[
 //   S = A11 - U^T Z,  Q = S^{-1},  W10 = -Q Z^T,  W00 = P - Z W10,  W11 = Q
 // on the matrix instructions, the operands through two tiles of LDS (X^T Y
 // of accumulator layouts needs no transposition, Z^T takes one).
-// Bound: the two chains of pivots (16 and nb - 16, about 120 cycles each in
-// FP64) and the LDS round trips between them, 7,300 cycles at 24 cells.
+// Bound: the two chains of pivots (16, then 8 or 16, about 120 cycles each
+// in FP64) and the LDS round trips between them, 7,300 cycles at 24 cells.
 // Measured against four pivots per step on the vector unit with an LDS round
 // trip each (boxes of 24 x 24 cells, all of Steps 1-2 and 4): 256 boxes with
 // eight seeds 155 -> 136 us, 4096 with four 1226 -> 942 us; FP32 222 ->
