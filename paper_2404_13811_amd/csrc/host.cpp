@@ -100,6 +100,7 @@ struct mrcm_ctx {
   size_t lds32_basis = 0, lds32_part = 0, lds32_smooth = 0;
   int form32 = 0;  // their kernel class (wave32_form of the largest box)
   int nrhs32 = 1;  // most seeds of a box
+  int nblk_box = 1;  // most lines (planes) of an oversampled box
   float *fac32 = nullptr, *facp32 = nullptr;
   int* d_iters = nullptr;
   unsigned long long* d_resid = nullptr;
@@ -725,6 +726,7 @@ mrcm_status make_plan(mrcm_ctx* c) {
   c->sarr.bstride = (ncell + 1) / 2 * 2;
   c->sarr.fstride = 4 * (c->S[0] + c->S[1] + 4 * c->l);
   c->form32 = wave32_form(nb32, nblk32);
+  c->nblk_box = nblk32;
   // 3-D boxes: one wave per box with plane blocks of at most 64 cells
   c->d3 = c->d == 3;
   c->lds3_basis = c->lds3_part = c->lds3_smooth = 0;
@@ -1449,9 +1451,10 @@ mrcm_status sweep(mrcm_ctx* c, hipStream_t s, int nt, double* p, double* gflux, 
 }
 
 // Threads per box of the smoothing kernels: the requested value, or the
-// fastest of 64, 128 and 256 over timed sweeps on copies of the current
-// state; for 3-D boxes in the FP32 form, whether a box holds its plane
-// inverses in registers (the variants give identical results).
+// fastest of 64, 128 and 256 (those that can be, see below) over timed sweeps
+// on copies of the current state; for 3-D boxes in the FP32 form, whether a
+// box holds its plane inverses in registers (the variants give identical
+// results).
 mrcm_status tune_smoothing(mrcm_ctx* c, hipStream_t s) {
   if (c->smooth_nt) return MRCM_OK;
   const bool f3 = c->d3 && c->prec == MRCM_FP32_REFINE;
@@ -1467,9 +1470,15 @@ mrcm_status tune_smoothing(mrcm_ctx* c, hipStream_t s) {
   HIPCHK(c, hipEventRecord(c->ev[10], s));
   float best = 0.f;
   int best_nt = 256, best_var = 8;
-  // (each is the fastest somewhere, with resident factors: 1024 boxes of 24
-  // x 24 cells 38, 29 and 27 us per phase, 1024 of 3 x 3 5.9, 6.1 and 6.6)
-  const std::vector<int> cand = f3 ? std::vector<int>{8, 4, 2, 0} : std::vector<int>{64, 128, 256};
+  // With resident factors one wave per box is the fastest only where its
+  // two halves are two lines each at most (1024 boxes per phase, 64, 128 and
+  // 256 threads: 2 x 2 cells 5.5, 5.9 and 6.4 us, 10 x 2 5.1, 5.6 and 6.3,
+  // 4 x 4 6.3, 6.4 and 7.0, but 3 x 5 6.9, 6.7 and 7.3, 24 x 24 38, 29 and
+  // 27); elsewhere timing it would only lengthen the first call.
+  const bool wave64 = c->prec != MRCM_FP64 || !c->lds_smooth_res || c->nblk_box <= 4;
+  const std::vector<int> cand = f3       ? std::vector<int>{8, 4, 2, 0}
+                                : wave64 ? std::vector<int>{64, 128, 256}
+                                         : std::vector<int>{256, 128};
   for (int v : cand) {
     const int nt = f3 ? 256 : v;
     if (f3) c->smooth_cached = v;
