@@ -466,8 +466,11 @@ __device__ __forceinline__ double seed_face(const Geo& g, const Box& B, const Bo
   const int q = face_side(R.b.m0, R.b.m1, u, t), a = q >> 1;
   face_cells(B.lo[0], B.lo[1], B.hi[0], B.hi[1], q, t, x, y, ox, oy);
   if (off_domain(g, a, a == 0 ? x : y, a == 0 ? ox : oy)) return 0.0;
-  const double kc = kat(R.b, B, x, y, a);
-  return robin_T(g, kc, robin_beta(g, a, kc, kat(R.b, B, ox, oy, a), beta));
+  // the tile by value: a select between fields of R is one of addresses, and
+  // R then lives in scratch memory
+  const double *kx = R.b.Kt, *ky = R.b.Ky, *K = a == 0 ? kx : ky;
+  const double kc = K[tile_at(R.b, B, x, y)];
+  return robin_T(g, kc, robin_beta(g, a, kc, K[tile_at(R.b, B, ox, oy)], beta));
 }
 // The faces' T^R tabled in R.red + NT / 64 by kernels whose boxes have at
 // most 33 lines (LDS reserved by the host: kSeedTable bytes); longer boxes

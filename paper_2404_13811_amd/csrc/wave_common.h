@@ -128,7 +128,8 @@ __device__ __forceinline__ BlockSrc block_src(const double* Wg, int nb, int nblk
   for (int i = 0; i < HB; ++i) {
     const int r = HB * h + i;
     const int hi = r > c ? r : c, lo = r > c ? c : r;
-    b.off[i] = (r < nb && c < nb) ? (hi * (hi + 1) / 2 + lo) * (int)sizeof(double) : bytes;
+    const int idx = hi * (hi + 1) / 2 + lo;
+    b.off[i] = (r < nb && c < nb) ? idx * (int)sizeof(double) : bytes;
   }
   b.bbytes = __builtin_amdgcn_readfirstlane(bsz * (int)sizeof(double));
   return b;
@@ -223,12 +224,7 @@ __device__ __forceinline__ BoxLds carve(double* base, const Box& B, int nrhs, in
 }
 
 // The halo tile of axis a's permeability entries.
-// (Values: a select between fields is one of addresses, and the struct then
-// lives in scratch memory.)
-__device__ __forceinline__ const double* ktile(const BoxLds& s, int a) {
-  const double *kx = s.Kt, *ky = s.Ky;
-  return a == 0 ? kx : ky;
-}
+__device__ __forceinline__ const double* ktile(const BoxLds& s, int a) { return a == 0 ? s.Kt : s.Ky; }
 
 // K along axis a at global cell (x, y), which must lie in the box or its
 // halo.
