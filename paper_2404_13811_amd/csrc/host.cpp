@@ -96,7 +96,7 @@ struct mrcm_ctx {
   // (0: some box does not fit, the factors are streamed) and what it keeps
   // per box (FP64 contexts only)
   size_t lds_smooth_res = 0;
-  SmoothArrays sarr{nullptr, nullptr, nullptr, 0, 0};
+  SmoothArrays sarr{nullptr, nullptr, nullptr, 0};
   size_t lds32_basis = 0, lds32_part = 0, lds32_smooth = 0;
   int form32 = 0;  // their kernel class (wave32_form of the largest box)
   int nrhs32 = 1;  // most seeds of a box
@@ -715,15 +715,21 @@ mrcm_status make_plan(mrcm_ctx* c) {
   if (c->lds_basis > 150 * 1024 || c->lds_smooth > 150 * 1024 || 2 * c->lds_part + 16 > 150 * 1024)
     c->wave = false;
   if (!c->wave || c->lds_smooth_res > 150 * 1024) c->lds_smooth_res = 0;
-  int nb32 = 1, nblk32 = 1, ncell = 1;
+  int nb32 = 1, nblk32 = 1;
   c->nrhs32 = 1;
   for (const Box& B : c->obox) {
     c->nrhs32 = std::max(c->nrhs32, B.nrhs);
     nb32 = std::max(nb32, B.nb);
     nblk32 = std::max(nblk32, B.nblk);
-    ncell = std::max(ncell, B.ncell);
   }
-  c->sarr.bstride = (ncell + 1) / 2 * 2;
+  if (c->wave) {
+    // the wave kernels keep one vector per box, and none per seed
+    c->scro_n = 0;
+    for (Box& B : c->obox) {
+      B.scr = c->scro_n;
+      c->scro_n += (B.ncell + 1) / 2 * 2;
+    }
+  }
   c->sarr.fstride = 4 * (c->S[0] + c->S[1] + 4 * c->l);
   c->form32 = wave32_form(nb32, nblk32);
   c->nblk_box = nblk32;
@@ -1266,7 +1272,7 @@ mrcm_status mrcm_build_basis(mrcm_ctx* c) {
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev[9], s));
   } else if (c->wave) {
     if (c->lds_smooth_res) {
-      HIPCHK(c, grow(c->sarr.b0, (long long)c->geo.nsub * c->sarr.bstride));
+      HIPCHK(c, grow(c->sarr.b0, c->scro_n));
       HIPCHK(c, grow(c->sarr.fc, (long long)c->geo.nsub * c->sarr.fstride));
       HIPCHK(c, grow(c->sarr.gc, (long long)c->geo.nsub * c->geo.gstride));
     }

@@ -481,7 +481,7 @@ __device__ __forceinline__ void smooth_box_res(const Geo2& g, const Box& B, cons
   FaceIn first{0.0, 0.0, 0.0, 0.0};
   if (tid < ns) first = face_in(g, lo0, lo1, hi0, hi1, sub, tid, fc, p, gflux);
   stage_factors<NT>(B, Wf, Wt, img);
-  stage_lds<NT>(st.b0 + (long long)sub * st.bstride, X, nc);
+  stage_lds<NT>(st.b0 + B.scr, X, nc);
   stage_lds<NT>(tcoup + B.scr, Tn, nc);
   if (tid < ns) AF[tid] = face_add(g.l > 0, first);
 #pragma unroll 1
@@ -626,7 +626,7 @@ hipError_t set_lds(KF kern, size_t bytes) {
   return hipSuccess;
 }
 
-SmoothStatic statics(const SmoothArrays& a) { return SmoothStatic{a.b0, a.fc, a.gc, a.bstride, a.fstride}; }
+SmoothStatic statics(const SmoothArrays& a) { return SmoothStatic{a.b0, a.fc, a.gc, a.fstride}; }
 
 }  // namespace
 

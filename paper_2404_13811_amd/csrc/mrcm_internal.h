@@ -70,6 +70,7 @@ struct Box {
   int seed0;          // first global seed index (basis boxes)
   long long fac;      // element offset of the cached block inverses
   long long scr;      // element offset of this box's right-hand-side scratch
+                      // (2-D wave kernels: of its one vector of couplings)
 };
 
 // Seed Robin data on one side of an oversampled box, and (with the same
@@ -150,12 +151,12 @@ size_t wave_smooth_lds_bytes(int m0, int m1, int kc);
 size_t wave_smooth_res_lds_bytes(int m0, int m1);
 long long wave_packed_elems(int nb);
 // What smoothing keeps per box beside the factors (written with them; null:
-// not kept): the static right-hand side (bstride doubles per box, even), two
-// coefficients per box-side face (fstride doubles per box), one per Gamma
-// face (layout of the Gamma fluxes).
+// not kept): the static right-hand side (layout of the block couplings),
+// two coefficients per box-side face (fstride doubles per box), one per
+// Gamma face (layout of the Gamma fluxes).
 struct SmoothArrays {
   double *b0, *fc, *gc;
-  int bstride, fstride;
+  int fstride;
 };
 // Steps 1-2 (oversampled boxes obox) and Step 4 (subdomain boxes pbox, one
 // or two per workgroup) in one launch; lds_part = LDS of one subdomain box,

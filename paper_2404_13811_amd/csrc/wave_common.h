@@ -1483,7 +1483,7 @@ __device__ __forceinline__ void lds_sweep(const Box& B, const double* img, const
 // the pressures on both sides of the box sides, and no permeability.
 struct SmoothStatic {
   double *b0, *fc, *gc;
-  int bstride, fstride;  // doubles of b0 (even) and fc per box
+  int fstride;  // doubles of fc per box
 };
 
 __device__ __forceinline__ int face_off(int m0, int m1, int q) {
@@ -1513,7 +1513,7 @@ __device__ __forceinline__ void smooth_static(const Geo& g, const Box& B, const 
                                               const double* __restrict__ bcv, double beta,
                                               const SmoothStatic& st) {
   const int tid = threadIdx.x % NT, m0 = s.m0, m1 = s.m1;
-  physical_rhs<NT>(g, B, s, f, bcv, st.b0 + (long long)B.sub * st.bstride);
+  physical_rhs<NT>(g, B, s, f, bcv, st.b0 + B.scr);
   double* fc = st.fc + (long long)B.sub * st.fstride;
 #pragma unroll 1
   for (int u = tid; u < 2 * (m0 + m1); u += NT) {
