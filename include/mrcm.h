@@ -268,13 +268,14 @@ mrcm_status mrcm_smooth(mrcm_ctx* ctx, int nsteps);
  * the nsteps sweeps of an mrcm_smooth call (nsteps x 2^dim colour phases)
  * are captured into one HIP graph at the first call with that step count
  * after a configuration change, and replayed as one launch on the context's
- * stream.  threads_per_box: 64, 128 or 256 threads per
- * oversampled box, or 0 (default) to time those that can be the fastest for
- * the boxes' size over a copy of the current state and keep the fastest (done
- * once per configuration and precision form, outside the timed region of
- * mrcm_smooth).  The choice does not change the results.  3-D boxes take one to four waves by their plane size and ignore
- * threads_per_box; in the FP32 form the autotuner instead times how many
- * planes' inverses a box holds in registers (mrcm_stats.smooth_cached).
+ * stream.  threads_per_box: 64, 128 or 256 threads per oversampled box, or 0
+ * (default) to time those that can be the fastest for the boxes' size over a
+ * copy of the current state and keep the fastest (done once per configuration
+ * and precision form, outside the timed region of mrcm_smooth).  The choice
+ * does not change the results.  3-D boxes take one to four waves by their
+ * plane size and ignore threads_per_box; in the FP32 form the autotuner
+ * instead times how many planes' inverses a box holds in registers
+ * (mrcm_stats.smooth_cached).
  * Errors: MRCM_EINVAL. */
 mrcm_status mrcm_set_smoothing(mrcm_ctx* ctx, int use_graph, int threads_per_box);
 
