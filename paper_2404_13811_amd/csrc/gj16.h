@@ -42,7 +42,8 @@ __device__ __forceinline__ float row_bcast(float v) {
 // The first pivot's columns may have been written by the instruction before
 // (two wait states); later, five per asm block, always in this order, keep
 // the same distance between the write of a DPP operand and its read: a
-// column is read again at the earliest five instructions after its write.
+// column is read again at the earliest five instructions after its write
+// (tests/test_dpp_hazards.py checks the built code for it).
 template <int K, int J>
 __device__ __forceinline__ void pivot_update5(double a[16], double n) {
 #define MRCM_C(i) a[(K + J + i) & 15]

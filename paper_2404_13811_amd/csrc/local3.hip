@@ -14,9 +14,10 @@
 // 16v + 15 of the plane block (padded with the identity to 16 NW) as NW
 // 16 x 16 tiles in the accumulator layout of the FP64 matrix instructions,
 // so a box of 64-cell planes spreads its block over four waves (four SIMDs)
-// and smaller planes take fewer.  W_j is computed in place by the symmetric
-// sweep of 16 pivots at a time (sweep3); block-vector products of all
-// right-hand sides are matrix instructions on the same tiles.  Solves:
+// and smaller planes take one wave per 16 cells.  W_j is computed in place by
+// the symmetric sweep of 16 pivots at a time (sweep3); block-vector products
+// of the seeds are matrix instructions on the same tiles, of the particular
+// problem's one vector dot products.  Solves:
 //   forward   z_j = W_j (b_j + t_{j-1} .* z_{j-1})
 //   backward  x_j = z_j + W_j (t_j .* x_{j+1}).
 // The inverses are stored whole (nb x nb, row-major), the layout the
@@ -144,8 +145,8 @@ __device__ __forceinline__ void publish3(Gj3& sm, const dbl4 T[NW]) {
 // and of the block set-up, about three quarters of the kernel's time; the
 // rest is the chain of four pivot inverses per plane.  Measured against four
 // pivots per step on the vector unit (17,920 boxes of 8 x 8 x 8 cells):
-// six seeds 5.92 -> 4.84 ms, 18 seeds (4,480 boxes) 2.00 -> 1.46 ms, the
-// particular problems of 4 x 4 x 4 cells 0.37 -> 0.25 ms.
+// six seeds 5.92 -> 4.79 ms, 18 seeds (4,480 boxes) 2.00 -> 1.41 ms, the
+// particular problems of 4 x 4 x 4 cells 0.37 -> 0.22 ms.
 template <int NW, int P>
 __device__ __forceinline__ void sweep3_step(int nb, Gj3& sm, dbl4 T[NW], bool& bad) {
   if constexpr (P < NW) {

@@ -25,7 +25,7 @@
 // chain of 2 (nblk + 1) / 2 block steps of about 270 cycles per FP32 solve.
 // Measured against one wave per box eliminated from one end (24 x 24 cells,
 // three FP32 solves): Steps 1-2 and 4 of 256 boxes with eight seeds 690 ->
-// 178 us, of 4096 with four 3776 -> 1305 us; smoothing per phase 65 -> 28 us
+// 164 us, of 4096 with four 3776 -> 1182 us; smoothing per phase 65 -> 28 us
 // (64 boxes), 140 -> 66 us (1024 boxes).
 #include "wave32_common.h"
 
