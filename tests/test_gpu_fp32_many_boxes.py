@@ -1,6 +1,6 @@
 """FP32 Steps 1-2 and 4 where the boxes are many (two waves per box, inverses
-streamed) at the edges of that form: lines of 6 to 32 cells, odd and even,
-boxes of 6 to 32 lines, up to four and eight seeds.  A batch of eight members
+streamed) at the edges of that form: lines of 5 to 32 cells, odd and even,
+boxes of 3 to 32 lines, up to 4, 8 and 14 seeds.  A batch of eight members
 of 128 subdomains takes it, a member alone (four waves per box) does not:
 equal bits, and the member against the oracle at the FP32 form's bar (1e-6)."""
 import numpy as np
@@ -22,7 +22,7 @@ def _need_gpu():
 
 
 @pytest.mark.parametrize("sub,overlap,space", [
-    ((4, 4), 1, "const"), ((4, 4), 1, "linear"), ((9, 7), 2, "const"), ((8, 8), 1, "linear"),
+    ((4, 4), 1, "const"), ((4, 4), 1, "linear"), ((3, 4), 1, "fine"), ((9, 7), 2, "const"), ((8, 8), 1, "linear"),
     ((14, 15), 1, "const"), ((5, 30), 1, "const"), ((30, 5), 1, "linear"), ((32, 3), 0, "const")])
 def test_two_waves_per_box(sub, overlap, space):
     from gpu_util import oracle_solve, rel
